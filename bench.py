@@ -553,9 +553,9 @@ KERNELS = {  # record key -> (kernel name, box edge, bytes per fluid update, por
     "bf16": ("void lbm::k_step<2, 1, true, false, 4>", 512, 76, True, 1),
     "f64": ("void lbm::k_step<3, 1, true, false, 1>", 512, 304, True, 1),
     "f32x": ("void lbm::k_step<4, 1, true, false, 1>", 512, 152, True, 1),
-    "f32x2": ("void lbm::k_step2<0, 4, true, false, false>", 512, 152, True, 2),
-    "f16x2": ("void lbm::k_step2<1, 4, true, false, false>", 512, 76, True, 2),
-    "f64x2": ("void lbm::k_step2<3, 4, true, false, false>", 512, 304, True, 2),
+    "f32x2": ("void lbm::k_step2<0, 4, true, false, 0>", 512, 152, True, 2),
+    "f16x2": ("void lbm::k_step2<1, 4, true, false, 0>", 512, 76, True, 2),
+    "f64x2": ("void lbm::k_step2<3, 4, true, false, 0>", 512, 304, True, 2),
     "adjoint": ("void lbm::k_adj<false, false, false>", 256, 228, False, 1),  # periodic, no flags
 }
 
@@ -564,15 +564,21 @@ def launch_threads(name, n):
     """Threads a launch of the named kernel has on an n^3 box (64 * M-cell
     segments per row, four per block, M = 4 for the 16-bit step kernels; the
     two-step kernel: 64 x TY tiles (TY = 13; 5 for FP64, 8 for F32X), z
-    chunks of 128 planes halved down to 16 until there are 1280 blocks,
-    64 (TY + 3) threads per block)."""
+    chunks of the length with the least rounds of 256 blocks times planes
+    plus four, 64 (TY + 3) threads per block).  Recorded traces whose
+    two-step kernel ends in a truth value had z chunks of 128 planes halved
+    down to 16 until there were 1280 blocks."""
     if name.startswith("void lbm::k_step2<"):
-        k = int(name.split("<")[1].split(",")[0])
-        ty = {3: 5, 4: 8}.get(k, 13)
+        args = [a.strip() for a in name.split("<")[1].split(">")[0].split(",")]
+        ty = {"3": 5, "4": 8}.get(args[0], 13)
         tiles = -(-n // 64) * -(-n // ty)
-        zc = min(n, 128)
-        while zc > 16 and tiles * -(-n // zc) < 1280:
-            zc = max(zc // 2, 16)
+        if args[4] in ("true", "false"):
+            zc = min(n, 128)
+            while zc > 16 and tiles * -(-n // zc) < 1280:
+                zc = max(zc // 2, 16)
+        else:
+            lengths = sorted({-(-n // c) for c in range(1, n + 1)} - {1} or {1}, reverse=True)
+            zc = min(lengths, key=lambda z: -(-(tiles * -(-n // z)) // 256) * (z + 4))
         return tiles * -(-n // zc) * 64 * (ty + 3)
     m = 4 if name.startswith("void lbm::k_step<1,") or name.startswith("void lbm::k_step<2,") else 1
     nseg = -(-n // (64 * m))
@@ -581,8 +587,8 @@ def launch_threads(name, n):
 
 def box_of(name, grid):
     """The box edge of a launch from its grid size, trying the bench's own
-    sizes first: the two-step kernel's launches at 256^3 and 512^3 have the
-    same size (1280 blocks), and the bench runs it at 512^3 (and 768^3) on
+    sizes first: two boxes can give the two-step kernel launches of the same
+    size, and the bench runs it at 512^3 (and 768^3) on
     the porous box and at 256^3 (and 128^3) on the adjoint's periodic box,
     without solids (walls = 0)."""
     periodic2 = name.startswith("void lbm::k_step2<") and name.split("<")[1].split(",")[1].strip() == "0"
@@ -772,14 +778,16 @@ def trace_summary(trace_dir, bench_json):
     for key, label, ms in checks:
         name, spl = KERNELS[key][0], KERNELS[key][4]
         n = round(d["config"]["cells"] ** (1 / 3))
-        v = groups.get((name, launch_threads(name, n)), [])
+        v = []
+        for name in (name, name.replace(", 0>", ", false>")):  # as named here, or in older traces
+            v = v or groups.get((name, launch_threads(name, n)), [])
         wl, sl = warm // spl, steps // spl
         if ms and len(v) >= wl + sl:
             timed = v[wl:wl + sl]
             per = f"{spl} steps per launch, " if spl > 1 else ""
             out.append(f"{label}: the bench line reports {ms * spl * 1e3:.1f} us per launch "
                        f"({per}HIP events around {steps} timed steps); the trace's {sl} launches "
-                       f"after the {wl} warm-up launches of {name.replace('void ', '')} at {n}^3 "
+                       f"after the {wl} warm-up launches of {KERNELS[key][0].replace('void ', '')} at {n}^3 "
                        f"average {statistics.mean(timed):.1f} us.")
     print("\n".join(out))
     return 0

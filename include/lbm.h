@@ -162,7 +162,7 @@ typedef struct {
                              obstacle_kernel = 1 (LBM_E_UNSUPPORTED).
                              LBM_STEPS_AUTO: pairs where the fused pass fills
                              the GPU (at least 128 blocks of its tiles: from
-                             about 128^3 cells on), single steps elsewhere and
+                             about 64^3 cells on), single steps elsewhere and
                              with the split design -- the fastest schedule
                              measured, the same bits either way. */
 } lbm_params;

@@ -62,9 +62,11 @@ hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, cons
                         hipStream_t s);
 // Blocks a two-step launch has on this grid (its tiles and z chunks).
 int step2_blocks(int storage, const Geo& g);
-// Fewer blocks than this leave most CUs idle: single steps are faster there
-// (measured on periodic cubes: 112 blocks at 100^3 ran 22.0k MLUPS FP32
-// against 27.5k for single steps, 160 at 128^3 40.9k against 34.2k).
+// Fewer blocks than this leave most CUs idle, and single steps are faster
+// (periodic boxes, us a step, single / pairs: FP32 48^3, 96 blocks, 5.6 / 8.1;
+// 64^3, 160 blocks, 9.6 / 8.5; 96^3 28.6 / 21.2; FP64 32^3, 112 blocks, 4.3 /
+// 5.9; 48^3, 240 blocks, 9.1 / 6.6; FP16 48^3, 96 blocks, 5.6 / 6.1; 64^3 6.8 /
+// 6.3).
 constexpr int kStep2MinBlocks = 128;
 // The same two steps storing the intermediate level too: mid = f*(t+1)
 // (FP32 storage only: hipErrorInvalidValue otherwise).

@@ -608,9 +608,8 @@ __device__ __forceinline__ U pick(uint32_t sel, U a, U b) {
     return U(bfi32(sel, uint32_t(a), uint32_t(b)));
   }
 }
-constexpr int kTB2Chunk = 128;     // longest z chunk (planes per block)
-constexpr int kTB2MinChunk = 16;   // shortest z chunk
-constexpr int kTB2MinBlocks = 1280;  // five blocks per CU on 256 CUs
+constexpr int kTB2MinChunk = 2;  // shortest z chunk (planes per block)
+constexpr int kCUs = 256;
 
 // Tile rows per block: 13 (16 waves, 1024 threads, one block per CU: the
 // FP32 ring takes 127 KB of LDS) for 4- and 2-byte storage, which fit 128
@@ -677,9 +676,10 @@ __device__ __forceinline__ void store_nt_at(uint64_t base, uint32_t off, T v) {
   __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) T*>(base + off));
 }
 
-// MID: the intermediate level f*(t+1) is stored as well, into `mid` (each
-// cell by the block whose tile and chunk own it), for callers that need every
-// state -- the adjoint's recomputation between checkpoints.
+// OUT = kOutMid: the intermediate level f*(t+1) is stored as well, into `mid`
+// (each cell by the block whose tile and chunk own it), for callers that need
+// every state -- the adjoint's recomputation between checkpoints.
+constexpr int kOutLast = 0, kOutMid = 1;
 //
 // WALLS = 4 here (resting walls, with the link mask; in the single-step
 // kernel 4 is the pull-copy probe): the solid neighbours of a
@@ -690,7 +690,7 @@ __device__ __forceinline__ void store_nt_at(uint64_t base, uint32_t off, T v) {
 // its mask bit.  The same values reach the collision as with the markers,
 // so the results are the same bits.  The mask of a plane is loaded two
 // planes ahead.
-template <int K, int WALLS, bool FORCE, bool INC, bool MID>
+template <int K, int WALLS, bool FORCE, bool INC, int OUT>
 __global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
     const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ mid,
     typename Storage<K>::T* __restrict__ dst, const uint8_t* __restrict__ flags,
@@ -855,7 +855,7 @@ __global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
                   D3Q19::cx[i]) = v;
       }
     }
-    if constexpr (MID) {
+    if constexpr (OUT == kOutMid) {
       if (out_ok && p >= z0 && p < zend) {
         uint64_t base = uniform_opaque(reinterpret_cast<uint64_t>(mid));
 #pragma unroll
@@ -1626,29 +1626,41 @@ static Geo2 make_geo2(const Geo& g, int rows) {
   h.plane = g.plane;
   h.ntx = (g.nx + 63) / 64;
   h.nty = (g.ny + rows - 1) / rows;
-  // The longest z chunk (128, 64, 32, 16 planes) that still gives at least
-  // kTB2MinBlocks blocks, else 16: a chunk recomputes two planes of step 1,
-  // and fewer blocks than five per CU leave CUs idle (measured on periodic
-  // cubes: 256^3 runs 45.0k MLUPS FP32 with 128-plane chunks, 160 blocks,
-  // and 56.9k with 16-plane chunks, 1280 blocks; 512^3 runs best with 128).
-  h.zc = g.nz < kTB2Chunk ? g.nz : kTB2Chunk;
-  while (h.zc > kTB2MinChunk &&
-         int64_t(h.ntx) * h.nty * ((g.nz + h.zc - 1) / h.zc) < kTB2MinBlocks)
-    h.zc = h.zc / 2 > kTB2MinChunk ? h.zc / 2 : kTB2MinChunk;
+  // z chunks: one block fills a CU, so the blocks run in rounds of kCUs, and
+  // a block's time is its planes plus the two it recomputes plus about two
+  // planes of start-up -- measured 6.1-6.6 us a plane and round in FP32 from
+  // 128^3 to 512^3, 4.1-4.3 in BF16 and 4.6-4.8 in FP64, whatever the chunk.
+  // So the chunk length is the one with the least rounds * (planes + 4).
+  // (Against chunks of 128 planes halved down to 16 until there were 1280
+  // blocks: 128^3 FP32 103 -> 85 us a pass, 128 x 128 x 256 204 -> 155,
+  // 200^3 404 -> 329, 256^3 589 -> 541, 200^3 BF16 289 -> 225, 100^3 FP64
+  // 130 -> 84; 512^3 keeps its 128 planes.)
+  const int64_t tiles = int64_t(h.ntx) * h.nty;
+  int64_t best = INT64_MAX;
+  h.zc = g.nz;
+  for (int n = 1; n <= g.nz; ++n) {
+    const int zc = (g.nz + n - 1) / n;
+    if (zc < kTB2MinChunk && n > 1) break;
+    const int64_t rounds = (tiles * ((g.nz + zc - 1) / zc) + kCUs - 1) / kCUs;
+    if (rounds * (zc + 4) < best) {
+      best = rounds * (zc + 4);
+      h.zc = zc;
+    }
+  }
   const int nzc = (g.nz + h.zc - 1) / h.zc;
   h.nblocks = h.ntx * h.nty * nzc;
   h.nb8 = (h.nblocks / 8) * 8;
   return h;
 }
 
-template <int K, int WALLS, bool FORCE, bool INC, bool MID = false>
+template <int K, int WALLS, bool FORCE, bool INC, int OUT = kOutLast>
 static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s,
                     void* mid = nullptr) {
   using S = Storage<K>;
   constexpr int rows = tb2_rows<K>();
   const Geo2 h = make_geo2(g, rows);
-  hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, MID>), dim3(h.nblocks), dim3(64 * (rows + 3)),
+  hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT>), dim3(h.nblocks), dim3(64 * (rows + 3)),
                      0, s, reinterpret_cast<const typename S::T*>(src),
                      reinterpret_cast<typename S::T*>(mid), reinterpret_cast<typename S::T*>(dst),
                      flags, lmask, h, make_stepk<typename S::C>(ph));
@@ -1708,8 +1720,8 @@ hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, cons
 template <int WALLS, bool INC>
 static void step2_mid_f(bool force, const Geo& g, const PhysParams& ph, const void* src, void* mid,
                         void* dst, const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
-  if (force) step2_t<ST_F32, WALLS, true, INC, true>(g, ph, src, dst, flags, lmask, s, mid);
-  else step2_t<ST_F32, WALLS, false, INC, true>(g, ph, src, dst, flags, lmask, s, mid);
+  if (force) step2_t<ST_F32, WALLS, true, INC, kOutMid>(g, ph, src, dst, flags, lmask, s, mid);
+  else step2_t<ST_F32, WALLS, false, INC, kOutMid>(g, ph, src, dst, flags, lmask, s, mid);
 }
 
 template <bool INC>

@@ -99,6 +99,18 @@ def test_two_step_pass_is_bit_identical(storage, case):
             check_solids(two, kw["flags"])
 
 
+@pytest.mark.parametrize("nz", [2, 3, 5, 47, 131, 257])
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+def test_two_step_pass_chunk_edges(storage, nz):
+    """z extents whose chunks are one or two planes, or end in a short one:
+    the same bits as single steps."""
+    shape = (nz, 30, 130)
+    say("two-step pass, chunk edges", storage, shape)
+    fl = I.random_flags(shape, 41, solid_fraction=0.15, noforce_fraction=0.1)
+    one, two = _pair(shape, 0.6, (1e-5, 0, 0), storage, 4, flags=fl, u0=_u0(shape, 42))
+    assert _same(one, two)
+
+
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 def test_two_step_pass_unpadded_and_without_force(storage):
     shape = (6, 10, 65)
