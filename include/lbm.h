@@ -249,6 +249,20 @@ lbm_status lbm_step_from(lbm_ctx* ctx, const void* src, void* dst);
  * LBM_E_HIP. */
 lbm_status lbm_step2_from(lbm_ctx* ctx, const void* src, void* mid, void* dst);
 
+/* n >= 1 steps from an arbitrary grid `src` (f*(t)) into `dst` (f*(t+n)), with
+ * `tmp` (NULL if one pass does) as the other grid of the passes in between; src
+ * and the context's own grids and time are untouched.  pairs != 0: pairs of
+ * steps in fused passes, the odd step last; the same bits either way.  With
+ * `moments` (NULL: none) step k stores, in record k, what the adjoint needs of
+ * its pre-collision state f(t+k+1) = P f*(t+k): delta_rho, j_x, j_y, j_z, four
+ * FP32 arrays of dir_stride elements in the grid layout.  keep_last = 0: dst is
+ * scratch only and f*(t+n) is not stored.  src, tmp and dst are distinct,
+ * 256-byte aligned grids, moments is 256-byte aligned.  Errors: LBM_E_ARG,
+ * LBM_E_UNSUPPORTED (storage other than LBM_F32, or obstacle_kernel = 1),
+ * LBM_E_HIP. */
+lbm_status lbm_segment(lbm_ctx* ctx, const void* src, void* tmp, void* dst, int32_t n,
+                       int32_t pairs, float* moments, int32_t keep_last);
+
 /* Macroscopic fields of the current time level t from the stored f*(t):
  * the moments of Sec. 2 (density and momentum as the zeroth and first
  * moments of the populations, the quantities of the collision step),
@@ -339,6 +353,15 @@ lbm_status lbm_adjoint_seed(lbm_ctx* ctx, const void* fstar_prev, const float* d
  * lambda^n.  nu_n must differ from both inputs. */
 lbm_status lbm_adjoint_step(lbm_ctx* ctx, const void* fstar_prev, const float* nu_np1,
                             float* nu_n, double* dLdF_partials);
+
+/* The same from the n records of moments that lbm_segment stored for f(m+1) ..
+ * f(m+n), latest first: seed != 0 makes the first a seed (into nu_a), the
+ * others are reverse steps, alternating from nu_a to nu_b and back (nu_b NULL
+ * only for a seed alone).  The same nu and partials as lbm_adjoint_seed and
+ * lbm_adjoint_step, bit for bit, without their 19 pulls of f* per cell. */
+lbm_status lbm_adjoint_segment(lbm_ctx* ctx, const float* moments, int32_t n, int32_t seed,
+                               const float* dL_drho, const float* dL_du, float* nu_a, float* nu_b,
+                               double* dLdF_partials);
 
 /* Initial-state adjoint from nu^1: lambda^0 = P^T nu^1 (gathered as above),
  * dL/du0 = sum_i lambda^0_i d f^eq_i/du (rho0, u0), written as float

@@ -60,6 +60,8 @@ _SIGNATURES = {
     "lbm_restore": (_st, [_vp, _vp, C.c_int64]),
     "lbm_adjoint_seed": (_st, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "lbm_adjoint_step": (_st, [_vp, _vp, _vp, _vp, _vp]),
+    "lbm_segment": (_st, [_vp, _vp, _vp, _vp, C.c_int32, C.c_int32, _vp, C.c_int32]),
+    "lbm_adjoint_segment": (_st, [_vp, _vp, C.c_int32, C.c_int32, _vp, _vp, _vp, _vp, _vp]),
     "lbm_adjoint_init": (_st, [_vp, _vp, _vp, _vp, _vp]),
     "lbm_adjoint_finish_dF": (_st, [_vp, _vp, _vp]),
     "lbm_stream_copy": (_st, [_vp, _vp, C.c_size_t, _vp]),
@@ -163,6 +165,11 @@ def lbm_step2_from(ctx, src, mid, dst):
     check(lib().lbm_step2_from(ctx, src, mid, dst))
 
 
+def lbm_segment(ctx, src, tmp, dst, n, pairs, moments, keep_last):
+    check(lib().lbm_segment(ctx, src, tmp, dst, int(n), int(bool(pairs)), moments,
+                            int(bool(keep_last))))
+
+
 def lbm_macroscopics(ctx, rho, u):
     check(lib().lbm_macroscopics(ctx, rho, u))
 
@@ -213,6 +220,11 @@ def lbm_adjoint_seed(ctx, fstar_prev, dL_drho, dL_du, nu_T, partials):
 
 def lbm_adjoint_step(ctx, fstar_prev, nu_np1, nu_n, partials):
     check(lib().lbm_adjoint_step(ctx, fstar_prev, nu_np1, nu_n, partials))
+
+
+def lbm_adjoint_segment(ctx, moments, n, seed, dL_drho, dL_du, nu_a, nu_b, partials):
+    check(lib().lbm_adjoint_segment(ctx, moments, int(n), int(bool(seed)), dL_drho, dL_du, nu_a,
+                                    nu_b, partials))
 
 
 def lbm_adjoint_init(ctx, nu_1, rho0, u0, dL_du0):

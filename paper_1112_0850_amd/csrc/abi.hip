@@ -460,6 +460,52 @@ lbm_status lbm_step2_from(lbm_ctx* c, const void* src, void* mid, void* dst) {
   return e == hipSuccess ? LBM_OK : hip_fail(e, "two-step launch");
 }
 
+lbm_status lbm_segment(lbm_ctx* c, const void* src, void* tmp, void* dst, int32_t n, int32_t pairs,
+                       float* moments, int32_t keep_last) {
+  lbm_status st = check_ctx(c);
+  if (st != LBM_OK) return st;
+  if (n < 1) return fail(LBM_E_ARG, "step count must be >= 1 (got %d)", n);
+  if (!src || !dst) return fail(LBM_E_ARG, "src and dst must not be NULL");
+  if (!moments && !keep_last) return fail(LBM_E_ARG, "nothing to store: moments is NULL, keep_last 0");
+  if (c->p.storage != LBM_F32)
+    return fail(LBM_E_UNSUPPORTED, "lbm_segment needs FP32 storage");
+  if (c->p.obstacle_kernel)
+    return fail(LBM_E_UNSUPPORTED, "lbm_segment is not available with obstacle_kernel = 1");
+  // passes: pairs and then a single step, or single steps
+  const int32_t passes = pairs ? n / 2 + n % 2 : n;
+  if (passes > 1 && !tmp) return fail(LBM_E_ARG, "tmp must not be NULL for more than one pass");
+  if (src == dst || (tmp && (src == tmp || tmp == dst)))
+    return fail(LBM_E_ARG, "src, tmp and dst must differ");
+  if (!aligned256(src) || !aligned256(tmp) || !aligned256(dst) || !aligned256(moments))
+    return fail(LBM_E_ARG, "src/tmp/dst/moments must be 256-byte aligned");
+  const bool solids = c->flags != nullptr;
+  const size_t record = size_t(4) * c->sz.dir;
+  const void* from = src;
+  int32_t t = 0;
+  for (int32_t left = passes; left > 0; --left) {
+    void* to = left % 2 ? dst : tmp;  // the last pass writes dst
+    if (left == 1 && !keep_last) to = nullptr;
+    const bool two = pairs && t + 2 <= n;
+    hipError_t e;
+    if (!moments)
+      e = two ? lbm::launch_step2(c->p.storage, solids, c->force, c->geo, c->ph, from, to, c->flags,
+                                  c->lmask, c->stream)
+              : lbm::launch_step(c->p.storage, solids, c->force, c->geo, c->ph, from, to, c->flags,
+                                 c->stream);
+    else if (two)
+      e = lbm::launch_step2_mom(solids, c->force, c->geo, c->ph, static_cast<const float*>(from),
+                                static_cast<float*>(to), moments + record * t,
+                                moments + record * (t + 1), c->flags, c->lmask, c->stream);
+    else
+      e = lbm::launch_step_mom(solids, c->force, c->geo, c->ph, static_cast<const float*>(from),
+                               static_cast<float*>(to), moments + record * t, c->flags, c->stream);
+    if (e != hipSuccess) return hip_fail(e, "segment launch");
+    t += two ? 2 : 1;
+    from = to;
+  }
+  return LBM_OK;
+}
+
 static lbm_status macro_any(lbm_ctx* c, void* rho, void* u, bool f64) {
   lbm_status st = check_ctx(c);
   if (st != LBM_OK) return st;
@@ -588,6 +634,38 @@ lbm_status lbm_adjoint_step(lbm_ctx* c, const void* fstar_prev, const float* nu_
                                       static_cast<const float*>(fstar_prev), c->flags, nu_np1, nu_n,
                                       partials, c->stream);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "adjoint step launch");
+}
+
+lbm_status lbm_adjoint_segment(lbm_ctx* c, const float* moments, int32_t n, int32_t seed,
+                               const float* dL_drho, const float* dL_du, float* nu_a, float* nu_b,
+                               double* partials) {
+  lbm_status st = adj_check(c);
+  if (st != LBM_OK) return st;
+  if (n < 1) return fail(LBM_E_ARG, "state count must be >= 1 (got %d)", n);
+  if (!moments || !nu_a || !partials)
+    return fail(LBM_E_ARG, "moments, nu_a and partials must not be NULL");
+  if (!nu_b && n > (seed ? 1 : 0)) return fail(LBM_E_ARG, "nu_b must not be NULL for a reverse step");
+  if (nu_a == nu_b || moments == nu_a || moments == nu_b)
+    return fail(LBM_E_ARG, "moments, nu_a and nu_b must differ");
+  if (!aligned256(moments) || !aligned256(nu_a) || !aligned256(nu_b))
+    return fail(LBM_E_ARG, "moments, nu_a and nu_b must be 256-byte aligned");
+  const size_t record = size_t(4) * c->sz.dir;
+  float *from = nu_a, *to = nu_b;
+  for (int32_t m = n - 1; m >= 0; --m) {
+    hipError_t e;
+    if (seed && m == n - 1) {
+      e = lbm::launch_adj_mom(c->flags != nullptr, c->geo, c->ph, moments + record * m, c->flags,
+                              dL_drho, dL_du, nullptr, nu_a, partials, c->stream);
+    } else {
+      e = lbm::launch_adj_mom(c->flags != nullptr, c->geo, c->ph, moments + record * m, c->flags,
+                              nullptr, nullptr, from, to, partials, c->stream);
+      float* x = from;
+      from = to;
+      to = x;
+    }
+    if (e != hipSuccess) return hip_fail(e, "adjoint segment launch");
+  }
+  return LBM_OK;
 }
 
 lbm_status lbm_adjoint_init(lbm_ctx* c, const float* nu_1, const float* rho0, const float* u0,

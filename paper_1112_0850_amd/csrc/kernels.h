@@ -73,6 +73,15 @@ constexpr int kStep2MinBlocks = 128;
 hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,
                             const PhysParams& ph, const void* src, void* mid, void* dst,
                             const uint8_t* flags, const uint32_t* lmask, hipStream_t s);
+// One or two FP32 steps (not for the split design) that also store the moments
+// of the pre-collision states: four arrays in the grid layout per state.  A
+// null dst stores the moments only.
+hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+                           const float* src, float* dst, float* mom, const uint8_t* flags,
+                           hipStream_t s);
+hipError_t launch_step2_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+                            const float* src, float* dst, float* mom1, float* mom2,
+                            const uint8_t* flags, const uint32_t* lmask, hipStream_t s);
 // The two-step kernel's link mask of every cell ([nz][ny][nx] uint32) from the
 // flags: bit i (1..18) for a blocked pull along c_i, bits 19 and 20 for the
 // cell's own SOLID and NOFORCE flags.
@@ -92,6 +101,10 @@ hipError_t launch_adj_seed(bool solids, const Geo& g, const PhysParams& ph, cons
 hipError_t launch_adj_step(bool solids, const Geo& g, const PhysParams& ph, const float* fprev,
                            const uint8_t* flags, const float* nu_np1, float* nu_n,
                            double* partials, hipStream_t s);
+// The seed (nu1 null) or one reverse step from stored moments.
+hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const float* mom,
+                          const uint8_t* flags, const float* dL_drho, const float* dL_du,
+                          const float* nu1, float* nu0, double* partials, hipStream_t s);
 hipError_t launch_adj_init(bool solids, const Geo& g, const PhysParams& ph, const uint8_t* flags,
                            const float* nu1, const float* rho0, const float* u0, float* dL_du0,
                            hipStream_t s);

@@ -427,6 +427,15 @@ __device__ __forceinline__ void stream_store(T* p, T v) {
   __builtin_nontemporal_store(v, p);
 }
 
+// delta_rho and j of a pre-collision state into the four moment arrays (FP32,
+// pb bytes apart): all that the transposed collision needs of the state.
+__device__ __forceinline__ void store_moments(float* mom, size_t pb, uint32_t own, const float* f) {
+  float m[4];
+  moments(f, m[0], m[1], m[2], m[3]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) stream_store(elem(mom, pb, i, own), m[i]);
+}
+
 // Pins a collision result as a rounded FP32 register value before its FP16
 // store conversion.  Without it the compiler may fold the last fused
 // multiply-add and the conversion into one mixed-precision instruction that
@@ -456,11 +465,16 @@ struct StepCells {
   static constexpr int M = (K == ST_F16 || K == ST_BF16) ? 4 : 1;
 };
 
-template <int K, int WALLS, bool FORCE, bool INC, int M>
-__global__ __launch_bounds__(kBlock) void k_step(const typename Storage<K>::T* __restrict__ src,
-                                                 typename Storage<K>::T* __restrict__ dst,
-                                                 const uint8_t* __restrict__ flags, Geo g,
-                                                 StepK<typename Storage<K>::C> k) {
+//
+// MOM: delta_rho and j of the pulled (pre-collision) state are stored as well,
+// into mom[4] (direction arrays of the grid layout), for the adjoint; with a
+// null dst only they are.
+template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM>
+__device__ __forceinline__ void step_body(const typename Storage<K>::T* __restrict__ src,
+                                          typename Storage<K>::T* __restrict__ dst,
+                                          const uint8_t* __restrict__ flags,
+                                          float* __restrict__ mom, const Geo& g,
+                                          const StepK<typename Storage<K>::C>& k) {
   using C = typename Storage<K>::C;
   using T = typename Storage<K>::T;
   constexpr bool SCALED = (K == ST_F16);
@@ -531,6 +545,11 @@ __global__ __launch_bounds__(kBlock) void k_step(const typename Storage<K>::T* _
         }
     }
   }
+  if constexpr (MOM) {
+    static_assert(M == 1 && K == ST_F32, "moments of FP32 grids, one cell per lane");
+    if (valid[0]) store_moments(mom, pb, n[0].own, f[0]);
+    if (!dst) return;
+  }
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     // Solid lanes run the collision on their (meaningless) pulls and discard it.
@@ -550,6 +569,23 @@ __global__ __launch_bounds__(kBlock) void k_step(const typename Storage<K>::T* _
       }
     }
   }
+}
+
+template <int K, int WALLS, bool FORCE, bool INC, int M>
+__global__ __launch_bounds__(kBlock) void k_step(const typename Storage<K>::T* __restrict__ src,
+                                                 typename Storage<K>::T* __restrict__ dst,
+                                                 const uint8_t* __restrict__ flags, Geo g,
+                                                 StepK<typename Storage<K>::C> k) {
+  step_body<K, WALLS, FORCE, INC, M, false>(src, dst, flags, nullptr, g, k);
+}
+
+template <int WALLS, bool FORCE, bool INC>
+__global__ __launch_bounds__(kBlock) void k_step_mom(const float* __restrict__ src,
+                                                     float* __restrict__ dst,
+                                                     const uint8_t* __restrict__ flags,
+                                                     float* __restrict__ mom, Geo g,
+                                                     StepK<float> k) {
+  step_body<ST_F32, WALLS, FORCE, INC, 1, true>(src, dst, flags, mom, g, k);
 }
 
 // ---------------------------------------------------------------------------
@@ -678,8 +714,10 @@ __device__ __forceinline__ void store_nt_at(uint64_t base, uint32_t off, T v) {
 
 // OUT = kOutMid: the intermediate level f*(t+1) is stored as well, into `mid`
 // (each cell by the block whose tile and chunk own it), for callers that need
-// every state -- the adjoint's recomputation between checkpoints.
-constexpr int kOutLast = 0, kOutMid = 1;
+// every state.  OUT = kOutMoments: the moments of both steps' pre-collision
+// states are stored, into mid (the first step's four arrays) and mom2 (the
+// second's), for the adjoint; with a null dst f*(t+2) is not.
+constexpr int kOutLast = 0, kOutMid = 1, kOutMoments = 2;
 //
 // WALLS = 4 here (resting walls, with the link mask; in the single-step
 // kernel 4 is the pull-copy probe): the solid neighbours of a
@@ -693,7 +731,8 @@ constexpr int kOutLast = 0, kOutMid = 1;
 template <int K, int WALLS, bool FORCE, bool INC, int OUT>
 __global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
     const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ mid,
-    typename Storage<K>::T* __restrict__ dst, const uint8_t* __restrict__ flags,
+    float* __restrict__ mom2, typename Storage<K>::T* __restrict__ dst,
+    const uint8_t* __restrict__ flags,
     const uint32_t* __restrict__ lmask, Geo2 g, StepK<typename Storage<K>::C> k) {
   using C = typename Storage<K>::C;
   using T = typename Storage<K>::T;
@@ -835,6 +874,9 @@ __global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
         if (i + 2 < Q) base = uniform_opaque(bo + pb);
       }
     }
+    if constexpr (OUT == kOutMoments) {
+      if (out_ok && p >= z0 && p < zend) store_moments(mid, pb, ownb / SZ, f);
+    }
     if (FORCE && SOLIDS)
       collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, (fl & FLAG_NOFORCE) ? C(0) : C(1));
     else
@@ -894,12 +936,15 @@ __global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
           h[i] = C(from_bits<K>(pick<typename Storage<K>::U>(
               link_sel(m_step2, i), raw_bits<K>(prevv[D3Q19::opp[i]]), raw_bits<K>(w))));
       }
+      if constexpr (OUT == kOutMoments) {
+        if (out_ok) store_moments(mom2, pb, qownb / SZ, h);
+      }
       if (FORCE && SOLIDS)
         collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, (fl_prev & FLAG_NOFORCE) ? C(0) : C(1));
       else
         collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, C(1));
       const T marker2 = solid_marker<K>(fl_prev, WALLS == 2);
-      if (out_ok) {
+      if (out_ok && (OUT != kOutMoments || dst)) {
         uint64_t base = uniform_opaque(dst_u);
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
@@ -1211,15 +1256,20 @@ __device__ __forceinline__ LamMoments lam_moments(const float* lam) {
 // the same transposed collision; the initial step gathers lambda^0 = P^T nu^1.
 // The solid cells of a nu grid hold the resting marker, written by the
 // solid lanes, so both gathers test markers as the forward pull does.
-template <bool SOLIDS, bool MOVING, bool SEED>
-__global__ __launch_bounds__(kBlock) void k_adj(const float* __restrict__ fprev,
-                                                const float* __restrict__ nu1,
-                                                float* __restrict__ nu0,
-                                                const uint8_t* __restrict__ flags,
-                                                const float* __restrict__ gr,
-                                                const float* __restrict__ gu,
-                                                double* __restrict__ partials, Geo g,
-                                                Phys<float> ph) {
+//
+// The transposed collision needs the moments of f(n) only.  MOMS: they are read
+// from the four arrays that the forward pass stored (store_moments, the same
+// FP32 sums), 16 B per cell in place of the 19 pulls of f*(n-1) (76 B): 168 B
+// per reverse step instead of 228, and the same bits.  Bound by HBM: 128^3 86 ->
+// 63 us a step (5.6 TB/s), 72 x 80 x 100 porous 36 -> 29 us; the pair pass pays
+// 98 us instead of 88 at 128^3 for storing the moments of its two steps.
+template <bool SOLIDS, bool MOVING, bool SEED, bool MOMS>
+__device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
+                                         const float* __restrict__ nu1, float* __restrict__ nu0,
+                                         const uint8_t* __restrict__ flags,
+                                         const float* __restrict__ gr, const float* __restrict__ gu,
+                                         double* __restrict__ partials, const Geo& g,
+                                         const Phys<float>& ph) {
   using U = Storage<ST_F32>::U;
   __shared__ double sh[3 * kBlock];
   double d[3] = {0.0, 0.0, 0.0};
@@ -1247,26 +1297,35 @@ __global__ __launch_bounds__(kBlock) void k_adj(const float* __restrict__ fprev,
     const uint8_t fl = SOLIDS ? flags[n.fown] : uint8_t(0);
     const bool solid = SOLIDS && (fl & FLAG_SOLID);
     const size_t pb = size_t(g.plane) * sizeof(float);
-    // f(n) = P f*(n-1), exactly as the forward pull
-    float f[Q];
-    bool mk[Q], mv[Q];
+    float drho, jx, jy, jz;
+    if constexpr (MOMS) {
+      drho = *elem(fprev, pb, 0, n.own);
+      jx = *elem(fprev, pb, 1, n.own);
+      jy = *elem(fprev, pb, 2, n.own);
+      jz = *elem(fprev, pb, 3, n.own);
+    } else {
+      // f(n) = P f*(n-1), exactly as the forward pull
+      float f[Q];
+      bool mk[Q], mv[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      const float v = *elem_rx(fprev, pb, i, src_row(n, i), src_x(n, i));
-      const U r = raw_bits<ST_F32>(v);
-      mk[i] = SOLIDS && i != 0 && (MOVING ? (r | 1u) == Storage<ST_F32>::kMoving
-                                         : r == Storage<ST_F32>::kRest);
-      mv[i] = MOVING && i != 0 && r == Storage<ST_F32>::kMoving;
-      f[i] = v;
-    }
-    if (SOLIDS) {
+      for (int i = 0; i < Q; ++i) {
+        const float v = *elem_rx(fprev, pb, i, src_row(n, i), src_x(n, i));
+        const U r = raw_bits<ST_F32>(v);
+        mk[i] = SOLIDS && i != 0 && (MOVING ? (r | 1u) == Storage<ST_F32>::kMoving
+                                           : r == Storage<ST_F32>::kRest);
+        mv[i] = MOVING && i != 0 && r == Storage<ST_F32>::kMoving;
+        f[i] = v;
+      }
+      if (SOLIDS) {
 #pragma unroll
-      for (int i = 1; i < Q; ++i)
-        if (mk[i] && !solid) {
-          float v = *elem_rx(fprev, pb, D3Q19::opp[i], n.row[1][1], n.xn[1]);
-          if (MOVING && mv[i]) v += ph.Kw[i];
-          f[i] = v;
-        }
+        for (int i = 1; i < Q; ++i)
+          if (mk[i] && !solid) {
+            float v = *elem_rx(fprev, pb, D3Q19::opp[i], n.row[1][1], n.xn[1]);
+            if (MOVING && mv[i]) v += ph.Kw[i];
+            f[i] = v;
+          }
+      }
+      moments(f, drho, jx, jy, jz);
     }
     float lam[Q];
     if (!SEED) {
@@ -1291,8 +1350,6 @@ __global__ __launch_bounds__(kBlock) void k_adj(const float* __restrict__ fprev,
     const bool forced = !(fl & FLAG_NOFORCE);
     const float Fx = forced ? ph.F[0] : 0.0f, Fy = forced ? ph.F[1] : 0.0f,
                 Fz = forced ? ph.F[2] : 0.0f;
-    float drho, jx, jy, jz;
-    moments(f, drho, jx, jy, jz);
     const bool inc = ph.incomp != 0;
     const float rho = inc ? 1.0f : 1.0f + drho;  // the density dividing j' in u
     const float inv_rho = inc ? 1.0f : 1.0f / rho;
@@ -1357,6 +1414,30 @@ __global__ __launch_bounds__(kBlock) void k_adj(const float* __restrict__ fprev,
       if (SEED) partials[size_t(lb) * 3 + k] = d[k];
       else partials[size_t(lb) * 3 + k] += d[k];
     }
+}
+
+template <bool SOLIDS, bool MOVING, bool SEED>
+__global__ __launch_bounds__(kBlock) void k_adj(const float* __restrict__ fprev,
+                                                const float* __restrict__ nu1,
+                                                float* __restrict__ nu0,
+                                                const uint8_t* __restrict__ flags,
+                                                const float* __restrict__ gr,
+                                                const float* __restrict__ gu,
+                                                double* __restrict__ partials, Geo g,
+                                                Phys<float> ph) {
+  adj_body<SOLIDS, MOVING, SEED, false>(fprev, nu1, nu0, flags, gr, gu, partials, g, ph);
+}
+
+template <bool SOLIDS, bool SEED>
+__global__ __launch_bounds__(kBlock) void k_adj_mom(const float* __restrict__ mom,
+                                                    const float* __restrict__ nu1,
+                                                    float* __restrict__ nu0,
+                                                    const uint8_t* __restrict__ flags,
+                                                    const float* __restrict__ gr,
+                                                    const float* __restrict__ gu,
+                                                    double* __restrict__ partials, Geo g,
+                                                    Phys<float> ph) {
+  adj_body<SOLIDS, false, SEED, true>(mom, nu1, nu0, flags, gr, gu, partials, g, ph);
 }
 
 // dL/du0 = sum_i lam0_i w_i rho0 (3 c_i + 9 (c_i.u0) c_i - 3 u0) = rho0 (3 L1 + 9 L2 u0 - 3 u0 L0),
@@ -1596,6 +1677,36 @@ static void step_w(bool solids, bool force, const Geo& g, const PhysParams& ph, 
   else step_f<K, 2, INC>(force, g, ph, src, dst, flags, s);
 }
 
+// One FP32 step storing the moments of its pre-collision state as well.
+template <int WALLS, bool INC>
+static void step_mom_f(bool force, const Geo& g, const PhysParams& ph, const float* src, float* dst,
+                       float* mom, const uint8_t* flags, hipStream_t s) {
+  const Geo h = step_geo(g, 1);
+  const StepK<float> k = make_stepk<float>(ph);
+  if (force)
+    hipLaunchKernelGGL((k_step_mom<WALLS, true, INC>), dim3(h.nblocks), dim3(kBlock), 0, s, src, dst,
+                       flags, mom, h, k);
+  else
+    hipLaunchKernelGGL((k_step_mom<WALLS, false, INC>), dim3(h.nblocks), dim3(kBlock), 0, s, src,
+                       dst, flags, mom, h, k);
+}
+
+template <bool INC>
+static void step_mom_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const float* src,
+                       float* dst, float* mom, const uint8_t* flags, hipStream_t s) {
+  if (!solids) step_mom_f<0, INC>(force, g, ph, src, dst, mom, flags, s);
+  else if (!ph.moving) step_mom_f<1, INC>(force, g, ph, src, dst, mom, flags, s);
+  else step_mom_f<2, INC>(force, g, ph, src, dst, mom, flags, s);
+}
+
+hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+                           const float* src, float* dst, float* mom, const uint8_t* flags,
+                           hipStream_t s) {
+  if (ph.incomp) step_mom_w<true>(solids, force, g, ph, src, dst, mom, flags, s);
+  else step_mom_w<false>(solids, force, g, ph, src, dst, mom, flags, s);
+  return hipGetLastError();
+}
+
 template <int K>
 static void step_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
                    void* dst, const uint8_t* flags, hipStream_t s) {
@@ -1656,14 +1767,14 @@ static Geo2 make_geo2(const Geo& g, int rows) {
 template <int K, int WALLS, bool FORCE, bool INC, int OUT = kOutLast>
 static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s,
-                    void* mid = nullptr) {
+                    void* mid = nullptr, float* mom2 = nullptr) {
   using S = Storage<K>;
   constexpr int rows = tb2_rows<K>();
   const Geo2 h = make_geo2(g, rows);
   hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT>), dim3(h.nblocks), dim3(64 * (rows + 3)),
                      0, s, reinterpret_cast<const typename S::T*>(src),
-                     reinterpret_cast<typename S::T*>(mid), reinterpret_cast<typename S::T*>(dst),
-                     flags, lmask, h, make_stepk<typename S::C>(ph));
+                     reinterpret_cast<typename S::T*>(mid), mom2,
+                     reinterpret_cast<typename S::T*>(dst), flags, lmask, h, make_stepk<typename S::C>(ph));
 }
 
 template <int K, int WALLS, bool INC>
@@ -1715,31 +1826,44 @@ hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, cons
   return hipGetLastError();
 }
 
-// Two fused steps that also store the intermediate level (FP32 storage, the
-// adjoint's storage): src = f*(t) -> mid = f*(t+1), dst = f*(t+2).
-template <int WALLS, bool INC>
-static void step2_mid_f(bool force, const Geo& g, const PhysParams& ph, const void* src, void* mid,
-                        void* dst, const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
-  if (force) step2_t<ST_F32, WALLS, true, INC, kOutMid>(g, ph, src, dst, flags, lmask, s, mid);
-  else step2_t<ST_F32, WALLS, false, INC, kOutMid>(g, ph, src, dst, flags, lmask, s, mid);
+// Two fused FP32 steps that also store the intermediate level (OUT = kOutMid:
+// src = f*(t) -> mid = f*(t+1), dst = f*(t+2)) or the moments of both
+// pre-collision states (OUT = kOutMoments: into mid and mom2).
+template <int OUT, int WALLS, bool INC>
+static void step2_out_f(bool force, const Geo& g, const PhysParams& ph, const void* src, void* mid,
+                        float* mom2, void* dst, const uint8_t* flags, const uint32_t* lmask,
+                        hipStream_t s) {
+  if (force) step2_t<ST_F32, WALLS, true, INC, OUT>(g, ph, src, dst, flags, lmask, s, mid, mom2);
+  else step2_t<ST_F32, WALLS, false, INC, OUT>(g, ph, src, dst, flags, lmask, s, mid, mom2);
 }
 
-template <bool INC>
-static void step2_mid_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
-                        const void* src, void* mid, void* dst, const uint8_t* flags,
+template <int OUT, bool INC>
+static void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
+                        const void* src, void* mid, float* mom2, void* dst, const uint8_t* flags,
                         const uint32_t* lmask, hipStream_t s) {
-  if (!solids) step2_mid_f<0, INC>(force, g, ph, src, mid, dst, flags, lmask, s);
-  else if (!ph.moving && lmask) step2_mid_f<4, INC>(force, g, ph, src, mid, dst, flags, lmask, s);
-  else if (!ph.moving) step2_mid_f<1, INC>(force, g, ph, src, mid, dst, flags, lmask, s);
-  else step2_mid_f<2, INC>(force, g, ph, src, mid, dst, flags, lmask, s);
+  if (!solids) step2_out_f<OUT, 0, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
+  else if (!ph.moving && lmask)
+    step2_out_f<OUT, 4, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
+  else if (!ph.moving) step2_out_f<OUT, 1, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
+  else step2_out_f<OUT, 2, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
 }
 
 hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,
                             const PhysParams& ph, const void* src, void* mid, void* dst,
                             const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (storage != ST_F32) return hipErrorInvalidValue;
-  if (ph.incomp) step2_mid_w<true>(solids, force, g, ph, src, mid, dst, flags, lmask, s);
-  else step2_mid_w<false>(solids, force, g, ph, src, mid, dst, flags, lmask, s);
+  if (ph.incomp)
+    step2_out_w<kOutMid, true>(solids, force, g, ph, src, mid, nullptr, dst, flags, lmask, s);
+  else step2_out_w<kOutMid, false>(solids, force, g, ph, src, mid, nullptr, dst, flags, lmask, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_step2_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+                            const float* src, float* dst, float* mom1, float* mom2,
+                            const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
+  if (ph.incomp)
+    step2_out_w<kOutMoments, true>(solids, force, g, ph, src, mom1, mom2, dst, flags, lmask, s);
+  else step2_out_w<kOutMoments, false>(solids, force, g, ph, src, mom1, mom2, dst, flags, lmask, s);
   return hipGetLastError();
 }
 
@@ -1875,6 +1999,21 @@ hipError_t launch_adj_step(bool solids, const Geo& g, const PhysParams& ph, cons
                            const uint8_t* flags, const float* nu_np1, float* nu_n,
                            double* partials, hipStream_t s) {
   adj_t<false>(solids, g, ph, fprev, nu_np1, nu_n, flags, nullptr, nullptr, partials, s);
+  return hipGetLastError();
+}
+
+// The same from stored moments (see store_moments): nu1 null for the seed.
+hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const float* mom,
+                          const uint8_t* flags, const float* dL_drho, const float* dL_du,
+                          const float* nu1, float* nu0, double* partials, hipStream_t s) {
+  const Geo h = step_geo(g, 1);
+  const Phys<float> p = to_phys<float>(ph);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s, mom, nu1, nu0, flags, dL_drho,
+                       dL_du, partials, h, p);
+  };
+  if (solids) nu1 ? go(k_adj_mom<true, false>) : go(k_adj_mom<true, true>);
+  else nu1 ? go(k_adj_mom<false, false>) : go(k_adj_mom<false, true>);
   return hipGetLastError();
 }
 

@@ -203,36 +203,56 @@ def copy_probe(dst, src, vec_per_thread=1, nontemporal=False, blocks=0, stream=N
                      blocks, ctypes.c_void_p(s.cuda_stream))
 
 
-# The reverse sweep recomputes two states per fused pass (lbm_step2_from)
-# from this many cells on: measured, the backward runs 3% faster at 256^3
-# and 6% slower at 128^3, where the pass has too few blocks to fill the GPU.
-FUSED_RECOMPUTE_MIN_CELLS = 1 << 24
+# The rollout steps in fused pairs from this many cells on, forward and in the
+# recomputation (the same states bit for bit): measured, single / pairs, 48^3
+# 5.6 / 8.1 us a step, 64^3 9.6 / 8.5, 128^3 61 / 42, 256^3 457 / 271.
+FUSED_RECOMPUTE_MIN_CELLS = 1 << 18
 
 
 class _Rollout(torch.autograd.Function):
     """(rho_T, u_T) after `steps` updates from f*(0) = f^eq(1, u0) under the
     body force g; backward runs the hand-written adjoint kernels with forward
-    checkpoints every k steps and recomputation inside each segment."""
+    checkpoints every k steps.  The reverse step n needs of the state f(n) its
+    moments only (16 B per cell and step); the forward sweep stores them for
+    the last segment, the others are recomputed from their checkpoints."""
 
     @staticmethod
-    def forward(ctx, u0, g, steps, tau, flags, k, wall_u, equilibrium, steps_per_pass):
+    def forward(ctx, u0, g, steps, tau, flags, k, wall_u, equilibrium, steps_per_pass, need_grad):
         force = [float(v) for v in g.detach().double().cpu().tolist()]
+        fused = math.prod(u0.shape[1:]) >= FUSED_RECOMPUTE_MIN_CELLS
         sim = LBM(u0.shape[1:], tau, force, "f32", flags=flags, u0=u0.detach(), device=u0.device,
-                  wall_u=wall_u, equilibrium=equilibrium, steps_per_pass=steps_per_pass)
-        ckpts = []
-        for t in range(0, steps, k):  # a checkpoint at the start of every segment of k steps
-            ckpts.append(sim.save())
-            sim.step(min(k, steps - t))
+                  wall_u=wall_u, equilibrium=equilibrium,
+                  steps_per_pass=2 if fused and steps_per_pass in (-1, 0, 1) else steps_per_pass)
+        if not need_grad:
+            sim.step(steps)
+            return sim.macroscopics()
+        pairs = fused or steps_per_pass == 2
+        starts = range(0, steps, k)  # a checkpoint at the start of every segment of k steps
+        ckpts = [sim.grids[0]]
+        tmp = sim.new_grid()
+        last = len(starts) - 1
+        for s, t in enumerate(starts):
+            n = min(k, steps - t)
+            dst = sim.grids[1] if s == last else sim.new_grid()
+            mom = _Rollout.moments(sim, n) if s == last else None
+            A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(tmp), _ptr(dst), n, pairs, _ptr(mom), True)
+            ckpts.append(dst)
+        sim.set_current(1, steps)
         rho, u = sim.macroscopics()
-        ctx.sim, ctx.ckpts, ctx.steps, ctx.k = sim, ckpts, steps, k
+        ctx.sim, ctx.ckpts, ctx.steps, ctx.k = sim, ckpts[:-1], steps, k
+        ctx.tmp, ctx.mom, ctx.fused = tmp, mom, fused
         ctx.g_meta = (g.dtype, g.device)
         return rho, u
 
     @staticmethod
+    def moments(sim, n):
+        return torch.empty(n * 4 * sim.dir_stride, dtype=torch.float32, device=sim.device)
+
+    @staticmethod
     def backward(ctx, g_rho, g_u):
-        """Reverse sweep in pull form: nu^T from the seed at f*(T-1), then
-        nu^{m+1} from nu^{m+2} at f*(m) for m = T-2 .. 0, then dL/du0 from
-        nu^1; the f*(m) are recomputed segment by segment from the
+        """Reverse sweep in pull form: nu^T from the seed at f(T), then nu^n
+        from nu^{n+1} at f(n) for n = T-1 .. 1, then dL/du0 from nu^1; the
+        moments of the f(n) are recomputed segment by segment from the
         checkpoints, latest segment first."""
         sim, ckpts, steps, k = ctx.sim, ctx.ckpts, ctx.steps, ctx.k
         dev = sim.device
@@ -241,34 +261,26 @@ class _Rollout(torch.autograd.Function):
         partials = torch.empty(sim.adj_partials_bytes // 8, dtype=torch.float64, device=dev)
         gr = None if g_rho is None else g_rho.to(torch.float32).contiguous()
         gu = None if g_u is None else g_u.to(torch.float32).contiguous()
-        cur = 0
-        seg = [None] + [sim.new_grid() for _ in range(min(k, steps) - 1)]
-        fused = math.prod(sim.shape) >= FUSED_RECOMPUTE_MIN_CELLS
+        cur, mom = 0, None
         for s in range(len(ckpts) - 1, -1, -1):
-            t0, t1 = s * k, min(s * k + k, steps)
-            seg[0] = ckpts[s]
-            j = 1
-            while j < t1 - t0:  # recompute the segment's states
-                if fused and j + 1 < t1 - t0:  # two states per pass
-                    sim.step2_from(seg[j - 1], seg[j], seg[j + 1])
-                    j += 2
-                else:
-                    sim.step_from(seg[j - 1], seg[j])
-                    j += 1
-            for m in range(t1 - 1, t0 - 1, -1):  # f*(m) gives nu^{m+1}
-                if m == steps - 1:
-                    A.lbm_adjoint_seed(sim.ctx, _ptr(seg[m - t0]), _ptr(gr), _ptr(gu),
-                                       _ptr(nu[cur]), _ptr(partials))
-                else:
-                    A.lbm_adjoint_step(sim.ctx, _ptr(seg[m - t0]), _ptr(nu[cur]),
-                                       _ptr(nu[cur ^ 1]), _ptr(partials))
-                    cur ^= 1
+            seed = s == len(ckpts) - 1
+            n = min(k, steps - s * k)
+            if seed:
+                seg = ctx.mom
+            else:
+                mom = _Rollout.moments(sim, k) if mom is None else mom
+                seg = mom
+                A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(ctx.tmp), _ptr(sim.grids[1]), n,
+                              ctx.fused, _ptr(seg), False)
+            A.lbm_adjoint_segment(sim.ctx, _ptr(seg), n, seed, _ptr(gr), _ptr(gu), _ptr(nu[cur]),
+                                  _ptr(nu[cur ^ 1]), _ptr(partials))
+            cur ^= (n - seed) & 1
         du0 = torch.empty((3,) + sim.shape, dtype=torch.float32, device=dev)
         A.lbm_adjoint_init(sim.ctx, _ptr(nu[cur]), _ptr(sim.rho0), _ptr(sim.u0), _ptr(du0))
         dF = torch.empty(3, dtype=torch.float64, device=dev)
         A.lbm_adjoint_finish_dF(sim.ctx, _ptr(partials), _ptr(dF))
         gdt, gdev = ctx.g_meta
-        return du0, dF.to(device=gdev, dtype=gdt), None, None, None, None, None, None, None
+        return (du0, dF.to(device=gdev, dtype=gdt)) + (None,) * 8
 
 
 def rollout(u0, g, *, steps, tau, flags=None, checkpoint_every=20, wall_u=(0.0, 0.0, 0.0),
@@ -277,9 +289,9 @@ def rollout(u0, g, *, steps, tau, flags=None, checkpoint_every=20, wall_u=(0.0, 
     with gradients for the initial velocity ``u0`` [3, nz, ny, nx] and the
     body-force density ``g`` [3].  Moving walls and the incompressible
     equilibrium are supported (no gradient for the wall velocity).
-    ``steps_per_pass=2`` runs the forward sweep in fused pairs of steps (the
-    same states bit for bit, so the same gradients); the reverse sweep
-    recomputes single states between checkpoints either way."""
+    ``steps_per_pass=2`` runs the forward sweep in fused pairs of steps on
+    every box, not only where they are faster (the same states bit for bit, so
+    the same gradients)."""
     if u0.dim() != 4 or u0.shape[0] != 3:
         raise ValueError("u0 must be [3, nz, ny, nx]")
     if g.numel() != 3:
@@ -287,4 +299,5 @@ def rollout(u0, g, *, steps, tau, flags=None, checkpoint_every=20, wall_u=(0.0, 
     if steps < 1 or checkpoint_every < 1:
         raise ValueError("steps and checkpoint_every must be >= 1")
     return _Rollout.apply(u0, g.reshape(3), int(steps), float(tau), flags, int(checkpoint_every),
-                          tuple(float(v) for v in wall_u), equilibrium, int(steps_per_pass))
+                          tuple(float(v) for v in wall_u), equilibrium, int(steps_per_pass),
+                          torch.is_grad_enabled() and (u0.requires_grad or g.requires_grad))

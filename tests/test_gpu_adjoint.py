@@ -242,3 +242,57 @@ def test_fused_recomputation_gives_identical_gradients(monkeypatch):
         monkeypatch.setattr(L, "FUSED_RECOMPUTE_MIN_CELLS", 0)
         got = _gpu_grad(u0, target, F, flags, tau, steps, k, steps_per_pass=spp)
         assert got[2] == ref[2] and np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]), k
+
+
+@pytest.mark.parametrize("pairs", [0, 1])
+@pytest.mark.parametrize("geo", ["box", "porous", "moving"])
+def test_segments_equal_single_calls(geo, pairs):
+    """lbm_segment and lbm_adjoint_segment (stored moments in place of the
+    pulls of f*) against lbm_step_from, lbm_adjoint_seed and lbm_adjoint_step:
+    the states, nu and dL/dF bit for bit, over segments of 1 to 5 steps."""
+    shape = (6, 15, 70)
+    say("segments vs single calls", geo, pairs)
+    rng = np.random.default_rng(8)
+    kw = {"u0": torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float()}
+    if geo != "box":
+        fl = I.random_flags(shape, 51, solid_fraction=0.15, noforce_fraction=0.1)
+        if geo == "moving":
+            fl |= I.cavity_flags(shape)
+            kw["wall_u"] = (0.03, 0.01, -0.02)
+        kw["u0"][:, torch.from_numpy(fl & 1 == 1)] = 0
+        kw["flags"] = fl
+    sim = LBM(shape, 0.6, (2e-5, -1e-5, 0), "f32", steps_per_pass=2, **kw)
+    gr = torch.from_numpy(rng.standard_normal(shape)).float().cuda()
+    gu = torch.from_numpy(rng.standard_normal((3,) + shape)).float().cuda()
+    nfl = sim.grid_bytes // 4
+    for n in (1, 2, 3, 5):
+        states = [sim.grids[0]] + [sim.new_grid().zero_() for _ in range(n)]
+        for a, b in zip(states, states[1:]):
+            sim.step_from(a, b)
+        ref = [torch.zeros(nfl, device="cuda") for _ in range(2)]
+        got = [torch.zeros(nfl, device="cuda") for _ in range(2)]
+        part = [torch.zeros(sim.adj_partials_bytes // 8, dtype=torch.float64, device="cuda")
+                for _ in range(2)]
+        A.lbm_adjoint_seed(sim.ctx, P(states[n - 1]), P(gr), P(gu), P(ref[0]), P(part[0]))
+        for k in range(1, n):
+            A.lbm_adjoint_step(sim.ctx, P(states[n - 1 - k]), P(ref[(k - 1) % 2]), P(ref[k % 2]),
+                               P(part[0]))
+        mom = torch.empty(n * 4 * sim.dir_stride, dtype=torch.float32, device="cuda")
+        dst, tmp = sim.new_grid().zero_(), sim.new_grid().zero_()
+        for keep in (True, False):  # without the last state: the same moments
+            mom.fill_(7.0)
+            A.lbm_segment(sim.ctx, P(states[0]), P(tmp), P(dst), n, pairs, P(mom), keep)
+            if keep:
+                assert torch.equal(dst, states[n]), n
+                A.lbm_segment(sim.ctx, P(states[0]), P(tmp), P(dst.zero_()), n, pairs, None, True)
+                assert torch.equal(dst, states[n]), n
+            A.lbm_adjoint_segment(sim.ctx, P(mom), n, True, P(gr), P(gu), P(got[0]), P(got[1]),
+                                  P(part[1]))
+            torch.cuda.synchronize()
+            x, y = got[(n - 1) % 2], ref[(n - 1) % 2]
+            assert torch.equal(x.view(torch.int32), y.view(torch.int32)), (n, keep)
+            assert torch.equal(part[0], part[1]), (n, keep)
+    with pytest.raises(A.LBMError):
+        A.lbm_segment(sim.ctx, P(states[0]), None, P(dst), 5, 0, None, True)
+    with pytest.raises(A.LBMError):
+        A.lbm_segment(sim.ctx, P(states[0]), P(tmp), P(dst), 1, 0, None, False)
