@@ -20,6 +20,9 @@ struct Geo {
   int32_t nrows;    // ny * nz
   int32_t nblocks;  // blocks launched (4 segments each)
   int32_t nb8;      // nblocks rounded down to a multiple of 8
+  int32_t units;    // step kernel: 64-cell units per row,
+  int32_t upw;      //   and the most of them that a segment holds
+  int32_t xfill;    // columns of a row that a single step stores: nx, or more (zeros past nx)
   int32_t yb;       // step kernel: rows are visited in bands of yb rows of y, z fastest
 };
 

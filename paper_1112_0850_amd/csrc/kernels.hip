@@ -40,6 +40,9 @@ Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
   const int64_t segs = int64_t(g.nseg) * g.nrows;
   g.nblocks = int32_t((segs + 3) / 4);
   g.nb8 = (g.nblocks / 8) * 8;
+  g.units = g.nseg;
+  g.upw = 1;
+  g.xfill = nx;
   g.yb = g.ny;
   return g;
 }
@@ -456,10 +459,10 @@ __device__ __forceinline__ bool is_marker(typename Storage<K>::U r) {
   return r == Storage<K>::kRest;
 }
 
-// Cells per lane of the step kernel: a wave owns a run of 64*M cells of one
-// row and each lane updates the cells x0 + 64 m, m < M.  More cells
-// per lane put more bytes in flight per wave, which is what the 16-bit
-// storages need to cover memory latency at the occupancy limit.
+// Most cells per lane of the step kernel: a wave owns up to M units of 64 cells
+// of one row and each lane updates the cells x0 + 64 m.  More cells per lane
+// put more bytes in flight per wave, which is what the 16-bit storages need to
+// cover memory latency at the occupancy limit.
 template <int K>
 struct StepCells {
   static constexpr int M = (K == ST_F16 || K == ST_BF16) ? 4 : 1;
@@ -469,42 +472,18 @@ struct StepCells {
 // MOM: delta_rho and j of the pulled (pre-collision) state are stored as well,
 // into mom[4] (direction arrays of the grid layout), for the adjoint; with a
 // null dst only they are.
-template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM>
-__device__ __forceinline__ void step_body(const typename Storage<K>::T* __restrict__ src,
-                                          typename Storage<K>::T* __restrict__ dst,
-                                          const uint8_t* __restrict__ flags,
-                                          float* __restrict__ mom, const Geo& g,
-                                          const StepK<typename Storage<K>::C>& k) {
+template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM, bool FILL>
+__device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restrict__ src,
+                                           typename Storage<K>::T* __restrict__ dst,
+                                           const uint8_t* __restrict__ flags,
+                                           float* __restrict__ mom, const Geo& g,
+                                           const StepK<typename Storage<K>::C>& k, Loc l, int x0) {
   using C = typename Storage<K>::C;
   using T = typename Storage<K>::T;
   constexpr bool SCALED = (K == ST_F16);
   constexpr bool SOLIDS = WALLS >= 1 && WALLS <= 3;
   constexpr bool MARKERS = WALLS == 1 || WALLS == 2;
   constexpr bool COPY = WALLS == 4;
-  // g describes 64*M-cell segments (step_geo); same block remap as locate().
-  const int b = blockIdx.x;
-  const int lb = (b < g.nb8) ? ((b & 7) * (g.nb8 >> 3) + (b >> 3)) : b;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int seg = lb * 4 + wave;
-  const int row = seg / g.nseg;
-  if (row >= g.nrows) return;
-  // Rows are visited in bands of yb consecutive y; inside a band y runs
-  // fastest, then z.  The rows y - 1 and y + 1 of a row are then processed
-  // by neighbouring waves and the rows z - 1 and z + 1 yb rows (a few dozen
-  // blocks) away, so a bounce-back reload of f*_opp(i)(x) finds in L2 the
-  // line that the solid neighbour's lane pulled (or brings it in for that
-  // lane).
-  Loc l;
-  {
-    const int per_band = g.nz * g.yb;
-    const int band = row / per_band;
-    const int y0 = band * g.yb;
-    const int h = min(g.yb, g.ny - y0);
-    const int idx = row - band * per_band;
-    l.z = idx / h;
-    l.y = y0 + (idx - l.z * h);
-  }
-  const int x0 = (seg - row * g.nseg) * 64 * M + int(threadIdx.x & 63);
   Nbhd n[M];
   bool valid[M];
 #pragma unroll
@@ -514,11 +493,11 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
     l.x = valid[m] ? x : g.nx - 1;  // past the row end: load in bounds, store nothing
     n[m] = neighbourhood(g, l);
   }
-  if (!valid[0]) return;
+  if (FILL ? x0 >= g.xfill : !valid[0]) return;
+  const size_t pb = size_t(g.plane) * sizeof(T);
   uint8_t fl[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) fl[m] = SOLIDS ? flags[n[m].fown] : uint8_t(0);
-  const size_t pb = size_t(g.plane) * sizeof(T);
   C f[M][Q];
   bool mark[M][Q];  // the pull returned a solid marker (raw-bit test at the load)
   bool mov[M][Q];   // ... the moving-wall marker
@@ -534,7 +513,7 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
   bool solid[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
-    solid[m] = SOLIDS && (fl[m] & FLAG_SOLID);
+    solid[m] = SOLIDS && (fl[m] & FLAG_SOLID) && (!FILL || valid[m]);
     if (MARKERS) {
 #pragma unroll
       for (int i = 1; i < Q; ++i)
@@ -560,7 +539,22 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
       collide<C, FORCE, SCALED, INC, K == ST_F32>(f[m], k, C(1));
     }
     const T marker = solid_marker<K>(fl[m], WALLS == 2 || (WALLS == 3 && k.moving));
-    if (valid[m]) {
+    if (FILL) {
+      const int x = x0 + 64 * m;
+      if (__builtin_amdgcn_ballot_w64(!valid[m])) {  // the row ends in this unit
+#pragma unroll
+        for (int i = 0; i < Q; ++i) f[m][i] = valid[m] ? f[m][i] : C(0);
+      }
+      if (x < g.xfill) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          C out = f[m][i];
+          if constexpr (K == ST_F16) out = fp32_result(out);
+          stream_store(elem_rx(dst, pb, i, n[m].row[1][1], uint32_t(x)),
+                       solid[m] ? marker : T(out));
+        }
+      }
+    } else if (valid[m]) {
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
         C out = f[m][i];
@@ -571,12 +565,64 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
   }
 }
 
+// One wave's cells: M units of a row, or (M = 0) however many the wave has.
+template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM, bool FILL>
+__device__ __forceinline__ void step_body(const typename Storage<K>::T* __restrict__ src,
+                                          typename Storage<K>::T* __restrict__ dst,
+                                          const uint8_t* __restrict__ flags,
+                                          float* __restrict__ mom, const Geo& g,
+                                          const StepK<typename Storage<K>::C>& k) {
+  // g describes the segments (step_geo); same block remap as locate().
+  const int b = blockIdx.x;
+  const int lb = (b < g.nb8) ? ((b & 7) * (g.nb8 >> 3) + (b >> 3)) : b;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int seg = lb * 4 + wave;
+  const int row = seg / g.nseg;
+  if (row >= g.nrows) return;
+  // Rows are visited in bands of yb consecutive y; inside a band y runs
+  // fastest, then z.  The rows y - 1 and y + 1 of a row are then processed
+  // by neighbouring waves and the rows z - 1 and z + 1 yb rows (a few dozen
+  // blocks) away, so a bounce-back reload of f*_opp(i)(x) finds in L2 the
+  // line that the solid neighbour's lane pulled (or brings it in for that
+  // lane).
+  Loc l;
+  {
+    const int per_band = g.nz * g.yb;
+    const int band = row / per_band;
+    const int y0 = band * g.yb;
+    const int h = min(g.yb, g.ny - y0);
+    const int idx = row - band * per_band;
+    l.z = idx / h;
+    l.y = y0 + (idx - l.z * h);
+  }
+  const int u0 = (seg - row * g.nseg) * g.upw;
+  const int x0 = u0 * 64 + int(threadIdx.x & 63);
+  if constexpr (M != 0) {
+    step_cells<K, WALLS, FORCE, INC, M, MOM, FILL>(src, dst, flags, mom, g, k, l, x0);
+  } else {
+    switch (min(g.upw, g.units - u0)) {
+      case 1: step_cells<K, WALLS, FORCE, INC, 1, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
+      case 2: step_cells<K, WALLS, FORCE, INC, 2, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
+      case 3: step_cells<K, WALLS, FORCE, INC, 3, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
+      case 4: step_cells<K, WALLS, FORCE, INC, 4, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
+    }
+  }
+}
+
 template <int K, int WALLS, bool FORCE, bool INC, int M>
 __global__ __launch_bounds__(kBlock) void k_step(const typename Storage<K>::T* __restrict__ src,
                                                  typename Storage<K>::T* __restrict__ dst,
                                                  const uint8_t* __restrict__ flags, Geo g,
                                                  StepK<typename Storage<K>::C> k) {
-  step_body<K, WALLS, FORCE, INC, M, false>(src, dst, flags, nullptr, g, k);
+  step_body<K, WALLS, FORCE, INC, M, false, false>(src, dst, flags, nullptr, g, k);
+}
+
+// The same storing g.xfill columns of a row, zeros past nx.
+template <int K, int WALLS, bool FORCE, bool INC, int M>
+__global__ __launch_bounds__(kBlock) void k_step_fill(
+    const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ dst,
+    const uint8_t* __restrict__ flags, Geo g, StepK<typename Storage<K>::C> k) {
+  step_body<K, WALLS, FORCE, INC, M, false, true>(src, dst, flags, nullptr, g, k);
 }
 
 template <int WALLS, bool FORCE, bool INC>
@@ -585,7 +631,7 @@ __global__ __launch_bounds__(kBlock) void k_step_mom(const float* __restrict__ s
                                                      const uint8_t* __restrict__ flags,
                                                      float* __restrict__ mom, Geo g,
                                                      StepK<float> k) {
-  step_body<ST_F32, WALLS, FORCE, INC, 1, true>(src, dst, flags, mom, g, k);
+  step_body<ST_F32, WALLS, FORCE, INC, 1, true, false>(src, dst, flags, mom, g, k);
 }
 
 // ---------------------------------------------------------------------------
@@ -1638,27 +1684,45 @@ static StepK<C> make_stepk(const PhysParams& p) {
 // rows (6% faster than plain (z, y) order) and the 1-cell kernels' at 32.
 constexpr int band_rows(int M) { return M >= 4 ? 16 : 32; }
 
-// Geometry of 64*M-cell segments for the step kernel.
+// Geometry of segments of up to M 64-cell units for the step kernel.
 static Geo step_geo(const Geo& g, int M) {
   Geo h = g;
   h.yb = band_rows(M) < g.ny ? band_rows(M) : g.ny;
-  h.nseg = (g.nx + 64 * M - 1) / (64 * M);
+  h.units = (g.nx + 63) / 64;
+  h.nseg = (h.units + M - 1) / M;
+  h.upw = (h.units + h.nseg - 1) / h.nseg;
   const int64_t segs = int64_t(h.nseg) * g.nrows;
   h.nblocks = int32_t((segs + 3) / 4);
   h.nb8 = (h.nblocks / 8) * 8;
   return h;
 }
 
+// A row's units are dealt evenly to as few waves as M allows.  Where every wave
+// gets M the kernel is the one for exactly M; elsewhere each wave runs its own
+// count (M = 0).  Waves of always 4 units ran 1, 2 or 3 of them past the row
+// end: FP16, us a step, 64^3 7.0 -> 5.8, 128^3 37.4 -> 34.2, 320^3 546 -> 518
+// (porous).  The kernel for exactly 4 stays, being 3% faster than the switch at
+// 256^3 (271 / 281) and 1% at 512^3.
 template <int K, int WALLS, bool FORCE, bool INC>
 static void step_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                    const uint8_t* flags, hipStream_t s) {
   using S = Storage<K>;
   constexpr int M = StepCells<K>::M;
   const Geo h = step_geo(g, M);
-  hipLaunchKernelGGL((k_step<K, WALLS, FORCE, INC, M>), dim3(h.nblocks), dim3(kBlock), 0, s,
-                     reinterpret_cast<const typename S::T*>(src),
-                     reinterpret_cast<typename S::T*>(dst), flags, h,
-                     make_stepk<typename S::C>(ph));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s,
+                       reinterpret_cast<const typename S::T*>(src),
+                       reinterpret_cast<typename S::T*>(dst), flags, h,
+                       make_stepk<typename S::C>(ph));
+  };
+  constexpr int ANY = M > 1 ? 0 : 1;
+  if constexpr (WALLS != 4) {
+    if (h.xfill > h.nx) return go(k_step_fill<K, WALLS, FORCE, INC, ANY>);
+  }
+  if constexpr (M > 1) {
+    if (h.units % M) return go(k_step<K, WALLS, FORCE, INC, ANY>);
+  }
+  go(k_step<K, WALLS, FORCE, INC, M>);
 }
 
 template <int K, int WALLS, bool INC>
@@ -1876,12 +1940,7 @@ hipError_t launch_link_mask(const Geo& g, const uint8_t* flags, uint32_t* mask, 
 
 template <int K>
 static void pull_t(const Geo& g, const void* src, void* dst, hipStream_t s) {
-  using S = Storage<K>;
-  constexpr int M = StepCells<K>::M;
-  const Geo h = step_geo(g, M);
-  hipLaunchKernelGGL((k_step<K, 4, false, false, M>), dim3(h.nblocks), dim3(kBlock), 0, s,
-                     reinterpret_cast<const typename S::T*>(src),
-                     reinterpret_cast<typename S::T*>(dst), nullptr, h, StepK<typename S::C>{});
+  step_t<K, 4, false, false>(g, PhysParams{}, src, dst, nullptr, s);
 }
 
 hipError_t launch_pull_copy(int storage, const Geo& g, const void* src, void* dst, hipStream_t s) {

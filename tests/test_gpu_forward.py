@@ -112,6 +112,38 @@ def test_write_coverage(storage):
     assert (v[..., nx:] == pattern).all()
 
 
+@pytest.mark.parametrize("nx", [31, 64, 100, 150, 200, 300, 450, 600])
+@pytest.mark.parametrize("storage", STORAGES)
+def test_rows_of_any_number_of_units(storage, nx):
+    """Rows of 1 to 10 64-cell units, dealt to waves of up to 4 in the 16-bit
+    kernels: the pull-copy probe is the periodic shift bit for bit, and steps
+    between the context's own grids (whose last sector of a row is filled up
+    with zeros) leave the same bytes, padding included, as lbm_step_from into
+    zeroed grids (which never writes the padding)."""
+    shape = (3, 5, nx)
+    say("row units", storage, shape)
+    e = R.e_w_opp()[0]
+    fl = I.random_flags(shape, 61, solid_fraction=0.2, noforce_fraction=0.1)
+    u0 = torch.from_numpy(0.02 * (np.random.default_rng(5).random((3,) + shape) - 0.5)).float()
+    u0[:, torch.from_numpy(fl & 1 == 1)] = 0
+    sim = LBM(shape, 0.7, (1e-4, 0, 0), storage, flags=fl, u0=u0,
+              f16_scale_log2=10 if storage == "f16" else 0)
+    src, dst = sim.grids[0].clone(), sim.new_grid().zero_()
+    sim.pull_copy(src, dst)
+    it = {1: torch.uint8, 2: torch.int16, 4: torch.int32, 8: torch.int64}[sim.dtype.itemsize]
+    a, b = sim.grid_view(src, it)[..., :nx], sim.grid_view(dst, it)
+    for i in range(19):
+        assert torch.equal(b[i, ..., :nx], torch.roll(a[i], tuple(int(c) for c in e[i][::-1]),
+                                                      (0, 1, 2))), i
+    assert not b[..., nx:].any()
+    one, two = sim.new_grid().zero_(), sim.new_grid().zero_()
+    sim.step_from(src, one)
+    sim.step_from(one, two)
+    sim.step(2)
+    torch.cuda.synchronize()
+    assert torch.equal(sim.grids[0], two) and torch.equal(sim.grids[1], one)
+
+
 def _run_pair(shape, tau, F, storage, flags, u0, steps, s=0):
     """(GPU LBM after `steps`, oracle f after `steps`) from f^eq(1, u0)."""
     u0 = np.asarray(u0, dtype=np.float32).astype(np.float64) if u0 is not None else None
