@@ -5,12 +5,15 @@ instructions disabled (-packed-fp32-ops) for all device code.
 """
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
-SOURCES = ["kernels.hip", "abi.hip"]
+# (source, defines) of each object; kernels.hip is compiled in parts
+SOURCES = [("kernels.hip", [f"-DLBM_PART={p}"]) for p in range(8)] + [("abi.hip", [])]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=on: multiply-adds are fused only inside one source
@@ -26,11 +29,17 @@ FLAGS = [
 
 
 def build(verbose: bool = False, extra=()) -> str:
-    cmd = [HIPCC] + FLAGS + list(extra) + [os.path.join(CSRC, s) for s in SOURCES] + \
-        ["-o", LIB + ".tmp"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+
+    flags = [f for f in FLAGS if f != "-shared"] + list(extra)
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(8) as pool:
+        objs = [os.path.join(tmp, f"{k}.o") for k in range(len(SOURCES))]
+        list(pool.map(run, [[HIPCC] + flags + defs + ["-c", os.path.join(CSRC, src), "-o", obj]
+                            for (src, defs), obj in zip(SOURCES, objs)]))
+        run([HIPCC] + FLAGS + objs + ["-o", LIB + ".tmp"])
     os.replace(LIB + ".tmp", LIB)
     return LIB
 

@@ -63,7 +63,7 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
 hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
                         const void* src, void* dst, const uint8_t* flags, const uint32_t* lmask,
                         hipStream_t s);
-// Blocks a two-step launch has on this grid (its tiles and z chunks).
+// Blocks of a two-step launch with the storage's first choice of tile rows.
 int step2_blocks(int storage, const Geo& g);
 // Fewer blocks than this leave most CUs idle, and single steps are faster
 // (periodic boxes, us a step, single / pairs: FP32 48^3, 96 blocks, 5.6 / 8.1;

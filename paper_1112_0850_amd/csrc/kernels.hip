@@ -26,8 +26,15 @@
 #include "d3q19.h"
 #include "kernels.h"
 
+// The file is compiled once per part: part 0 holds everything but the step
+// kernels, whose many instantiations are shared out over the other parts.
+#ifndef LBM_PART
+#error "LBM_PART is not set (see build.py)"
+#endif
+
 namespace lbm {
 
+#if LBM_PART == 0
 Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
   Geo g;
   g.nx = nx;
@@ -46,6 +53,7 @@ Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
   g.yb = g.ny;
   return g;
 }
+#endif  // LBM_PART == 0
 
 template <typename C>
 struct Phys {
@@ -693,16 +701,34 @@ __device__ __forceinline__ U pick(uint32_t sel, U a, U b) {
 constexpr int kTB2MinChunk = 2;  // shortest z chunk (planes per block)
 constexpr int kCUs = 256;
 
-// Tile rows per block: 13 (16 waves, 1024 threads, one block per CU: the
-// FP32 ring takes 127 KB of LDS) for 4- and 2-byte storage, which fit 128
-// VGPRs without spills; measured at 512^3, 13 rows beat 12, 8, 6 and 5.
-// FP64 storage takes 5 (118 KB of LDS; 6 rows cap the 9 waves at 168
-// VGPRs, spill and ran 0.7% slower), and F32X (FP64 arithmetic) 8, whose 11
-// waves may use 168 VGPRs.
+// Tile rows per block, the first the one that large grids take: 13 (16 waves,
+// 1024 threads, one block per CU: the FP32 ring takes 127 KB of LDS) for 4- and
+// 2-byte storage, which fit 128 VGPRs without spills; at 512^3 13 rows beat 12,
+// 8, 6 and 5.  FP64 storage takes 5 (118 KB of LDS; 6 rows cap the 9 waves at
+// 168 VGPRs, spill and ran 0.7% slower), and F32X (FP64 arithmetic) 8, whose 11
+// waves may use 168 VGPRs.  The others serve the sizes that the first leaves a
+// last round nearly empty on (see make_geo2); `cost` is the measured time of a
+// plane against the first's (FP32 6.2 / 4.55 / 4.1 us, FP16 4.3 / 3.3 / 2.9,
+// FP64 4.7 / 4.0).
+struct Tb2Rows {
+  int rows;
+  double cost;
+};
 template <int K>
-__host__ __device__ constexpr int tb2_rows() {
-  return K == ST_F64 ? 5 : (K == ST_F32X ? 8 : 13);
-}
+struct Tb2 {
+  static constexpr int N = 3;
+  static constexpr Tb2Rows choice[N] = {{13, 1.0}, {10, 0.74}, {8, 0.67}};
+};
+template <>
+struct Tb2<ST_F64> {
+  static constexpr int N = 2;
+  static constexpr Tb2Rows choice[N] = {{5, 1.0}, {4, 0.85}};
+};
+template <>
+struct Tb2<ST_F32X> {
+  static constexpr int N = 1;
+  static constexpr Tb2Rows choice[N] = {{8, 1.0}};
+};
 __host__ __device__ constexpr int tb2_nslot(int i) {
   return D3Q19::cz[i] > 0 ? 3 : (D3Q19::cz[i] == 0 ? 2 : 1);
 }
@@ -774,15 +800,15 @@ constexpr int kOutLast = 0, kOutMid = 1, kOutMoments = 2;
 // its mask bit.  The same values reach the collision as with the markers,
 // so the results are the same bits.  The mask of a plane is loaded two
 // planes ahead.
-template <int K, int WALLS, bool FORCE, bool INC, int OUT>
-__global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
+template <int K, int WALLS, bool FORCE, bool INC, int OUT, int TY>
+__global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
     const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ mid,
     float* __restrict__ mom2, typename Storage<K>::T* __restrict__ dst,
     const uint8_t* __restrict__ flags,
     const uint32_t* __restrict__ lmask, Geo2 g, StepK<typename Storage<K>::C> k) {
   using C = typename Storage<K>::C;
   using T = typename Storage<K>::T;
-  constexpr int TY = tb2_rows<K>(), TX = 64, EX = TX + 2, EY = TY + 2;
+  constexpr int TX = 64, EX = TX + 2, EY = TY + 2;
   constexpr uint32_t SZ = sizeof(T);
   constexpr uint32_t PLB = uint32_t(EY * EX) * SZ;  // bytes of one LDS plane-array
   constexpr bool SOLIDS = WALLS >= 1;
@@ -1010,6 +1036,7 @@ __global__ __launch_bounds__(64 * (tb2_rows<K>() + 3)) void k_step2(
   }
 }
 
+#if LBM_PART == 0
 // The link mask of every cell for the two-step kernel's resting walls: bit i
 // (1..18) set when the pull along c_i is blocked (x - c_i solid, periodic),
 // plus the cell's own SOLID and NOFORCE flags.
@@ -1646,6 +1673,7 @@ hipError_t launch_mark_solids(int storage, const Geo& g, const PhysParams& ph, v
   }
   return hipGetLastError();
 }
+#endif  // LBM_PART == 0
 
 // Host-side construction of the uniform step constants (see StepK).
 template <typename C>
@@ -1756,12 +1784,18 @@ static void step_mom_f(bool force, const Geo& g, const PhysParams& ph, const flo
 }
 
 template <bool INC>
-static void step_mom_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const float* src,
+void step_mom_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const float* src,
                        float* dst, float* mom, const uint8_t* flags, hipStream_t s) {
   if (!solids) step_mom_f<0, INC>(force, g, ph, src, dst, mom, flags, s);
   else if (!ph.moving) step_mom_f<1, INC>(force, g, ph, src, dst, mom, flags, s);
   else step_mom_f<2, INC>(force, g, ph, src, dst, mom, flags, s);
 }
+
+#if LBM_PART == 0
+extern template void step_mom_w<false>(bool, bool, const Geo&, const PhysParams&, const float*,
+                                       float*, float*, const uint8_t*, hipStream_t);
+extern template void step_mom_w<true>(bool, bool, const Geo&, const PhysParams&, const float*,
+                                      float*, float*, const uint8_t*, hipStream_t);
 
 hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
                            const float* src, float* dst, float* mom, const uint8_t* flags,
@@ -1770,13 +1804,26 @@ hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysPara
   else step_mom_w<false>(solids, force, g, ph, src, dst, mom, flags, s);
   return hipGetLastError();
 }
+#endif  // LBM_PART == 0
 
 template <int K>
-static void step_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
+void step_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
                    void* dst, const uint8_t* flags, hipStream_t s) {
   if (ph.incomp) step_w<K, true>(solids, force, g, ph, src, dst, flags, s);
   else step_w<K, false>(solids, force, g, ph, src, dst, flags, s);
 }
+
+#if LBM_PART == 0
+extern template void step_k<ST_F32>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                  const uint8_t*, hipStream_t);
+extern template void step_k<ST_F16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                  const uint8_t*, hipStream_t);
+extern template void step_k<ST_BF16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                  const uint8_t*, hipStream_t);
+extern template void step_k<ST_F64>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                  const uint8_t*, hipStream_t);
+extern template void step_k<ST_F32X>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                  const uint8_t*, hipStream_t);
 
 hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
                        const void* src, void* dst, const uint8_t* flags, hipStream_t s) {
@@ -1790,9 +1837,19 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
   }
   return hipGetLastError();
 }
+#endif  // LBM_PART == 0
 
-// Geometry of the two-step kernel's launch.
-static Geo2 make_geo2(const Geo& g, int rows) {
+// Geometry of the two-step kernel's launch with tiles of `rows` rows; *cost gets
+// its time in planes.  One block fills a CU, so the blocks run in rounds of
+// kCUs, and a block's time is its planes plus the two it recomputes plus about
+// two planes of start-up -- measured 6.1-6.6 us a plane and round in FP32 from
+// 128^3 to 512^3, 4.1-4.3 in BF16 and 4.6-4.8 in FP64, whatever the z chunk.  So
+// the chunk length is the one with the least rounds * (planes + 4).  (Against
+// chunks of 128 planes halved down to 16 until there were 1280 blocks: 128^3
+// FP32 103 -> 85 us a pass, 128 x 128 x 256 204 -> 155, 200^3 404 -> 329, 256^3
+// 589 -> 541, 200^3 BF16 289 -> 225, 100^3 FP64 130 -> 84; 512^3 keeps its 128
+// planes.)
+static inline Geo2 make_geo2(const Geo& g, int rows, int64_t* cost) {
   Geo2 h;
   h.nx = g.nx;
   h.ny = g.ny;
@@ -1801,24 +1858,15 @@ static Geo2 make_geo2(const Geo& g, int rows) {
   h.plane = g.plane;
   h.ntx = (g.nx + 63) / 64;
   h.nty = (g.ny + rows - 1) / rows;
-  // z chunks: one block fills a CU, so the blocks run in rounds of kCUs, and
-  // a block's time is its planes plus the two it recomputes plus about two
-  // planes of start-up -- measured 6.1-6.6 us a plane and round in FP32 from
-  // 128^3 to 512^3, 4.1-4.3 in BF16 and 4.6-4.8 in FP64, whatever the chunk.
-  // So the chunk length is the one with the least rounds * (planes + 4).
-  // (Against chunks of 128 planes halved down to 16 until there were 1280
-  // blocks: 128^3 FP32 103 -> 85 us a pass, 128 x 128 x 256 204 -> 155,
-  // 200^3 404 -> 329, 256^3 589 -> 541, 200^3 BF16 289 -> 225, 100^3 FP64
-  // 130 -> 84; 512^3 keeps its 128 planes.)
   const int64_t tiles = int64_t(h.ntx) * h.nty;
-  int64_t best = INT64_MAX;
+  *cost = INT64_MAX;
   h.zc = g.nz;
   for (int n = 1; n <= g.nz; ++n) {
     const int zc = (g.nz + n - 1) / n;
     if (zc < kTB2MinChunk && n > 1) break;
     const int64_t rounds = (tiles * ((g.nz + zc - 1) / zc) + kCUs - 1) / kCUs;
-    if (rounds * (zc + 4) < best) {
-      best = rounds * (zc + 4);
+    if (rounds * (zc + 4) < *cost) {
+      *cost = rounds * (zc + 4);
       h.zc = zc;
     }
   }
@@ -1828,17 +1876,58 @@ static Geo2 make_geo2(const Geo& g, int rows) {
   return h;
 }
 
+// The choice of tile rows for a grid: the first unless another one's time, by
+// the same measure, is 6% less (the halo rows of smaller tiles cost memory
+// traffic that the measure leaves out).  Measured, us a pass, 13 rows against
+// the chosen: FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256
+// 171 / 157 (8), 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4); 200^3 and from
+// 256^3 on keep the first.
+template <int K>
+static int tb2_choice(const Geo& g) {
+  int best = 0;
+  double least = 0.0;
+  for (int i = 0; i < Tb2<K>::N; ++i) {
+    int64_t planes;
+    make_geo2(g, Tb2<K>::choice[i].rows, &planes);
+    const double c = double(planes) * Tb2<K>::choice[i].cost;
+    if (i == 0) least = 0.94 * c;
+    else if (c < least) {
+      least = c;
+      best = i;
+    }
+  }
+  return best;
+}
+
+template <int K, int WALLS, bool FORCE, bool INC, int OUT, int CHOICE>
+static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* dst,
+                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s, void* mid,
+                     float* mom2) {
+  using S = Storage<K>;
+  constexpr int rows = Tb2<K>::choice[CHOICE].rows;
+  int64_t cost;
+  const Geo2 h = make_geo2(g, rows, &cost);
+  hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT, rows>), dim3(h.nblocks),
+                     dim3(64 * (rows + 3)), 0, s, reinterpret_cast<const typename S::T*>(src),
+                     reinterpret_cast<typename S::T*>(mid), mom2,
+                     reinterpret_cast<typename S::T*>(dst), flags, lmask, h,
+                     make_stepk<typename S::C>(ph));
+}
+
 template <int K, int WALLS, bool FORCE, bool INC, int OUT = kOutLast>
 static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s,
                     void* mid = nullptr, float* mom2 = nullptr) {
-  using S = Storage<K>;
-  constexpr int rows = tb2_rows<K>();
-  const Geo2 h = make_geo2(g, rows);
-  hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT>), dim3(h.nblocks), dim3(64 * (rows + 3)),
-                     0, s, reinterpret_cast<const typename S::T*>(src),
-                     reinterpret_cast<typename S::T*>(mid), mom2,
-                     reinterpret_cast<typename S::T*>(dst), flags, lmask, h, make_stepk<typename S::C>(ph));
+  const int c = OUT == kOutMid ? 0 : tb2_choice<K>(g);  // (mid: one instantiation)
+  if constexpr (Tb2<K>::N > 2 && OUT != kOutMid) {
+    if (c == 2)
+      return step2_go<K, WALLS, FORCE, INC, OUT, 2>(g, ph, src, dst, flags, lmask, s, mid, mom2);
+  }
+  if constexpr (Tb2<K>::N > 1 && OUT != kOutMid) {
+    if (c == 1)
+      return step2_go<K, WALLS, FORCE, INC, OUT, 1>(g, ph, src, dst, flags, lmask, s, mid, mom2);
+  }
+  step2_go<K, WALLS, FORCE, INC, OUT, 0>(g, ph, src, dst, flags, lmask, s, mid, mom2);
 }
 
 template <int K, int WALLS, bool INC>
@@ -1859,19 +1948,37 @@ static void step2_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
 }
 
 template <int K>
-static void step2_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
+void step2_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
                     void* dst, const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (ph.incomp) step2_w<K, true>(solids, force, g, ph, src, dst, flags, lmask, s);
   else step2_w<K, false>(solids, force, g, ph, src, dst, flags, lmask, s);
 }
 
+#if LBM_PART == 0
+extern template void step2_k<ST_F32>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                   const uint8_t*, const uint32_t*, hipStream_t);
+extern template void step2_k<ST_F16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                   const uint8_t*, const uint32_t*, hipStream_t);
+extern template void step2_k<ST_BF16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                   const uint8_t*, const uint32_t*, hipStream_t);
+extern template void step2_k<ST_F64>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                   const uint8_t*, const uint32_t*, hipStream_t);
+extern template void step2_k<ST_F32X>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+                                   const uint8_t*, const uint32_t*, hipStream_t);
+
+template <int K>
+static int step2_blocks_k(const Geo& g) {
+  int64_t cost;
+  return make_geo2(g, Tb2<K>::choice[0].rows, &cost).nblocks;
+}
+
 int step2_blocks(int storage, const Geo& g) {
   switch (storage) {
-    case ST_F32: return make_geo2(g, tb2_rows<ST_F32>()).nblocks;
-    case ST_F16: return make_geo2(g, tb2_rows<ST_F16>()).nblocks;
-    case ST_BF16: return make_geo2(g, tb2_rows<ST_BF16>()).nblocks;
-    case ST_F64: return make_geo2(g, tb2_rows<ST_F64>()).nblocks;
-    case ST_F32X: return make_geo2(g, tb2_rows<ST_F32X>()).nblocks;
+    case ST_F32: return step2_blocks_k<ST_F32>(g);
+    case ST_F16: return step2_blocks_k<ST_F16>(g);
+    case ST_BF16: return step2_blocks_k<ST_BF16>(g);
+    case ST_F64: return step2_blocks_k<ST_F64>(g);
+    case ST_F32X: return step2_blocks_k<ST_F32X>(g);
     default: return 0;
   }
 }
@@ -1889,6 +1996,7 @@ hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, cons
   }
   return hipGetLastError();
 }
+#endif  // LBM_PART == 0
 
 // Two fused FP32 steps that also store the intermediate level (OUT = kOutMid:
 // src = f*(t) -> mid = f*(t+1), dst = f*(t+2)) or the moments of both
@@ -1902,7 +2010,7 @@ static void step2_out_f(bool force, const Geo& g, const PhysParams& ph, const vo
 }
 
 template <int OUT, bool INC>
-static void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
+void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
                         const void* src, void* mid, float* mom2, void* dst, const uint8_t* flags,
                         const uint32_t* lmask, hipStream_t s) {
   if (!solids) step2_out_f<OUT, 0, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
@@ -1911,6 +2019,51 @@ static void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams&
   else if (!ph.moving) step2_out_f<OUT, 1, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
   else step2_out_f<OUT, 2, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
 }
+
+// The step kernels' instantiations, shared out over the parts.
+#define LBM_STEP_K(K)                                                                            \
+  template void step_k<K>(bool, bool, const Geo&, const PhysParams&, const void*, void*,         \
+                          const uint8_t*, hipStream_t);                                          \
+  template void step2_k<K>(bool, bool, const Geo&, const PhysParams&, const void*, void*,        \
+                           const uint8_t*, const uint32_t*, hipStream_t);
+#define LBM_STEP_OUT(INC)                                                                        \
+  template void step_mom_w<INC>(bool, bool, const Geo&, const PhysParams&, const float*, float*, \
+                                float*, const uint8_t*, hipStream_t);                            \
+  template void step2_out_w<kOutMid, INC>(bool, bool, const Geo&, const PhysParams&, const void*, \
+                                          void*, float*, void*, const uint8_t*, const uint32_t*, \
+                                          hipStream_t);                                          \
+  template void step2_out_w<kOutMoments, INC>(bool, bool, const Geo&, const PhysParams&,         \
+                                              const void*, void*, float*, void*, const uint8_t*, \
+                                              const uint32_t*, hipStream_t);
+#if LBM_PART == 1
+LBM_STEP_K(ST_F32)
+#elif LBM_PART == 2
+LBM_STEP_K(ST_F16)
+#elif LBM_PART == 3
+LBM_STEP_K(ST_BF16)
+#elif LBM_PART == 4
+LBM_STEP_K(ST_F64)
+#elif LBM_PART == 5
+LBM_STEP_K(ST_F32X)
+#elif LBM_PART == 6
+LBM_STEP_OUT(false)
+#elif LBM_PART == 7
+LBM_STEP_OUT(true)
+#endif
+
+#if LBM_PART == 0
+extern template void step2_out_w<kOutMid, false>(bool, bool, const Geo&, const PhysParams&,
+                                          const void*, void*, float*, void*, const uint8_t*,
+                                          const uint32_t*, hipStream_t);
+extern template void step2_out_w<kOutMid, true>(bool, bool, const Geo&, const PhysParams&,
+                                          const void*, void*, float*, void*, const uint8_t*,
+                                          const uint32_t*, hipStream_t);
+extern template void step2_out_w<kOutMoments, false>(bool, bool, const Geo&, const PhysParams&,
+                                          const void*, void*, float*, void*, const uint8_t*,
+                                          const uint32_t*, hipStream_t);
+extern template void step2_out_w<kOutMoments, true>(bool, bool, const Geo&, const PhysParams&,
+                                          const void*, void*, float*, void*, const uint8_t*,
+                                          const uint32_t*, hipStream_t);
 
 hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,
                             const PhysParams& ph, const void* src, void* mid, void* dst,
@@ -2121,5 +2274,6 @@ hipError_t launch_copy_variant(void* c, const void* a, size_t n16, int vec, bool
   }
   return hipGetLastError();
 }
+#endif  // LBM_PART == 0
 
 }  // namespace lbm

@@ -111,6 +111,17 @@ def test_two_step_pass_chunk_edges(storage, nz):
     assert _same(one, two)
 
 
+@pytest.mark.parametrize("shape", [(64, 64, 64), (24, 63, 130), (40, 50, 70), (160, 160, 65)])
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f64"])
+def test_two_step_pass_tile_rows(storage, shape):
+    """Boxes on which the pass takes tiles of 8, 10 or 13 rows (FP64: 4 or 5),
+    with full and partial last tiles: the same bits as single steps."""
+    say("two-step pass, tile rows", storage, shape)
+    fl = I.random_flags(shape, 43, solid_fraction=0.15, noforce_fraction=0.1)
+    one, two = _pair(shape, 0.6, (1e-5, 0, 0), storage, 4, flags=fl, u0=_u0(shape, 44))
+    assert _same(one, two)
+
+
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 def test_two_step_pass_unpadded_and_without_force(storage):
     shape = (6, 10, 65)
