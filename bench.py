@@ -553,9 +553,9 @@ KERNELS = {  # record key -> (kernel name, box edge, bytes per fluid update, por
     "bf16": ("void lbm::k_step<2, 1, true, false, 4>", 512, 76, True, 1),
     "f64": ("void lbm::k_step<3, 1, true, false, 1>", 512, 304, True, 1),
     "f32x": ("void lbm::k_step<4, 1, true, false, 1>", 512, 152, True, 1),
-    "f32x2": ("void lbm::k_step2<0, 4, true, false, 0, 13>", 512, 152, True, 2),
-    "f16x2": ("void lbm::k_step2<1, 4, true, false, 0, 13>", 512, 76, True, 2),
-    "f64x2": ("void lbm::k_step2<3, 4, true, false, 0, 5>", 512, 304, True, 2),
+    "f32x2": ("void lbm::k_step2<0, 4, true, false, 0, 13, true>", 512, 152, True, 2),
+    "f16x2": ("void lbm::k_step2<1, 4, true, false, 0, 13, true>", 512, 76, True, 2),
+    "f64x2": ("void lbm::k_step2<3, 4, true, false, 0, 5, true>", 512, 304, True, 2),
     "adjoint": ("void lbm::k_adj<false, false, false>", 256, 228, False, 1),  # periodic, no flags
 }
 
@@ -563,7 +563,7 @@ KERNELS = {  # record key -> (kernel name, box edge, bytes per fluid update, por
 def launch_threads(name, n):
     """Threads a launch of the named kernel has on an n^3 box (64 * M-cell
     segments per row, four per block, M = 4 for the 16-bit step kernels; the
-    two-step kernel: 64 x TY tiles, TY its last template argument, z chunks
+    two-step kernel: 64 x TY tiles, TY its sixth template argument, z chunks
     of the length with the least rounds of 256 blocks times planes plus four,
     64 (TY + 3) threads per block).  Recorded traces whose two-step kernel
     ends in a truth value had TY = 13 (5 for FP64, 8 for F32X) and z chunks
@@ -780,7 +780,7 @@ def trace_summary(trace_dir, bench_json):
         name, spl = KERNELS[key][0], KERNELS[key][4]
         n = round(d["config"]["cells"] ** (1 / 3))
         v = []
-        for name in (name, re.sub(r", 0, \d+>", ", false>", name)):  # as named here, or in older traces
+        for name in (name, re.sub(r", 0, \d+, true>", ", false>", name)):  # as named here, or in older traces
             v = v or groups.get((name, launch_threads(name, n)), [])
         wl, sl = warm // spl, steps // spl
         if ms and len(v) >= wl + sl:

@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
 # (source, defines) of each object; kernels.hip is compiled in parts
-SOURCES = [("kernels.hip", [f"-DLBM_PART={p}"]) for p in range(8)] + [("abi.hip", [])]
+SOURCES = [("kernels.hip", [f"-DLBM_PART={p}"]) for p in range(11)] + [("abi.hip", [])]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=on: multiply-adds are fused only inside one source

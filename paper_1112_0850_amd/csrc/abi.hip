@@ -180,18 +180,29 @@ lbm_status noalloc_scratch_here(int* dev_out, double** out) {
 // zero there anyway (never for a caller's grid, whose padding stays as it is).
 // A partly written sector costs a read of memory: single steps at 300^3 with it
 // FP16 511 -> 456 us, FP32 880 -> 854, FP64 1702 -> 1631; 250^3 FP16 299 -> 266,
-// FP32 516 -> 470.  Grids that stay in the 256 MB cache gain nothing in 4 and 8
-// bytes (100^3 FP32 38.4 / 38.9) and a little in 2 (27.8 -> 26.8).  Filling 128
+// FP32 516 -> 470.  Grids that stay in the cache gain nothing.  Filling 128
 // bytes gains less; zeros stored apart from the row (by the lanes past its end,
 // ahead of their pulls) half as much; the pair pass is not bound by its stores,
 // lost 1-2% and does not fill.
 constexpr size_t kSector = 64;
-constexpr size_t kFillBytes = size_t(128) << 20;
-int32_t row_fill(const lbm::Geo& g, size_t es, size_t grid_bytes) {
-  if (es > 2 && grid_bytes < kFillBytes) return g.nx;
+int32_t row_fill(const lbm::Geo& g, size_t es) {
+  if (!g.stream) return g.nx;
   const int32_t n = int32_t(kSector / es);
   const int32_t up = (g.nx + n - 1) / n * n;
   return up < g.xs ? up : g.xs;
+}
+
+// Plain stores where both grids fit the 256 MB cache, and for single steps a
+// little past it; non-temporal ones from there on.  Measured, us a step,
+// non-temporal / plain, by the size of both grids: single 233 MB (112^3 FP32) 46
+// / 29, 289 MB (144^3 FP16) 64 / 60, 304 MB (128^3 FP32) 63 / 58, 342 MB (96^3
+// FP64) 55 / 53, 356 MB (160^3 FP16) 75 / 88, 371 MB (100^3 FP64) 65 / 70;
+// pairs 186 MB (100^3 FP32) 28 / 21, 304 MB 41 / 43, 371 MB 43 / 46; the
+// adjoint from moments 304 MB 60 / 66 (72 x 80 x 100 FP32, 137 MB: 29 / 20).
+constexpr size_t kCached1 = size_t(340) << 20, kCached2 = size_t(256) << 20;
+void store_policy(lbm::Geo* g, size_t grid_bytes) {
+  g->stream = 2 * grid_bytes > kCached1;
+  g->stream2 = 2 * grid_bytes > kCached2;
 }
 
 struct lbm_ctx {
@@ -389,8 +400,9 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
   c->p = *p;
   c->sz = sz;
   c->geo = lbm::make_geo(p->nx, p->ny, p->nz, int(sz.xs), sz.dir);
+  store_policy(&c->geo, sz.grid_bytes);
   c->geo_own = c->geo;
-  c->geo_own.xfill = row_fill(c->geo, elem_size(p->storage), sz.grid_bytes);
+  c->geo_own.xfill = row_fill(c->geo, elem_size(p->storage));
   c->ph.omega = std::isinf(p->tau) ? 0.0 : 1.0 / p->tau;
   for (int d = 0; d < 3; ++d) c->ph.F[d] = p->force[d];
   c->ph.scale = p->storage == LBM_F16 ? std::ldexp(1.0, p->f16_scale_log2) : 1.0;

@@ -23,6 +23,8 @@ struct Geo {
   int32_t units;    // step kernel: 64-cell units per row,
   int32_t upw;      //   and the most of them that a segment holds
   int32_t xfill;    // columns of a row that a single step stores: nx, or more (zeros past nx)
+  int32_t stream;   // non-temporal stores in the single step,
+  int32_t stream2;  //   and in the pair pass and the adjoint (see store_policy)
   int32_t yb;       // step kernel: rows are visited in bands of yb rows of y, z fastest
 };
 

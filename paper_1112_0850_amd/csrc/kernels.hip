@@ -23,6 +23,8 @@
 // With the incompressible equilibrium of He & Luo (rho0 = 1) u = j' and the
 // same coefficient form holds with t = 0 below.  Walls moving with u_w add
 // 6 w_i (c_i.u_w) to each bounced-back population (Ladd 1994, rho0 = 1).
+#include <type_traits>
+
 #include "d3q19.h"
 #include "kernels.h"
 
@@ -50,6 +52,7 @@ Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
   g.units = g.nseg;
   g.upw = 1;
   g.xfill = nx;
+  g.stream = g.stream2 = 1;
   g.yb = g.ny;
   return g;
 }
@@ -438,13 +441,27 @@ __device__ __forceinline__ void stream_store(T* p, T v) {
   __builtin_nontemporal_store(v, p);
 }
 
+// A plain or a non-temporal store.  Non-temporal stores leave the L2 to the
+// pulls, which large grids gain from (512^3 FP32 3.78 ms a step against 3.94);
+// but they also keep the grid out of the 256 MB memory-side cache, from which
+// the next step of a grid that fits would be fed: 100^3 FP32 37 us a step
+// against 25, 128^3 FP16 35 against 24, 64^3 FP64 17.7 against 12.3.  (NT is a
+// template argument of the kernels: a branch between two store loops kept the
+// stores from mixing with the last of the collision, 2% of the 512^3 pass.)
+template <bool NT, typename T>
+__device__ __forceinline__ void store_kind(T* p, T v) {
+  if constexpr (NT) stream_store(p, v);
+  else *p = v;
+}
+
 // delta_rho and j of a pre-collision state into the four moment arrays (FP32,
 // pb bytes apart): all that the transposed collision needs of the state.
+template <bool NT>
 __device__ __forceinline__ void store_moments(float* mom, size_t pb, uint32_t own, const float* f) {
   float m[4];
   moments(f, m[0], m[1], m[2], m[3]);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) stream_store(elem(mom, pb, i, own), m[i]);
+  for (int i = 0; i < 4; ++i) store_kind<NT>(elem(mom, pb, i, own), m[i]);
 }
 
 // Pins a collision result as a rounded FP32 register value before its FP16
@@ -480,7 +497,7 @@ struct StepCells {
 // MOM: delta_rho and j of the pulled (pre-collision) state are stored as well,
 // into mom[4] (direction arrays of the grid layout), for the adjoint; with a
 // null dst only they are.
-template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM, bool FILL>
+template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM, bool FILL, bool NT>
 __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restrict__ src,
                                            typename Storage<K>::T* __restrict__ dst,
                                            const uint8_t* __restrict__ flags,
@@ -534,7 +551,7 @@ __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restr
   }
   if constexpr (MOM) {
     static_assert(M == 1 && K == ST_F32, "moments of FP32 grids, one cell per lane");
-    if (valid[0]) store_moments(mom, pb, n[0].own, f[0]);
+    if (valid[0]) store_moments<NT>(mom, pb, n[0].own, f[0]);
     if (!dst) return;
   }
 #pragma unroll
@@ -548,33 +565,25 @@ __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restr
     }
     const T marker = solid_marker<K>(fl[m], WALLS == 2 || (WALLS == 3 && k.moving));
     if (FILL) {
-      const int x = x0 + 64 * m;
       if (__builtin_amdgcn_ballot_w64(!valid[m])) {  // the row ends in this unit
 #pragma unroll
         for (int i = 0; i < Q; ++i) f[m][i] = valid[m] ? f[m][i] : C(0);
       }
-      if (x < g.xfill) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          C out = f[m][i];
-          if constexpr (K == ST_F16) out = fp32_result(out);
-          stream_store(elem_rx(dst, pb, i, n[m].row[1][1], uint32_t(x)),
-                       solid[m] ? marker : T(out));
-        }
-      }
-    } else if (valid[m]) {
+    }
+    const uint32_t xs = FILL ? uint32_t(x0 + 64 * m) : n[m].xn[1];
+    if (FILL ? x0 + 64 * m < g.xfill : valid[m]) {
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
         C out = f[m][i];
         if constexpr (K == ST_F16) out = fp32_result(out);
-        stream_store(elem_rx(dst, pb, i, n[m].row[1][1], n[m].xn[1]), solid[m] ? marker : T(out));
+        store_kind<NT>(elem_rx(dst, pb, i, n[m].row[1][1], xs), solid[m] ? marker : T(out));
       }
     }
   }
 }
 
 // One wave's cells: M units of a row, or (M = 0) however many the wave has.
-template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM, bool FILL>
+template <int K, int WALLS, bool FORCE, bool INC, int M, bool MOM, bool FILL, bool NT>
 __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restrict__ src,
                                           typename Storage<K>::T* __restrict__ dst,
                                           const uint8_t* __restrict__ flags,
@@ -606,13 +615,13 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
   const int u0 = (seg - row * g.nseg) * g.upw;
   const int x0 = u0 * 64 + int(threadIdx.x & 63);
   if constexpr (M != 0) {
-    step_cells<K, WALLS, FORCE, INC, M, MOM, FILL>(src, dst, flags, mom, g, k, l, x0);
+    step_cells<K, WALLS, FORCE, INC, M, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0);
   } else {
     switch (min(g.upw, g.units - u0)) {
-      case 1: step_cells<K, WALLS, FORCE, INC, 1, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
-      case 2: step_cells<K, WALLS, FORCE, INC, 2, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
-      case 3: step_cells<K, WALLS, FORCE, INC, 3, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
-      case 4: step_cells<K, WALLS, FORCE, INC, 4, MOM, FILL>(src, dst, flags, mom, g, k, l, x0); break;
+      case 1: step_cells<K, WALLS, FORCE, INC, 1, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
+      case 2: step_cells<K, WALLS, FORCE, INC, 2, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
+      case 3: step_cells<K, WALLS, FORCE, INC, 3, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
+      case 4: step_cells<K, WALLS, FORCE, INC, 4, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
     }
   }
 }
@@ -622,7 +631,15 @@ __global__ __launch_bounds__(kBlock) void k_step(const typename Storage<K>::T* _
                                                  typename Storage<K>::T* __restrict__ dst,
                                                  const uint8_t* __restrict__ flags, Geo g,
                                                  StepK<typename Storage<K>::C> k) {
-  step_body<K, WALLS, FORCE, INC, M, false, false>(src, dst, flags, nullptr, g, k);
+  step_body<K, WALLS, FORCE, INC, M, false, false, true>(src, dst, flags, nullptr, g, k);
+}
+
+// The same with plain stores, for grids that stay in the cache.
+template <int K, int WALLS, bool FORCE, bool INC, int M>
+__global__ __launch_bounds__(kBlock) void k_step_cached(
+    const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ dst,
+    const uint8_t* __restrict__ flags, Geo g, StepK<typename Storage<K>::C> k) {
+  step_body<K, WALLS, FORCE, INC, M, false, false, false>(src, dst, flags, nullptr, g, k);
 }
 
 // The same storing g.xfill columns of a row, zeros past nx.
@@ -630,16 +647,16 @@ template <int K, int WALLS, bool FORCE, bool INC, int M>
 __global__ __launch_bounds__(kBlock) void k_step_fill(
     const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ dst,
     const uint8_t* __restrict__ flags, Geo g, StepK<typename Storage<K>::C> k) {
-  step_body<K, WALLS, FORCE, INC, M, false, true>(src, dst, flags, nullptr, g, k);
+  step_body<K, WALLS, FORCE, INC, M, false, true, true>(src, dst, flags, nullptr, g, k);
 }
 
-template <int WALLS, bool FORCE, bool INC>
+template <int WALLS, bool FORCE, bool INC, bool NT>
 __global__ __launch_bounds__(kBlock) void k_step_mom(const float* __restrict__ src,
                                                      float* __restrict__ dst,
                                                      const uint8_t* __restrict__ flags,
                                                      float* __restrict__ mom, Geo g,
                                                      StepK<float> k) {
-  step_body<ST_F32, WALLS, FORCE, INC, 1, true, false>(src, dst, flags, mom, g, k);
+  step_body<ST_F32, WALLS, FORCE, INC, 1, true, false, NT>(src, dst, flags, mom, g, k);
 }
 
 // ---------------------------------------------------------------------------
@@ -779,9 +796,11 @@ template <typename T>
 __device__ __forceinline__ T load_at(uint64_t base, uint32_t off) {
   return *reinterpret_cast<const __attribute__((address_space(1))) T*>(base + off);
 }
-template <typename T>
-__device__ __forceinline__ void store_nt_at(uint64_t base, uint32_t off, T v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<__attribute__((address_space(1))) T*>(base + off));
+template <bool NT, typename T>
+__device__ __forceinline__ void store_at(uint64_t base, uint32_t off, T v) {
+  auto* p = reinterpret_cast<__attribute__((address_space(1))) T*>(base + off);
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
 }
 
 // OUT = kOutMid: the intermediate level f*(t+1) is stored as well, into `mid`
@@ -800,7 +819,7 @@ constexpr int kOutLast = 0, kOutMid = 1, kOutMoments = 2;
 // its mask bit.  The same values reach the collision as with the markers,
 // so the results are the same bits.  The mask of a plane is loaded two
 // planes ahead.
-template <int K, int WALLS, bool FORCE, bool INC, int OUT, int TY>
+template <int K, int WALLS, bool FORCE, bool INC, int OUT, int TY, bool NT>
 __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
     const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ mid,
     float* __restrict__ mom2, typename Storage<K>::T* __restrict__ dst,
@@ -947,7 +966,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
       }
     }
     if constexpr (OUT == kOutMoments) {
-      if (out_ok && p >= z0 && p < zend) store_moments(mid, pb, ownb / SZ, f);
+      if (out_ok && p >= z0 && p < zend) store_moments<NT>(mid, pb, ownb / SZ, f);
     }
     if (FORCE && SOLIDS)
       collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, (fl & FLAG_NOFORCE) ? C(0) : C(1));
@@ -974,7 +993,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
         uint64_t base = uniform_opaque(reinterpret_cast<uint64_t>(mid));
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-          store_nt_at<T>(base, ownb, cur[i]);
+          store_at<true, T>(base, ownb, cur[i]);
           if (i + 1 < Q) base = uniform_opaque(base + pb);
         }
       }
@@ -1009,7 +1028,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
               link_sel(m_step2, i), raw_bits<K>(prevv[D3Q19::opp[i]]), raw_bits<K>(w))));
       }
       if constexpr (OUT == kOutMoments) {
-        if (out_ok) store_moments(mom2, pb, qownb / SZ, h);
+        if (out_ok) store_moments<NT>(mom2, pb, qownb / SZ, h);
       }
       if (FORCE && SOLIDS)
         collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, (fl_prev & FLAG_NOFORCE) ? C(0) : C(1));
@@ -1022,7 +1041,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
         for (int i = 0; i < Q; ++i) {
           C o = h[i];
           if constexpr (K == ST_F16) o = fp32_result(o);
-          store_nt_at<T>(base, qownb, solid2 ? marker2 : T(o));
+          store_at<NT, T>(base, qownb, solid2 ? marker2 : T(o));
           if (i + 1 < Q) base = uniform_opaque(base + pb);
         }
       }
@@ -1336,7 +1355,7 @@ __device__ __forceinline__ LamMoments lam_moments(const float* lam) {
 // per reverse step instead of 228, and the same bits.  Bound by HBM: 128^3 86 ->
 // 63 us a step (5.6 TB/s), 72 x 80 x 100 porous 36 -> 29 us; the pair pass pays
 // 98 us instead of 88 at 128^3 for storing the moments of its two steps.
-template <bool SOLIDS, bool MOVING, bool SEED, bool MOMS>
+template <bool SOLIDS, bool MOVING, bool SEED, bool MOMS, bool NT>
 __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
                                          const float* __restrict__ nu1, float* __restrict__ nu0,
                                          const uint8_t* __restrict__ flags,
@@ -1409,8 +1428,9 @@ __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
       bool mb[Q];
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
-        const float v = __builtin_nontemporal_load(
-            elem_rx(nu1, pb, i, n.row[1 + D3Q19::cz[i]][1 + D3Q19::cy[i]], n.xn[1 - D3Q19::cx[i]]));
+        const float* p =
+            elem_rx(nu1, pb, i, n.row[1 + D3Q19::cz[i]][1 + D3Q19::cy[i]], n.xn[1 - D3Q19::cx[i]]);
+        const float v = NT ? __builtin_nontemporal_load(p) : *p;
         mb[i] = SOLIDS && i != 0 && raw_bits<ST_F32>(v) == Storage<ST_F32>::kRest;
         lam[i] = v;
       }
@@ -1473,7 +1493,7 @@ __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const float mu = om1 * lam[i] + a0 + cdot<float>(i, bhx, bhy, bhz);
-      stream_store(elem_rx(nu0, pb, i, n.row[1][1], n.xn[1]), solid ? marker : mu);
+      store_kind<NT>(elem_rx(nu0, pb, i, n.row[1][1], n.xn[1]), solid ? marker : mu);
     }
     if (forced && !solid) {
       d[0] += double(fpre * (3.0f * m.L1x - 3.0f * ux * m.L0 + 9.0f * Lux) + 0.5f * bhx);
@@ -1498,10 +1518,10 @@ __global__ __launch_bounds__(kBlock) void k_adj(const float* __restrict__ fprev,
                                                 const float* __restrict__ gu,
                                                 double* __restrict__ partials, Geo g,
                                                 Phys<float> ph) {
-  adj_body<SOLIDS, MOVING, SEED, false>(fprev, nu1, nu0, flags, gr, gu, partials, g, ph);
+  adj_body<SOLIDS, MOVING, SEED, false, true>(fprev, nu1, nu0, flags, gr, gu, partials, g, ph);
 }
 
-template <bool SOLIDS, bool SEED>
+template <bool SOLIDS, bool SEED, bool NT>
 __global__ __launch_bounds__(kBlock) void k_adj_mom(const float* __restrict__ mom,
                                                     const float* __restrict__ nu1,
                                                     float* __restrict__ nu0,
@@ -1510,7 +1530,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_mom(const float* __restrict__ mo
                                                     const float* __restrict__ gu,
                                                     double* __restrict__ partials, Geo g,
                                                     Phys<float> ph) {
-  adj_body<SOLIDS, false, SEED, true>(mom, nu1, nu0, flags, gr, gu, partials, g, ph);
+  adj_body<SOLIDS, false, SEED, true, NT>(mom, nu1, nu0, flags, gr, gu, partials, g, ph);
 }
 
 // dL/du0 = sum_i lam0_i w_i rho0 (3 c_i + 9 (c_i.u0) c_i - 3 u0) = rho0 (3 L1 + 9 L2 u0 - 3 u0 L0),
@@ -1713,7 +1733,7 @@ static StepK<C> make_stepk(const PhysParams& p) {
 constexpr int band_rows(int M) { return M >= 4 ? 16 : 32; }
 
 // Geometry of segments of up to M 64-cell units for the step kernel.
-static Geo step_geo(const Geo& g, int M) {
+[[maybe_unused]] static Geo step_geo(const Geo& g, int M) {
   Geo h = g;
   h.yb = band_rows(M) < g.ny ? band_rows(M) : g.ny;
   h.units = (g.nx + 63) / 64;
@@ -1744,6 +1764,10 @@ static void step_t(const Geo& g, const PhysParams& ph, const void* src, void* ds
                        make_stepk<typename S::C>(ph));
   };
   constexpr int ANY = M > 1 ? 0 : 1;
+  if (!h.stream) {
+    if (M > 1 && h.units % M) return go(k_step_cached<K, WALLS, FORCE, INC, ANY>);
+    return go(k_step_cached<K, WALLS, FORCE, INC, M>);
+  }
   if constexpr (WALLS != 4) {
     if (h.xfill > h.nx) return go(k_step_fill<K, WALLS, FORCE, INC, ANY>);
   }
@@ -1775,12 +1799,11 @@ static void step_mom_f(bool force, const Geo& g, const PhysParams& ph, const flo
                        float* mom, const uint8_t* flags, hipStream_t s) {
   const Geo h = step_geo(g, 1);
   const StepK<float> k = make_stepk<float>(ph);
-  if (force)
-    hipLaunchKernelGGL((k_step_mom<WALLS, true, INC>), dim3(h.nblocks), dim3(kBlock), 0, s, src, dst,
-                       flags, mom, h, k);
-  else
-    hipLaunchKernelGGL((k_step_mom<WALLS, false, INC>), dim3(h.nblocks), dim3(kBlock), 0, s, src,
-                       dst, flags, mom, h, k);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s, src, dst, flags, mom, h, k);
+  };
+  if (force) h.stream ? go(k_step_mom<WALLS, true, INC, true>) : go(k_step_mom<WALLS, true, INC, false>);
+  else h.stream ? go(k_step_mom<WALLS, false, INC, true>) : go(k_step_mom<WALLS, false, INC, false>);
 }
 
 template <bool INC>
@@ -1849,7 +1872,7 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
 // FP32 103 -> 85 us a pass, 128 x 128 x 256 204 -> 155, 200^3 404 -> 329, 256^3
 // 589 -> 541, 200^3 BF16 289 -> 225, 100^3 FP64 130 -> 84; 512^3 keeps its 128
 // planes.)
-static inline Geo2 make_geo2(const Geo& g, int rows, int64_t* cost) {
+[[maybe_unused]] static Geo2 make_geo2(const Geo& g, int rows, int64_t* cost) {
   Geo2 h;
   h.nx = g.nx;
   h.ny = g.ny;
@@ -1899,7 +1922,7 @@ static int tb2_choice(const Geo& g) {
   return best;
 }
 
-template <int K, int WALLS, bool FORCE, bool INC, int OUT, int CHOICE>
+template <int K, int WALLS, bool FORCE, bool INC, int OUT, int CHOICE, bool NT>
 static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                      const uint8_t* flags, const uint32_t* lmask, hipStream_t s, void* mid,
                      float* mom2) {
@@ -1907,7 +1930,7 @@ static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* 
   constexpr int rows = Tb2<K>::choice[CHOICE].rows;
   int64_t cost;
   const Geo2 h = make_geo2(g, rows, &cost);
-  hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT, rows>), dim3(h.nblocks),
+  hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT, rows, NT>), dim3(h.nblocks),
                      dim3(64 * (rows + 3)), 0, s, reinterpret_cast<const typename S::T*>(src),
                      reinterpret_cast<typename S::T*>(mid), mom2,
                      reinterpret_cast<typename S::T*>(dst), flags, lmask, h,
@@ -1918,16 +1941,26 @@ template <int K, int WALLS, bool FORCE, bool INC, int OUT = kOutLast>
 static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s,
                     void* mid = nullptr, float* mom2 = nullptr) {
-  const int c = OUT == kOutMid ? 0 : tb2_choice<K>(g);  // (mid: one instantiation)
-  if constexpr (Tb2<K>::N > 2 && OUT != kOutMid) {
-    if (c == 2)
-      return step2_go<K, WALLS, FORCE, INC, OUT, 2>(g, ph, src, dst, flags, lmask, s, mid, mom2);
+  auto go = [&](auto choice, auto nt) {
+    step2_go<K, WALLS, FORCE, INC, OUT, choice.value, nt.value>(g, ph, src, dst, flags, lmask, s,
+                                                                mid, mom2);
+  };
+  constexpr std::integral_constant<int, 0> c0;
+  // one instantiation for the rare ones: the intermediate level, and resting
+  // walls without the link mask (pairs of direction arrays over 4 GiB)
+  if constexpr (OUT != kOutMid && WALLS != 1) {
+    const int c = tb2_choice<K>(g);
+    if constexpr (Tb2<K>::N > 2) {
+      constexpr std::integral_constant<int, 2> c2;
+      if (c == 2) return g.stream2 ? go(c2, std::true_type{}) : go(c2, std::false_type{});
+    }
+    if constexpr (Tb2<K>::N > 1) {
+      constexpr std::integral_constant<int, 1> c1;
+      if (c == 1) return g.stream2 ? go(c1, std::true_type{}) : go(c1, std::false_type{});
+    }
+    if (!g.stream2) return go(c0, std::false_type{});
   }
-  if constexpr (Tb2<K>::N > 1 && OUT != kOutMid) {
-    if (c == 1)
-      return step2_go<K, WALLS, FORCE, INC, OUT, 1>(g, ph, src, dst, flags, lmask, s, mid, mom2);
-  }
-  step2_go<K, WALLS, FORCE, INC, OUT, 0>(g, ph, src, dst, flags, lmask, s, mid, mom2);
+  go(c0, std::true_type{});
 }
 
 template <int K, int WALLS, bool INC>
@@ -2023,7 +2056,8 @@ void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
 // The step kernels' instantiations, shared out over the parts.
 #define LBM_STEP_K(K)                                                                            \
   template void step_k<K>(bool, bool, const Geo&, const PhysParams&, const void*, void*,         \
-                          const uint8_t*, hipStream_t);                                          \
+                          const uint8_t*, hipStream_t);
+#define LBM_STEP2_K(K)                                                                           \
   template void step2_k<K>(bool, bool, const Geo&, const PhysParams&, const void*, void*,        \
                            const uint8_t*, const uint32_t*, hipStream_t);
 #define LBM_STEP_OUT(INC)                                                                        \
@@ -2036,19 +2070,27 @@ void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
                                               const void*, void*, float*, void*, const uint8_t*, \
                                               const uint32_t*, hipStream_t);
 #if LBM_PART == 1
-LBM_STEP_K(ST_F32)
+LBM_STEP2_K(ST_F32)
 #elif LBM_PART == 2
-LBM_STEP_K(ST_F16)
+LBM_STEP2_K(ST_F16)
 #elif LBM_PART == 3
-LBM_STEP_K(ST_BF16)
+LBM_STEP2_K(ST_BF16)
 #elif LBM_PART == 4
-LBM_STEP_K(ST_F64)
+LBM_STEP2_K(ST_F64)
 #elif LBM_PART == 5
-LBM_STEP_K(ST_F32X)
+LBM_STEP2_K(ST_F32X)
 #elif LBM_PART == 6
 LBM_STEP_OUT(false)
 #elif LBM_PART == 7
 LBM_STEP_OUT(true)
+#elif LBM_PART == 8
+LBM_STEP_K(ST_F16)
+#elif LBM_PART == 9
+LBM_STEP_K(ST_BF16)
+#elif LBM_PART == 10
+LBM_STEP_K(ST_F32)
+LBM_STEP_K(ST_F64)
+LBM_STEP_K(ST_F32X)
 #endif
 
 #if LBM_PART == 0
@@ -2224,8 +2266,11 @@ hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const
     hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s, mom, nu1, nu0, flags, dL_drho,
                        dL_du, partials, h, p);
   };
-  if (solids) nu1 ? go(k_adj_mom<true, false>) : go(k_adj_mom<true, true>);
-  else nu1 ? go(k_adj_mom<false, false>) : go(k_adj_mom<false, true>);
+  auto pick_nt = [&](auto nt) {
+    if (solids) nu1 ? go(k_adj_mom<true, false, nt.value>) : go(k_adj_mom<true, true, nt.value>);
+    else nu1 ? go(k_adj_mom<false, false, nt.value>) : go(k_adj_mom<false, true, nt.value>);
+  };
+  h.stream2 ? pick_nt(std::true_type{}) : pick_nt(std::false_type{});
   return hipGetLastError();
 }
 

@@ -416,3 +416,29 @@ def test_automatic_steps_per_pass(storage, n):
     auto = LBM(shape, 0.6, (1e-5, 0, 0), storage, steps_per_pass="auto", **kw).step(7)
     torch.cuda.synchronize()
     assert _same(one, auto)
+
+
+@pytest.mark.parametrize("spp", [0, 2])
+@pytest.mark.parametrize("storage,below,above", [("f32", (100, 100, 128), (120, 120, 192)),
+                                                 ("f16", (128, 128, 128), (190, 160, 192)),
+                                                 ("f64", (64, 64, 128), (100, 100, 128))])
+def test_store_policies_give_the_same_bits(storage, below, above, spp):
+    """Boxes on both sides of the cache size (plain and non-temporal stores)
+    against lbm_step_from of a context whose own box decides the same way, and
+    one against the other: a z-periodic column of the small box, tiled to the
+    large one's layout, evolves to the same values."""
+    s = 10 if storage == "f16" else 0
+    for shape in (below, above):
+        say("store policy", storage, shape, spp)
+        u0 = torch.zeros((3,) + shape)
+        rng = np.random.default_rng(71)
+        u0[:, :, :20, :20] = torch.from_numpy(0.03 * (rng.random((3, 1, 20, 20)) - 0.5)).float()
+        sim = LBM(shape, 0.6, (1e-5, 0, 0), storage, u0=u0, f16_scale_log2=s,
+                  steps_per_pass=spp).step(4)
+        v = sim.populations()[:, 0, 2:18, 2:18].clone()  # 4 steps reach 4 cells: none wraps
+        torch.cuda.synchronize()
+        if shape == below:
+            ref = v
+        del sim
+    core = slice(2, 14)  # cells whose 4-step neighbourhood lies in the 20 x 20 patch
+    assert torch.equal(ref[:, core, core], v[:, core, core])
