@@ -160,11 +160,12 @@ typedef struct {
                              passes), bit-identical to single steps; an odd
                              remainder is one single step.  Not with
                              obstacle_kernel = 1 (LBM_E_UNSUPPORTED).
-                             LBM_STEPS_AUTO: pairs where the fused pass fills
-                             the GPU (at least 128 blocks of its tiles: from
-                             about 64^3 cells on), single steps elsewhere and
-                             with the split design -- the fastest schedule
-                             measured, the same bits either way. */
+                             LBM_STEPS_AUTO: pairs where they are faster (small
+                             boxes up to about 34^3 cells in FP32 and 50^3 in
+                             the other storages, and boxes from about 64^3 on),
+                             single steps elsewhere and with the split design --
+                             the fastest schedule measured, the same bits either
+                             way. */
 } lbm_params;
 
 typedef struct lbm_ctx lbm_ctx;

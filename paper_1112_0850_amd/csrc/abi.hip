@@ -260,7 +260,7 @@ lbm_status enqueue_steps(lbm_ctx* c, int32_t n, int* cur, hipStream_t s, int32_t
   const bool pairs =
       c->p.steps_per_pass == 2 ||
       (c->p.steps_per_pass == LBM_STEPS_AUTO && c->p.obstacle_kernel == 0 &&
-       lbm::step2_blocks(c->p.storage, c->geo) >= lbm::kStep2MinBlocks);
+       lbm::step2_pays(c->p.storage, c->geo));
   while (n > 0) {
     const int k = *cur;
     if (pairs && n >= 2) {

@@ -36,6 +36,15 @@ struct Geo2 {
   int32_t ntx, nty, zc, nblocks, nb8;
 };
 
+// Launch geometry of the two-step kernel on small boxes: 3-D tiles.
+struct GeoT {
+  int32_t nx, ny, nz;
+  int32_t xs;      // x stride of a population row, in cells
+  uint32_t plane;  // elements from one direction array to the next
+  int32_t tx, ty, tz;
+  int32_t ntx, nty, nblocks, nb8;
+};
+
 constexpr int kBlock = 256;
 constexpr int kReduceBlocks = 1024;
 
@@ -65,14 +74,14 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
 hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
                         const void* src, void* dst, const uint8_t* flags, const uint32_t* lmask,
                         hipStream_t s);
-// Blocks of a two-step launch with the storage's first choice of tile rows.
-int step2_blocks(int storage, const Geo& g);
-// Fewer blocks than this leave most CUs idle, and single steps are faster
-// (periodic boxes, us a step, single / pairs: FP32 48^3, 96 blocks, 5.6 / 8.1;
-// 64^3, 160 blocks, 9.6 / 8.5; 96^3 28.6 / 21.2; FP64 32^3, 112 blocks, 4.3 /
-// 5.9; 48^3, 240 blocks, 9.1 / 6.6; FP16 48^3, 96 blocks, 5.6 / 6.1; 64^3 6.8 /
-// 6.3).
-constexpr int kStep2MinBlocks = 128;
+// Whether two fused steps are faster than two single ones on this grid (they
+// give the same bits).
+bool step2_pays(int storage, const Geo& g);
+// Whether they go through the small-box kernel: us a step, small-box / z-marching
+// kernel, FP32 48^3 4.9 / 6.3, 64^3 7.7 / 7.1; FP64 48^3 5.8 / 6.8, 64^3 10.8 / 10.8.
+inline bool step2_tiles(const Geo& g) {
+  return int64_t(g.nx) * g.ny * g.nz <= (int64_t(1) << 17);
+}
 // The same two steps storing the intermediate level too: mid = f*(t+1)
 // (FP32 storage only: hipErrorInvalidValue otherwise).
 hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,

@@ -1055,6 +1055,141 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
   }
 }
 
+// ---------------------------------------------------------------------------
+// Two fused steps on small boxes.  There the pass above has too few blocks, and
+// a single step's launch (1.7 us of GPU for an empty kernel, 2.6-4 us of host)
+// and load latency cost more than its work.  A block owns a 3-D tile of up to
+// 512 cells: step 1 on the tile and its one-cell halo (up to 1024 cells, two
+// per thread) from src, all 19 results of each cell into LDS, one barrier, step
+// 2 on the tile from there.  Both are the single step's pull, marker test,
+// collision and rounding, so the result has the same bits.  Halo cells are
+// computed by every tile that needs them (2 to 3 times the tile's own work, so
+// only for small boxes: 64^3 FP32 runs 7.1 us a step in z-marching tiles, 7.7
+// here).  Bound by latency and the collisions' issue: 32^3 FP32 2.9 us a step
+// against 3.3-4.1 single, 24^3 2.8 against 3.3-4.1, 48^3 FP64 5.8 against 7.6.
+// ---------------------------------------------------------------------------
+constexpr int kTileThreads = 512;  // of a block; at most as many tile cells, and twice as many with the halo
+
+template <int K, int WALLS, bool FORCE, bool INC, int OUT>
+__global__ __launch_bounds__(kTileThreads, 4) void k_step2_tile(
+    const typename Storage<K>::T* __restrict__ src, float* __restrict__ mom1,
+    float* __restrict__ mom2, typename Storage<K>::T* __restrict__ dst,
+    const uint8_t* __restrict__ flags, GeoT g, StepK<typename Storage<K>::C> k) {
+  using C = typename Storage<K>::C;
+  using T = typename Storage<K>::T;
+  constexpr bool SOLIDS = WALLS >= 1;
+  constexpr uint32_t SZ = sizeof(T);
+  extern __shared__ __align__(16) char tile_lds[];
+  T* lv = reinterpret_cast<T*>(tile_lds);
+  const int b = blockIdx.x;
+  const int lb = (b < g.nb8) ? ((b & 7) * (g.nb8 >> 3) + (b >> 3)) : b;
+  const int bx = lb % g.ntx, by = (lb / g.ntx) % g.nty, bz = lb / (g.ntx * g.nty);
+  const int x0 = bx * g.tx, y0 = by * g.ty, z0 = bz * g.tz;
+  const int EX = g.tx + 2, EY = g.ty + 2, E = EX * EY * (g.tz + 2);
+  const size_t pb = size_t(g.plane) * SZ;
+  const uint32_t rowe = uint32_t(g.xs), zst = uint32_t(g.ny) * rowe;
+  const int tid = int(threadIdx.x);
+  // step 2's cell of this thread
+  const int ox = tid % g.tx, oy = (tid / g.tx) % g.ty, oz = tid / (g.tx * g.ty);
+  const bool out_ok = oz < g.tz && x0 + ox < g.nx && y0 + oy < g.ny && z0 + oz < g.nz;
+  uint8_t fl2 = 0;
+  if (SOLIDS && out_ok)
+    fl2 = flags[(uint32_t(z0 + oz) * uint32_t(g.ny) + uint32_t(y0 + oy)) * uint32_t(g.nx) +
+                uint32_t(x0 + ox)];
+  // step 1 on the extended tile: up to two cells per thread, all their pulls first
+  T nv[2][Q];
+  uint8_t fl[2] = {0, 0};
+  uint32_t own[2] = {0, 0};
+  bool mine[2] = {false, false};
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int e = tid + r * kTileThreads;
+    if (e < E) {
+      const int ez = e / (EX * EY), er = e - ez * (EX * EY), ey = er / EX, ex = er - ey * EX;
+      const int gx = wrap_mod(x0 + ex - 1, g.nx), gy = wrap_mod(y0 + ey - 1, g.ny),
+                gz = wrap_mod(z0 + ez - 1, g.nz);
+      const uint32_t xb[3] = {uint32_t(gx + 1 == g.nx ? 0 : gx + 1), uint32_t(gx),
+                              uint32_t(gx == 0 ? g.nx - 1 : gx - 1)};
+      const uint32_t yb[3] = {uint32_t(gy + 1 == g.ny ? 0 : gy + 1) * rowe, uint32_t(gy) * rowe,
+                              uint32_t(gy == 0 ? g.ny - 1 : gy - 1) * rowe};
+      const uint32_t zb[3] = {uint32_t(gz + 1 == g.nz ? 0 : gz + 1) * zst, uint32_t(gz) * zst,
+                              uint32_t(gz == 0 ? g.nz - 1 : gz - 1) * zst};
+#pragma unroll
+      for (int i = 0; i < Q; ++i)
+        nv[r][i] = *elem(src, pb, i, zb[1 + D3Q19::cz[i]] + yb[1 + D3Q19::cy[i]] +
+                                         xb[1 + D3Q19::cx[i]]);
+      own[r] = zb[1] + yb[1] + xb[1];
+      if (SOLIDS)
+        fl[r] = flags[(uint32_t(gz) * uint32_t(g.ny) + uint32_t(gy)) * uint32_t(g.nx) +
+                      uint32_t(gx)];
+      mine[r] = ex >= 1 && ex <= g.tx && ey >= 1 && ey <= g.ty && ez >= 1 && ez <= g.tz &&
+                x0 + ex - 1 < g.nx && y0 + ey - 1 < g.ny && z0 + ez - 1 < g.nz;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int e = tid + r * kTileThreads;
+    if (e < E) {
+      const bool solid = SOLIDS && (fl[r] & FLAG_SOLID);
+      C f[Q];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        f[i] = C(nv[r][i]);
+        if (SOLIDS && i != 0 && is_marker<K, WALLS>(raw_bits<K>(nv[r][i])) && !solid) {
+          C bb = C(*elem(src, pb, D3Q19::opp[i], own[r]));
+          if (WALLS == 2 && raw_bits<K>(nv[r][i]) == Storage<K>::kMoving) bb += k.Kw[i];
+          f[i] = bb;
+        }
+      }
+      if constexpr (OUT == kOutMoments) {
+        if (mine[r]) store_moments<false>(mom1, pb, own[r], f);
+      }
+      if (FORCE && SOLIDS)
+        collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, (fl[r] & FLAG_NOFORCE) ? C(0) : C(1));
+      else
+        collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, C(1));
+      const T marker = solid_marker<K>(fl[r], WALLS == 2);
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        C o = f[i];
+        if constexpr (K == ST_F16) o = fp32_result(o);
+        lv[i * E + e] = solid ? marker : T(o);
+      }
+    }
+  }
+  __syncthreads();
+  if (!out_ok) return;
+  const int c = ((oz + 1) * EY + oy + 1) * EX + ox + 1;
+  const bool solid2 = SOLIDS && (fl2 & FLAG_SOLID);
+  const uint32_t own2 = uint32_t(z0 + oz) * zst + uint32_t(y0 + oy) * rowe + uint32_t(x0 + ox);
+  C h[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const T w = lv[i * E + c - ((D3Q19::cz[i] * EY + D3Q19::cy[i]) * EX + D3Q19::cx[i])];
+    h[i] = C(w);
+    if (SOLIDS && i != 0 && is_marker<K, WALLS>(raw_bits<K>(w)) && !solid2) {
+      C bb = C(lv[D3Q19::opp[i] * E + c]);
+      if (WALLS == 2 && raw_bits<K>(w) == Storage<K>::kMoving) bb += k.Kw[i];
+      h[i] = bb;
+    }
+  }
+  if constexpr (OUT == kOutMoments) {
+    store_moments<false>(mom2, pb, own2, h);
+    if (!dst) return;
+  }
+  if (FORCE && SOLIDS)
+    collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, (fl2 & FLAG_NOFORCE) ? C(0) : C(1));
+  else
+    collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, C(1));
+  const T marker2 = solid_marker<K>(fl2, WALLS == 2);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    C o = h[i];
+    if constexpr (K == ST_F16) o = fp32_result(o);
+    *elem(dst, pb, i, own2) = solid2 ? marker2 : T(o);
+  }
+}
+
 #if LBM_PART == 0
 // The link mask of every cell for the two-step kernel's resting walls: bit i
 // (1..18) set when the pull along c_i is blocked (x - c_i solid, periodic),
@@ -1937,6 +2072,51 @@ static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* 
                      make_stepk<typename S::C>(ph));
 }
 
+// The tile of the small-box kernel: the least rounds of kCUs blocks times the
+// waves of a block's two steps, the rows its pulls touch weighing a tenth of a
+// wave each (32^3 FP32: 16 x 2 x 4 5.8 us a pass, 8 x 4 x 4 and 32 x 2 x 2 6.2,
+// 8 x 4 x 2 6.8).
+[[maybe_unused]] static GeoT make_geot(const Geo& g) {
+  static constexpr int dims[][3] = {{8, 4, 2}, {16, 2, 4}, {8, 4, 4}, {8, 8, 4}, {12, 6, 6}};
+  GeoT best{};
+  double least = 0.0;
+  for (const auto& d : dims) {
+    GeoT h;
+    h.nx = g.nx;
+    h.ny = g.ny;
+    h.nz = g.nz;
+    h.xs = g.xs;
+    h.plane = g.plane;
+    h.tx = d[0];
+    h.ty = d[1];
+    h.tz = d[2];
+    h.ntx = (g.nx + h.tx - 1) / h.tx;
+    h.nty = (g.ny + h.ty - 1) / h.ty;
+    h.nblocks = h.ntx * h.nty * ((g.nz + h.tz - 1) / h.tz);
+    h.nb8 = h.nblocks / 8 * 8;
+    const int rows = (h.ty + 2) * (h.tz + 2), e = (h.tx + 2) * rows, o = h.tx * h.ty * h.tz;
+    const double c =
+        ((h.nblocks + kCUs - 1) / kCUs) * ((e + 63) / 64 + (o + 63) / 64 + 0.1 * rows);
+    if (!best.nblocks || c < least) {
+      least = c;
+      best = h;
+    }
+  }
+  return best;
+}
+
+template <int K, int WALLS, bool FORCE, bool INC, int OUT>
+static void step2_tile_go(const Geo& g, const PhysParams& ph, const void* src, void* dst,
+                          const uint8_t* flags, hipStream_t s, void* mom1, float* mom2) {
+  using S = Storage<K>;
+  const GeoT h = make_geot(g);
+  const size_t lds = size_t(h.tx + 2) * (h.ty + 2) * (h.tz + 2) * Q * sizeof(typename S::T);
+  hipLaunchKernelGGL((k_step2_tile<K, WALLS, FORCE, INC, OUT>), dim3(h.nblocks), dim3(kTileThreads),
+                     lds, s, reinterpret_cast<const typename S::T*>(src),
+                     static_cast<float*>(mom1), mom2, reinterpret_cast<typename S::T*>(dst), flags,
+                     h, make_stepk<typename S::C>(ph));
+}
+
 template <int K, int WALLS, bool FORCE, bool INC, int OUT = kOutLast>
 static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s,
@@ -1946,6 +2126,11 @@ static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* d
                                                                 mid, mom2);
   };
   constexpr std::integral_constant<int, 0> c0;
+  if constexpr (OUT != kOutMid) {
+    if (step2_tiles(g))
+      return step2_tile_go<K, WALLS == 4 ? 1 : WALLS, FORCE, INC, OUT>(g, ph, src, dst, flags, s,
+                                                                       mid, mom2);
+  }
   // one instantiation for the rare ones: the intermediate level, and resting
   // walls without the link mask (pairs of direction arrays over 4 GiB)
   if constexpr (OUT != kOutMid && WALLS != 1) {
@@ -1999,21 +2184,31 @@ extern template void step2_k<ST_F64>(bool, bool, const Geo&, const PhysParams&, 
 extern template void step2_k<ST_F32X>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
 
+constexpr int64_t kTilePairCellsF32 = 40000;
+
+// Blocks of a z-marching launch with the storage's first choice of tile rows.
 template <int K>
 static int step2_blocks_k(const Geo& g) {
   int64_t cost;
   return make_geo2(g, Tb2<K>::choice[0].rows, &cost).nblocks;
 }
 
-int step2_blocks(int storage, const Geo& g) {
+// Single steps / pairs, us a step: in the small-box kernel FP32 24^3 3.4 / 2.8,
+// 32^3 3.5 / 2.9, 40^3 4.3 / 4.3, porous 40^3 5.2 / 5.6; FP16 porous 48^3 7.0 /
+// 5.6; FP64 40^3 5.9 / 4.6.  In the z-marching kernel fewer blocks than 128
+// leave most CUs idle: FP32 64^3, 160 blocks, 7.4 / 7.1, 96^3 18.6 / 17.8.
+bool step2_pays(int storage, const Geo& g) {
+  if (step2_tiles(g))
+    return storage != ST_F32 || int64_t(g.nx) * g.ny * g.nz <= kTilePairCellsF32;
+  int blocks = 0;
   switch (storage) {
-    case ST_F32: return step2_blocks_k<ST_F32>(g);
-    case ST_F16: return step2_blocks_k<ST_F16>(g);
-    case ST_BF16: return step2_blocks_k<ST_BF16>(g);
-    case ST_F64: return step2_blocks_k<ST_F64>(g);
-    case ST_F32X: return step2_blocks_k<ST_F32X>(g);
-    default: return 0;
+    case ST_F32: blocks = step2_blocks_k<ST_F32>(g); break;
+    case ST_F16: blocks = step2_blocks_k<ST_F16>(g); break;
+    case ST_BF16: blocks = step2_blocks_k<ST_BF16>(g); break;
+    case ST_F64: blocks = step2_blocks_k<ST_F64>(g); break;
+    case ST_F32X: blocks = step2_blocks_k<ST_F32X>(g); break;
   }
+  return blocks >= 128;
 }
 
 hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,

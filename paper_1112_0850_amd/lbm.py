@@ -50,9 +50,9 @@ class LBM:
     ``obstacle_kernel=1`` selects the split design (a separate bounce-back
     kernel before each step) instead of the fused solid markers;
     ``steps_per_pass=2`` runs pairs of steps as one temporally blocked pass
-    (same results, bit for bit); ``steps_per_pass="auto"`` does so where the
-    pass fills the GPU (from about 64^3 cells on) and runs single steps
-    elsewhere."""
+    (same results, bit for bit); ``steps_per_pass="auto"`` does so where pairs
+    are faster (all but FP32 boxes between 34^3 and 64^3 cells) and runs single
+    steps elsewhere."""
 
     def __init__(self, shape, tau, force=(0.0, 0.0, 0.0), storage="f32", flags=None, u0=None,
                  rho0=None, f16_scale_log2=0, x_align=0, device="cuda", wall_u=(0.0, 0.0, 0.0),
@@ -204,9 +204,12 @@ def copy_probe(dst, src, vec_per_thread=1, nontemporal=False, blocks=0, stream=N
 
 
 # The rollout steps in fused pairs from this many cells on, forward and in the
-# recomputation (the same states bit for bit): measured, single / pairs, 48^3
-# 5.6 / 8.1 us a step, 64^3 9.6 / 8.5, 128^3 61 / 42, 256^3 457 / 271.
+# recomputation (the same states bit for bit), and up to FUSED_SMALL_CELLS,
+# where the library's small-box kernel runs them: measured, single / pairs, us a
+# step, 24^3 3.4 / 2.8, 32^3 3.5 / 2.9, 48^3 5.3 / 5.2, 64^3 7.4 / 7.1, 128^3 57 / 41,
+# 256^3 457 / 271.
 FUSED_RECOMPUTE_MIN_CELLS = 1 << 18
+FUSED_SMALL_CELLS = 40000
 
 
 class _Rollout(torch.autograd.Function):
@@ -219,7 +222,8 @@ class _Rollout(torch.autograd.Function):
     @staticmethod
     def forward(ctx, u0, g, steps, tau, flags, k, wall_u, equilibrium, steps_per_pass, need_grad):
         force = [float(v) for v in g.detach().double().cpu().tolist()]
-        fused = math.prod(u0.shape[1:]) >= FUSED_RECOMPUTE_MIN_CELLS
+        cells = math.prod(u0.shape[1:])
+        fused = cells >= FUSED_RECOMPUTE_MIN_CELLS or cells <= FUSED_SMALL_CELLS
         sim = LBM(u0.shape[1:], tau, force, "f32", flags=flags, u0=u0.detach(), device=u0.device,
                   wall_u=wall_u, equilibrium=equilibrium,
                   steps_per_pass=2 if fused and steps_per_pass in (-1, 0, 1) else steps_per_pass)

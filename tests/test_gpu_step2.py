@@ -122,6 +122,26 @@ def test_two_step_pass_tile_rows(storage, shape):
     assert _same(one, two)
 
 
+@pytest.mark.parametrize("geo", ["periodic", "porous", "moving"])
+@pytest.mark.parametrize("shape", [(23, 81, 101), (33, 37, 41), (5, 6, 7), (48, 48, 48)])
+@pytest.mark.parametrize("storage", STORAGES)
+def test_two_step_kernels_on_ragged_boxes(storage, shape, geo):
+    """The z-marching kernel (the first shape) and the small-box kernel (its
+    tile shapes, partial tiles, a box smaller than a tile) in every storage,
+    wall kind and equilibrium: the same bits as single steps."""
+    say("two-step kernels", storage, shape, geo)
+    kw = dict(u0=_u0(shape, 45))
+    if geo != "periodic":
+        kw["flags"] = I.random_flags(shape, 46, solid_fraction=0.15, noforce_fraction=0.1)
+        if geo == "moving":
+            kw["flags"] |= I.cavity_flags(shape)
+            kw["wall_u"] = (0.04, -0.01, 0.02)
+        kw["u0"][:, torch.from_numpy(kw["flags"] & 1 == 1)] = 0
+    for eq, F in (("qian", (2e-5, -1e-5, 3e-5)), ("incompressible", (0, 0, 0))):
+        one, two = _pair(shape, 0.63, F, storage, 5, equilibrium=eq, **kw)
+        assert _same(one, two), eq
+
+
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 def test_two_step_pass_unpadded_and_without_force(storage):
     shape = (6, 10, 65)
