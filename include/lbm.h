@@ -49,7 +49,7 @@
  *    moving-wall marker.  Any other value is data: a NaN or infinity that
  *    arises in a fluid cell (a 16-bit overflow, corrupted input) enters the
  *    neighbours' collisions and so reaches lbm_reduce as a non-finite sum.
- *    (The two-step pass at resting walls decides the same bounce-backs
+ *    (The two-step pass decides the same bounce-backs
  *    from a link mask built from the flags instead, with the same results.)
  *    Padding stays 0.  The library maintains the markers itself (init, step,
  *    save/restore); after writing a grid from outside, call
@@ -211,8 +211,8 @@ lbm_status lbm_solid_markers(int32_t storage, uint64_t* rest, uint64_t* moving);
  *   grid_a, grid_b  two grids of grid_bytes (the two lattices of Sec. 2);
  *   flags           uint8 [nz][ny][nx] or NULL (all fluid);
  *   scratch         scratch_bytes of device memory (lbm_reduce's partials;
- *                   with flags and resting walls, the link mask that the
- *                   two-step pass reads -- bit i of a cell set when its pull
+ *                   with flags, the link mask that the two-step pass
+ *                   reads -- bit i of a cell set when its pull
  *                   along c_i comes from a solid cell, built here from the
  *                   flags);
  *   rho0            float [nz][ny][nx] or NULL (uniform 1);

@@ -214,7 +214,7 @@ struct lbm_ctx {
   void* grid[2];
   const uint8_t* flags;
   double* scratch;
-  uint32_t* lmask;  // the two-step link mask in scratch (resting walls), or NULL
+  uint32_t* lmask;  // the two-step link mask in scratch, or NULL
   hipStream_t stream;
   int32_t cur;
   int64_t t;
@@ -415,7 +415,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
   c->grid[1] = grid_b;
   c->flags = flags;
   c->scratch = static_cast<double*>(scratch);
-  c->lmask = (flags && sz.mask_off && !c->ph.moving)
+  c->lmask = (flags && sz.mask_off)
                  ? reinterpret_cast<uint32_t*>(static_cast<char*>(scratch) + sz.mask_off)
                  : nullptr;
   c->stream = static_cast<hipStream_t>(stream);
@@ -431,7 +431,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
   if (e == hipSuccess) e = lbm::launch_fill_zero(grid_b, sz.grid_bytes, c->stream);
   if (e == hipSuccess)
     e = lbm::launch_init(p->storage, c->geo, c->ph, grid_a, flags, rho0, u0, c->stream);
-  if (e == hipSuccess && c->lmask) e = lbm::launch_link_mask(c->geo, flags, c->lmask, c->stream);
+  if (e == hipSuccess && c->lmask) e = lbm::launch_link_mask(c->geo, c->ph.moving, flags, c->lmask, c->stream);
   if (e != hipSuccess) {
     delete c;
     return hip_fail(e, "initialisation launch");
@@ -584,7 +584,7 @@ lbm_status lbm_refresh_solids(lbm_ctx* c) {
   if (!c->flags) return LBM_OK;
   hipError_t e =
       lbm::launch_mark_solids(c->p.storage, c->geo, c->ph, c->grid[c->cur], c->flags, c->stream);
-  if (e == hipSuccess && c->lmask) e = lbm::launch_link_mask(c->geo, c->flags, c->lmask, c->stream);
+  if (e == hipSuccess && c->lmask) e = lbm::launch_link_mask(c->geo, c->ph.moving, c->flags, c->lmask, c->stream);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "solid marker launch");
 }
 

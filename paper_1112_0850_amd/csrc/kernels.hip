@@ -693,6 +693,10 @@ constexpr int kTB2Arrays = 32;  // LDS plane-arrays of [TY + 2][66]
 // link-mask bits besides the 18 links (bit i: the pull along c_i is blocked)
 constexpr uint32_t kLinkSolid = 1u << 19;
 constexpr uint32_t kLinkNoforce = 1u << 20;
+// with moving walls: one of the blocked links ends at a moving-wall cell; the
+// cell itself is one
+constexpr uint32_t kLinkToMoving = 1u << 21;
+constexpr uint32_t kLinkMoving = 1u << 22;
 // All ones when bit i of m is set, else 0 (one sign-extending bit extract).
 __device__ __forceinline__ uint32_t link_sel(uint32_t m, int i) {
   return uint32_t(__builtin_amdgcn_sbfe(int32_t(m), i, 1));
@@ -831,7 +835,8 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
   constexpr uint32_t SZ = sizeof(T);
   constexpr uint32_t PLB = uint32_t(EY * EX) * SZ;  // bytes of one LDS plane-array
   constexpr bool SOLIDS = WALLS >= 1;
-  constexpr bool LINKS = WALLS == 4;
+  constexpr bool LINKS = WALLS >= 4;
+  constexpr bool MOVING = WALLS == 2 || WALLS == 5;
   constexpr bool MARKERS = SOLIDS && !LINKS;
   static_assert(sizeof(T) * kTB2Arrays * EY * EX <= 160 * 1024, "ring exceeds the LDS of a CU");
   __shared__ T ring[kTB2Arrays * EY * EX];
@@ -919,6 +924,18 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
       nfl = SOLIDS ? flags[uint32_t(pz) * fl_z + fl_yx] : uint8_t(0);
     }
   };
+  // WALLS = 5: adds the wall term to the pulls of plane p that bounced back
+  // from a moving wall (m: the cell's links, 0 for none)
+  auto add_wall_terms = [&](C* v, uint32_t m, int p) __attribute__((always_inline)) {
+    if (!__builtin_amdgcn_ballot_w64((m & kLinkToMoving) != 0)) return;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      if (!((m & kLinkToMoving) && (m >> i & 1u))) continue;
+      const int sx = wrap_mod(gx - D3Q19::cx[i], g.nx), sy = wrap_mod(gy - D3Q19::cy[i], g.ny),
+                sz = wrap_mod(p - D3Q19::cz[i], g.nz);
+      if (flags[(size_t(sz) * g.ny + sy) * g.nx + sx] & FLAG_MOVING) v[i] += k.Kw[i];
+    }
+  };
   // own column's step-1 results: planes p - 1 (prev) and p - 2 (pp5)
   T prevv[Q], pp5 = T(0);
 #pragma unroll
@@ -935,7 +952,8 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
       m1 = m2;
     }
     const uint8_t fl = LINKS ? uint8_t((m0 & kLinkSolid ? FLAG_SOLID : 0) |
-                                       (m0 & kLinkNoforce ? FLAG_NOFORCE : 0))
+                                       (m0 & kLinkNoforce ? FLAG_NOFORCE : 0) |
+                                       (MOVING && (m0 & kLinkMoving) ? FLAG_MOVING : 0))
                              : nfl;
     const bool solid = SOLIDS && (fl & FLAG_SOLID);
     C f[Q];
@@ -965,6 +983,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
         if (i + 2 < Q) base = uniform_opaque(bo + pb);
       }
     }
+    if constexpr (WALLS == 5) add_wall_terms(f, solid ? 0u : m0, p);
     if constexpr (OUT == kOutMoments) {
       if (out_ok && p >= z0 && p < zend) store_moments<NT>(mid, pb, ownb / SZ, f);
     }
@@ -972,14 +991,16 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
       collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, (fl & FLAG_NOFORCE) ? C(0) : C(1));
     else
       collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, C(1));
-    const T marker = solid_marker<K>(fl, WALLS == 2);
+    const T marker = solid_marker<K>(fl, MOVING);
+    // (with the links no step 2 uses a solid cell's values)
+    const bool mark_step1 = solid && (!LINKS || OUT == kOutMid);
     const uint32_t w1 = lane_opaque(lane_b), w2 = phase_base(p, 2), w3 = phase_base(p, 3);
     T cur[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       C o = f[i];
       if constexpr (K == ST_F16) o = fp32_result(o);
-      const T v = solid ? marker : T(o);
+      const T v = mark_step1 ? marker : T(o);
       cur[i] = v;
       if (i != 0 && i != 5 && i != 6) {
         const int tx = ex + D3Q19::cx[i], ty = ey + D3Q19::cy[i];
@@ -1027,6 +1048,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
           h[i] = C(from_bits<K>(pick<typename Storage<K>::U>(
               link_sel(m_step2, i), raw_bits<K>(prevv[D3Q19::opp[i]]), raw_bits<K>(w))));
       }
+      if constexpr (WALLS == 5) add_wall_terms(h, m_step2, q);
       if constexpr (OUT == kOutMoments) {
         if (out_ok) store_moments<NT>(mom2, pb, qownb / SZ, h);
       }
@@ -1034,7 +1056,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
         collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, (fl_prev & FLAG_NOFORCE) ? C(0) : C(1));
       else
         collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, C(1));
-      const T marker2 = solid_marker<K>(fl_prev, WALLS == 2);
+      const T marker2 = solid_marker<K>(fl_prev, MOVING);
       if (out_ok && (OUT != kOutMoments || dst)) {
         uint64_t base = uniform_opaque(dst_u);
 #pragma unroll
@@ -1193,9 +1215,11 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_step2_tile(
 #if LBM_PART == 0
 // The link mask of every cell for the two-step kernel's resting walls: bit i
 // (1..18) set when the pull along c_i is blocked (x - c_i solid, periodic),
-// plus the cell's own SOLID and NOFORCE flags.
+// plus the cell's own SOLID and NOFORCE flags (`moving`: and the moving-wall
+// bits).
 __global__ __launch_bounds__(kBlock) void k_link_mask(const uint8_t* __restrict__ flags,
-                                                      uint32_t* __restrict__ mask, Geo g) {
+                                                      uint32_t* __restrict__ mask, Geo g,
+                                                      int moving) {
   const size_t n = size_t(g.nx) * g.ny * g.nz;
   const size_t idx = size_t(blockIdx.x) * kBlock + threadIdx.x;
   if (idx >= n) return;
@@ -1208,8 +1232,10 @@ __global__ __launch_bounds__(kBlock) void k_link_mask(const uint8_t* __restrict_
   for (int i = 1; i < Q; ++i) {
     const int xs = wrap_mod(x - D3Q19::cx[i], g.nx), ys = wrap_mod(y - D3Q19::cy[i], g.ny),
               zs = wrap_mod(z - D3Q19::cz[i], g.nz);
-    if (flags[(size_t(zs) * g.ny + ys) * g.nx + xs] & FLAG_SOLID) m |= 1u << i;
+    const uint8_t fs = flags[(size_t(zs) * g.ny + ys) * g.nx + xs];
+    if (fs & FLAG_SOLID) m |= 1u << i | (moving && (fs & FLAG_MOVING) ? kLinkToMoving : 0u);
   }
+  if (moving && (fl & FLAG_MOVING)) m |= kLinkMoving;
   mask[idx] = m;
 }
 
@@ -2128,12 +2154,13 @@ static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* d
   constexpr std::integral_constant<int, 0> c0;
   if constexpr (OUT != kOutMid) {
     if (step2_tiles(g))
-      return step2_tile_go<K, WALLS == 4 ? 1 : WALLS, FORCE, INC, OUT>(g, ph, src, dst, flags, s,
+      return step2_tile_go<K, WALLS == 4 ? 1 : (WALLS == 5 ? 2 : WALLS), FORCE, INC, OUT>(g, ph, src, dst, flags, s,
                                                                        mid, mom2);
   }
-  // one instantiation for the rare ones: the intermediate level, and resting
-  // walls without the link mask (pairs of direction arrays over 4 GiB)
-  if constexpr (OUT != kOutMid && WALLS != 1) {
+  // one instantiation for the rare ones: the intermediate level, and walls
+  // without the link mask (pairs of direction arrays over 4 GiB, or a context
+  // made for single steps)
+  if constexpr (OUT != kOutMid && WALLS != 1 && WALLS != 2) {
     const int c = tb2_choice<K>(g);
     if constexpr (Tb2<K>::N > 2) {
       constexpr std::integral_constant<int, 2> c2;
@@ -2155,12 +2182,14 @@ static void step2_f(bool force, const Geo& g, const PhysParams& ph, const void* 
   else step2_t<K, WALLS, false, INC>(g, ph, src, dst, flags, lmask, s);
 }
 
-// walls: none (0), resting with markers (1) or with the link mask (4), moving (2)
+// walls: none (0), resting with markers (1) or with the link mask (4), moving with
+// markers (2) or with the mask (5)
 template <int K, bool INC>
 static void step2_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
                     void* dst, const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (!solids) step2_f<K, 0, INC>(force, g, ph, src, dst, flags, lmask, s);
-  else if (!ph.moving && lmask) step2_f<K, 4, INC>(force, g, ph, src, dst, flags, lmask, s);
+  else if (lmask && !ph.moving) step2_f<K, 4, INC>(force, g, ph, src, dst, flags, lmask, s);
+  else if (lmask) step2_f<K, 5, INC>(force, g, ph, src, dst, flags, lmask, s);
   else if (!ph.moving) step2_f<K, 1, INC>(force, g, ph, src, dst, flags, lmask, s);
   else step2_f<K, 2, INC>(force, g, ph, src, dst, flags, lmask, s);
 }
@@ -2242,8 +2271,9 @@ void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
                         const void* src, void* mid, float* mom2, void* dst, const uint8_t* flags,
                         const uint32_t* lmask, hipStream_t s) {
   if (!solids) step2_out_f<OUT, 0, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
-  else if (!ph.moving && lmask)
+  else if (lmask && !ph.moving)
     step2_out_f<OUT, 4, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
+  else if (lmask) step2_out_f<OUT, 5, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
   else if (!ph.moving) step2_out_f<OUT, 1, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
   else step2_out_f<OUT, 2, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
 }
@@ -2321,10 +2351,11 @@ hipError_t launch_step2_mom(bool solids, bool force, const Geo& g, const PhysPar
   return hipGetLastError();
 }
 
-hipError_t launch_link_mask(const Geo& g, const uint8_t* flags, uint32_t* mask, hipStream_t s) {
+hipError_t launch_link_mask(const Geo& g, bool moving, const uint8_t* flags, uint32_t* mask,
+                            hipStream_t s) {
   const size_t n = size_t(g.nx) * g.ny * g.nz;
   hipLaunchKernelGGL(k_link_mask, dim3(unsigned((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                     flags, mask, g);
+                     flags, mask, g, moving ? 1 : 0);
   return hipGetLastError();
 }
 
