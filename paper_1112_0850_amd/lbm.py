@@ -211,6 +211,12 @@ def copy_probe(dst, src, vec_per_thread=1, nontemporal=False, blocks=0, stream=N
 FUSED_RECOMPUTE_MIN_CELLS = 1 << 18
 FUSED_SMALL_CELLS = 40000
 
+# How much of the device's memory a rollout may take for the moments that its
+# forward sweep keeps beyond the last segment's (288 GB: 4.5 GB, 134 steps of
+# 128^3).  Kept, a step's moments cost the pass that runs anyway 5 us at 128^3;
+# recomputed, half of a 95 us pass.
+KEPT_MOMENTS_SHARE = 1 / 64
+
 
 class _Rollout(torch.autograd.Function):
     """(rho_T, u_T) after `steps` updates from f*(0) = f^eq(1, u0) under the
@@ -231,22 +237,46 @@ class _Rollout(torch.autograd.Function):
             sim.step(steps)
             return sim.macroscopics()
         pairs = fused or steps_per_pass == 2
-        starts = range(0, steps, k)  # a checkpoint at the start of every segment of k steps
-        ckpts = [sim.grids[0]]
-        tmp = sim.new_grid()
+        starts = range(0, steps, k)  # the segments of k steps
         last = len(starts) - 1
+        first = _Rollout.first_kept(sim, steps, k)
+        cur, spare, tmp = sim.grids[0], None, sim.new_grid()
+        ckpts, moms = [], []
         for s, t in enumerate(starts):
+            if s < first:
+                ckpts.append(cur)
+            if s + 1 < first:
+                dst = sim.new_grid()
+            elif first == 0:
+                dst = sim.grids[1 - s % 2]
+            elif (last - s) % 2 == 0:
+                dst = sim.grids[1]
+            else:
+                dst = spare = sim.new_grid() if spare is None else spare
             n = min(k, steps - t)
-            dst = sim.grids[1] if s == last else sim.new_grid()
-            mom = _Rollout.moments(sim, n) if s == last else None
-            A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(tmp), _ptr(dst), n, pairs, _ptr(mom), True)
-            ckpts.append(dst)
-        sim.set_current(1, steps)
+            moms.append(None if s < first else _Rollout.moments(sim, n))
+            A.lbm_segment(sim.ctx, _ptr(cur), _ptr(tmp), _ptr(dst), n, pairs, _ptr(moms[s]), True)
+            cur = dst
+        sim.set_current(0 if cur is sim.grids[0] else 1, steps)
         rho, u = sim.macroscopics()
-        ctx.sim, ctx.ckpts, ctx.steps, ctx.k = sim, ckpts[:-1], steps, k
-        ctx.tmp, ctx.mom, ctx.fused = tmp, mom, fused
+        ctx.sim, ctx.ckpts, ctx.steps, ctx.k = sim, ckpts, steps, k
+        ctx.tmp, ctx.moms, ctx.fused = tmp, moms, fused
         ctx.g_meta = (g.dtype, g.device)
         return rho, u
+
+    @staticmethod
+    def first_kept(sim, steps, k):
+        """The first segment whose moments the forward sweep keeps: as many of the
+        latest ones as fit in KEPT_MOMENTS_SHARE of the device's memory, but the
+        last one alone where less than half of that memory is free."""
+        last = (steps - 1) // k
+        if last == 0:
+            return 0
+        free, total = torch.cuda.mem_get_info(sim.device)
+        if 2 * free < total:
+            return last
+        fit = int(KEPT_MOMENTS_SHARE * total) // (16 * sim.dir_stride)  # steps
+        return min(last, max(0, -((fit - steps) // k)))
 
     @staticmethod
     def moments(sim, n):
@@ -258,7 +288,7 @@ class _Rollout(torch.autograd.Function):
         from nu^{n+1} at f(n) for n = T-1 .. 1, then dL/du0 from nu^1; the
         moments of the f(n) are recomputed segment by segment from the
         checkpoints, latest segment first."""
-        sim, ckpts, steps, k = ctx.sim, ctx.ckpts, ctx.steps, ctx.k
+        sim, ckpts, moms, steps, k = ctx.sim, ctx.ckpts, ctx.moms, ctx.steps, ctx.k
         dev = sim.device
         nfl = sim.grid_bytes // 4
         nu = [torch.empty(nfl, dtype=torch.float32, device=dev) for _ in range(2)]
@@ -266,12 +296,11 @@ class _Rollout(torch.autograd.Function):
         gr = None if g_rho is None else g_rho.to(torch.float32).contiguous()
         gu = None if g_u is None else g_u.to(torch.float32).contiguous()
         cur, mom = 0, None
-        for s in range(len(ckpts) - 1, -1, -1):
-            seed = s == len(ckpts) - 1
+        for s in range(len(moms) - 1, -1, -1):
+            seed = s == len(moms) - 1
             n = min(k, steps - s * k)
-            if seed:
-                seg = ctx.mom
-            else:
+            seg = moms[s]
+            if seg is None:
                 mom = _Rollout.moments(sim, k) if mom is None else mom
                 seg = mom
                 A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(ctx.tmp), _ptr(sim.grids[1]), n,

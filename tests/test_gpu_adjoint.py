@@ -11,6 +11,7 @@ import torch
 from oracle import oracle as O
 from paper_1112_0850_amd import _abi as A
 from paper_1112_0850_amd import inputs as I
+from paper_1112_0850_amd import lbm
 from paper_1112_0850_amd.lbm import LBM, rollout
 from tests.gpu_util import f_to_grid, from_nu_grid, grid_to_f, rel_linf, say, to_nu_grid
 from tests.test_oracle_adjoint import rollout_grad, rollout_loss
@@ -296,3 +297,28 @@ def test_segments_equal_single_calls(geo, pairs):
         A.lbm_segment(sim.ctx, P(states[0]), None, P(dst), 5, 0, None, True)
     with pytest.raises(A.LBMError):
         A.lbm_segment(sim.ctx, P(states[0]), P(tmp), P(dst), 1, 0, None, False)
+
+
+@pytest.mark.parametrize("shape", [(6, 15, 70), (24, 20, 40)])
+@pytest.mark.parametrize("every", [1, 2, 5])
+def test_kept_moments_give_the_recomputed_gradients(shape, every, monkeypatch):
+    """The moments of no segment, of some and of all of them kept by the forward
+    sweep: the same fields and gradients bit for bit."""
+    say("kept moments", shape, every)
+    steps = 11
+    rng = np.random.default_rng(12)
+    start = torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float().cuda()
+    flags = I.random_flags(shape, 61, solid_fraction=0.1)
+    sim = LBM(shape, 0.7, storage="f32")
+    total = torch.cuda.mem_get_info()[1]
+    runs = []
+    for kept in (0, 4, 7, steps):
+        monkeypatch.setattr(lbm, "KEPT_MOMENTS_SHARE", (kept + 0.5) * 16 * sim.dir_stride / total)
+        u0 = start.clone().requires_grad_(True)
+        g = torch.tensor([2e-5, -1e-5, 1e-5], dtype=torch.float64, requires_grad=True)
+        rho, u = rollout(u0, g, steps=steps, tau=0.7, flags=flags, checkpoint_every=every)
+        ((u * u).sum() + 0.3 * (rho * rho).sum()).backward()
+        runs.append((rho.detach(), u.detach(), u0.grad, g.grad))
+    for run in runs[1:]:
+        for a, b in zip(run, runs[0]):
+            assert torch.equal(a, b), every
