@@ -455,7 +455,11 @@ __device__ __forceinline__ void store_kind(T* p, T v) {
 }
 
 // delta_rho and j of a pre-collision state into the four moment arrays (FP32,
-// pb bytes apart): all that the transposed collision needs of the state.
+// pb bytes apart): all that the transposed collision needs of the state.  Each
+// is read once, a whole rollout later, so they pass the memory-side cache by on
+// both ways and leave it to the grids: 72 x 80 x 100 FP32, 24 steps forward and
+// backward, 1.24 -> 1.18 ms.  (Boxes of the small-box kernel stay in the cache
+// with all of their moments.)
 template <bool NT>
 __device__ __forceinline__ void store_moments(float* mom, size_t pb, uint32_t own, const float* f) {
   float m[4];
@@ -551,7 +555,7 @@ __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restr
   }
   if constexpr (MOM) {
     static_assert(M == 1 && K == ST_F32, "moments of FP32 grids, one cell per lane");
-    if (valid[0]) store_moments<NT>(mom, pb, n[0].own, f[0]);
+    if (valid[0]) store_moments<true>(mom, pb, n[0].own, f[0]);
     if (!dst) return;
   }
 #pragma unroll
@@ -985,7 +989,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
     }
     if constexpr (WALLS == 5) add_wall_terms(f, solid ? 0u : m0, p);
     if constexpr (OUT == kOutMoments) {
-      if (out_ok && p >= z0 && p < zend) store_moments<NT>(mid, pb, ownb / SZ, f);
+      if (out_ok && p >= z0 && p < zend) store_moments<true>(mid, pb, ownb / SZ, f);
     }
     if (FORCE && SOLIDS)
       collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(f, k, (fl & FLAG_NOFORCE) ? C(0) : C(1));
@@ -1050,7 +1054,7 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
       }
       if constexpr (WALLS == 5) add_wall_terms(h, m_step2, q);
       if constexpr (OUT == kOutMoments) {
-        if (out_ok) store_moments<NT>(mom2, pb, qownb / SZ, h);
+        if (out_ok) store_moments<true>(mom2, pb, qownb / SZ, h);
       }
       if (FORCE && SOLIDS)
         collide<C, FORCE, K == ST_F16, INC, K == ST_F32>(h, k, (fl_prev & FLAG_NOFORCE) ? C(0) : C(1));
@@ -1552,10 +1556,10 @@ __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
     const size_t pb = size_t(g.plane) * sizeof(float);
     float drho, jx, jy, jz;
     if constexpr (MOMS) {
-      drho = *elem(fprev, pb, 0, n.own);
-      jx = *elem(fprev, pb, 1, n.own);
-      jy = *elem(fprev, pb, 2, n.own);
-      jz = *elem(fprev, pb, 3, n.own);
+      drho = __builtin_nontemporal_load(elem(fprev, pb, 0, n.own));
+      jx = __builtin_nontemporal_load(elem(fprev, pb, 1, n.own));
+      jy = __builtin_nontemporal_load(elem(fprev, pb, 2, n.own));
+      jz = __builtin_nontemporal_load(elem(fprev, pb, 3, n.own));
     } else {
       // f(n) = P f*(n-1), exactly as the forward pull
       float f[Q];

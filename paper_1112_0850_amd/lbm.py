@@ -231,7 +231,7 @@ class _Rollout(torch.autograd.Function):
         cells = math.prod(u0.shape[1:])
         fused = cells >= FUSED_RECOMPUTE_MIN_CELLS or cells <= FUSED_SMALL_CELLS
         sim = LBM(u0.shape[1:], tau, force, "f32", flags=flags, u0=u0.detach(), device=u0.device,
-                  wall_u=wall_u, equilibrium=equilibrium,
+                  x_align=_Rollout.row_align(u0.shape[1:]), wall_u=wall_u, equilibrium=equilibrium,
                   steps_per_pass=2 if fused and steps_per_pass in (-1, 0, 1) else steps_per_pass)
         if not need_grad:
             sim.step(steps)
@@ -263,6 +263,18 @@ class _Rollout(torch.autograd.Function):
         ctx.tmp, ctx.moms, ctx.fused = tmp, moms, fused
         ctx.g_meta = (g.dtype, g.device)
         return rho, u
+
+    @staticmethod
+    def row_align(shape):
+        """Rows padded to 16 bytes only, where two such grids stay in the 256 MB cache
+        and the rows span a sixteenth fewer of the 128-byte lines in which it is
+        read (24 steps and back: 72 x 80 x 100 1.19 -> 1.11 ms, 100^3 1.90 -> 1.67,
+        120^3 3.25 -> 2.52; 90^3, where 4% are saved, 1.35 -> 1.40).  Grids streamed
+        from memory want their rows on 64-byte sectors (a reverse step of 200^3 314
+        us padded, 355 tight) and keep the default."""
+        nz, ny, nx = shape
+        tight, lines = -(-nx // 4) * 4, -(-nx // 32) * 32
+        return 4 if 16 * tight <= 15 * lines and 2 * 76 * nz * ny * tight <= 256 << 20 else 0
 
     @staticmethod
     def first_kept(sim, steps, k):
