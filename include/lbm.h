@@ -364,6 +364,18 @@ lbm_status lbm_adjoint_segment(lbm_ctx* ctx, const float* moments, int32_t n, in
                                const float* dL_drho, const float* dL_du, float* nu_a, float* nu_b,
                                double* dLdF_partials);
 
+/* Two reverse steps in one pass over the grid, nu^{m+2} -> nu^m, from the
+ * moments of f(m+1) (mom_later) and of f(m) (mom_earlier), records as
+ * lbm_segment stores them.  The same nu as two reverse steps, bit for bit;
+ * dL/dF is summed in another order (FP64).  nu_in and nu_out must differ.
+ * LBM_E_UNSUPPORTED where lbm_adjoint_pairs returns 0: with solid cells when the
+ * context has no link mask (steps_per_pass 2 or LBM_STEPS_AUTO, two direction
+ * arrays below 4 GiB), and on boxes so flat that the pass has more blocks than
+ * partials has records. */
+int32_t lbm_adjoint_pairs(const lbm_ctx* ctx);
+lbm_status lbm_adjoint_pair(lbm_ctx* ctx, const float* mom_later, const float* mom_earlier,
+                            const float* nu_in, float* nu_out, double* dLdF_partials);
+
 /* Initial-state adjoint from nu^1: lambda^0 = P^T nu^1 (gathered as above),
  * dL/du0 = sum_i lambda^0_i d f^eq_i/du (rho0, u0), written as float
  * [3][nz][ny][nx] (0 on solid cells).  rho0 / u0 as passed to lbm_init

@@ -62,6 +62,8 @@ _SIGNATURES = {
     "lbm_adjoint_step": (_st, [_vp, _vp, _vp, _vp, _vp]),
     "lbm_segment": (_st, [_vp, _vp, _vp, _vp, C.c_int32, C.c_int32, _vp, C.c_int32]),
     "lbm_adjoint_segment": (_st, [_vp, _vp, C.c_int32, C.c_int32, _vp, _vp, _vp, _vp, _vp]),
+    "lbm_adjoint_pairs": (C.c_int32, [_vp]),
+    "lbm_adjoint_pair": (_st, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "lbm_adjoint_init": (_st, [_vp, _vp, _vp, _vp, _vp]),
     "lbm_adjoint_finish_dF": (_st, [_vp, _vp, _vp]),
     "lbm_stream_copy": (_st, [_vp, _vp, C.c_size_t, _vp]),
@@ -225,6 +227,14 @@ def lbm_adjoint_step(ctx, fstar_prev, nu_np1, nu_n, partials):
 def lbm_adjoint_segment(ctx, moments, n, seed, dL_drho, dL_du, nu_a, nu_b, partials):
     check(lib().lbm_adjoint_segment(ctx, moments, int(n), int(bool(seed)), dL_drho, dL_du, nu_a,
                                     nu_b, partials))
+
+
+def lbm_adjoint_pairs(ctx):
+    return bool(lib().lbm_adjoint_pairs(ctx))
+
+
+def lbm_adjoint_pair(ctx, mom_later, mom_earlier, nu_in, nu_out, partials):
+    check(lib().lbm_adjoint_pair(ctx, mom_later, mom_earlier, nu_in, nu_out, partials))
 
 
 def lbm_adjoint_init(ctx, nu_1, rho0, u0, dL_du0):

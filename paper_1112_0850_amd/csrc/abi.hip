@@ -699,6 +699,29 @@ lbm_status lbm_adjoint_segment(lbm_ctx* c, const float* moments, int32_t n, int3
   return LBM_OK;
 }
 
+int32_t lbm_adjoint_pairs(const lbm_ctx* c) {
+  return c && c->p.storage == LBM_F32 && !(c->flags && !c->lmask) && lbm::adj_pair_fits(c->geo);
+}
+
+lbm_status lbm_adjoint_pair(lbm_ctx* c, const float* mom_later, const float* mom_earlier,
+                            const float* nu_in, float* nu_out, double* partials) {
+  lbm_status st = adj_check(c);
+  if (st != LBM_OK) return st;
+  if (!mom_later || !mom_earlier || !nu_in || !nu_out || !partials)
+    return fail(LBM_E_ARG, "the moments, nu_in, nu_out and partials must not be NULL");
+  if (nu_in == nu_out) return fail(LBM_E_ARG, "nu_in and nu_out must differ");
+  if (!aligned256(nu_in) || !aligned256(nu_out))
+    return fail(LBM_E_ARG, "nu_in and nu_out must be 256-byte aligned");
+  if ((reinterpret_cast<uintptr_t>(mom_later) | reinterpret_cast<uintptr_t>(mom_earlier)) & 3u)
+    return fail(LBM_E_ARG, "the moments must be 4-byte aligned");
+  if (!lbm_adjoint_pairs(c))
+    return fail(LBM_E_UNSUPPORTED, "two reverse steps per pass need the link mask of two steps "
+                                   "per pass and at least as many blocks of cells");
+  hipError_t e = lbm::launch_adj_pair(c->geo, c->ph, mom_later, mom_earlier, nu_in, nu_out,
+                                      c->flags ? c->lmask : nullptr, partials, c->stream);
+  return e == hipSuccess ? LBM_OK : hip_fail(e, "adjoint pair launch");
+}
+
 lbm_status lbm_adjoint_init(lbm_ctx* c, const float* nu_1, const float* rho0, const float* u0,
                             float* dL_du0) {
   lbm_status st = adj_check(c);

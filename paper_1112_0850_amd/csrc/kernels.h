@@ -121,6 +121,11 @@ hipError_t launch_adj_step(bool solids, const Geo& g, const PhysParams& ph, cons
 hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const float* mom,
                           const uint8_t* flags, const float* dL_drho, const float* dL_du,
                           const float* nu1, float* nu0, double* partials, hipStream_t s);
+// Two reverse steps from stored moments; lmask NULL when there are no solids.
+bool adj_pair_fits(const Geo& g);
+hipError_t launch_adj_pair(const Geo& g, const PhysParams& ph, const float* mom1, const float* mom2,
+                           const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
+                           hipStream_t s);
 hipError_t launch_adj_init(bool solids, const Geo& g, const PhysParams& ph, const uint8_t* flags,
                            const float* nu1, const float* rho0, const float* u0, float* dL_du0,
                            hipStream_t s);

@@ -1500,6 +1500,62 @@ __device__ __forceinline__ LamMoments lam_moments(const float* lam) {
   return m;
 }
 
+// Force and velocity of a state from its moments, as the transposed collision
+// needs them.
+struct AdjState {
+  float Fx, Fy, Fz, rho, inv_rho, ux, uy, uz;
+  bool inc;
+};
+
+__device__ __forceinline__ AdjState adj_state(float drho, float jx, float jy, float jz, bool forced,
+                                              const Phys<float>& ph) {
+  AdjState s;
+  s.Fx = forced ? ph.F[0] : 0.0f;
+  s.Fy = forced ? ph.F[1] : 0.0f;
+  s.Fz = forced ? ph.F[2] : 0.0f;
+  s.inc = ph.incomp != 0;
+  s.rho = s.inc ? 1.0f : 1.0f + drho;  // the density dividing j' in u
+  s.inv_rho = s.inc ? 1.0f : 1.0f / s.rho;
+  s.ux = (jx + 0.5f * s.Fx) * s.inv_rho;
+  s.uy = (jy + 0.5f * s.Fy) * s.inv_rho;
+  s.uz = (jz + 0.5f * s.Fz) * s.inv_rho;
+  return s;
+}
+
+// lam -> nu^n = J(f(n))^T lam in place; dF = JF(f(n))^T lam.
+__device__ __forceinline__ void adj_collide(float* lam, const AdjState& s, const Phys<float>& ph,
+                                            float* dF) {
+  const float Fx = s.Fx, Fy = s.Fy, Fz = s.Fz, ux = s.ux, uy = s.uy, uz = s.uz;
+  const float inv_rho = s.inv_rho;
+  const bool inc = s.inc;
+  const float om = ph.omega, om1 = 1.0f - om, fpre = 1.0f - 0.5f * om;
+  const LamMoments m = lam_moments(lam);
+  const float Lux = m.Lxx * ux + m.Lxy * uy + m.Lxz * uz;
+  const float Luy = m.Lxy * ux + m.Lyy * uy + m.Lyz * uz;
+  const float Luz = m.Lxz * ux + m.Lyz * uy + m.Lzz * uz;
+  const float LFx = m.Lxx * Fx + m.Lxy * Fy + m.Lxz * Fz;
+  const float LFy = m.Lxy * Fx + m.Lyy * Fy + m.Lyz * Fz;
+  const float LFz = m.Lxz * Fx + m.Lyz * Fy + m.Lzz * Fz;
+  const float uu = ux * ux + uy * uy + uz * uz;
+  const float a = inc ? om * m.L0
+                      : om * (m.L0 + 3.0f * (m.L1x * ux + m.L1y * uy + m.L1z * uz) +
+                              4.5f * (ux * Lux + uy * Luy + uz * Luz) - 1.5f * uu * m.L0);
+  const float orho = om * s.rho;
+  const float bx = orho * (3.0f * m.L1x + 9.0f * Lux - 3.0f * ux * m.L0) +
+                   fpre * (9.0f * LFx - 3.0f * Fx * m.L0);
+  const float by = orho * (3.0f * m.L1y + 9.0f * Luy - 3.0f * uy * m.L0) +
+                   fpre * (9.0f * LFy - 3.0f * Fy * m.L0);
+  const float bz = orho * (3.0f * m.L1z + 9.0f * Luz - 3.0f * uz * m.L0) +
+                   fpre * (9.0f * LFz - 3.0f * Fz * m.L0);
+  const float bhx = bx * inv_rho, bhy = by * inv_rho, bhz = bz * inv_rho;
+  const float a0 = inc ? a : a - (bhx * ux + bhy * uy + bhz * uz);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) lam[i] = om1 * lam[i] + a0 + cdot<float>(i, bhx, bhy, bhz);
+  dF[0] = fpre * (3.0f * m.L1x - 3.0f * ux * m.L0 + 9.0f * Lux) + 0.5f * bhx;
+  dF[1] = fpre * (3.0f * m.L1y - 3.0f * uy * m.L0 + 9.0f * Luy) + 0.5f * bhy;
+  dF[2] = fpre * (3.0f * m.L1z - 3.0f * uz * m.L0 + 9.0f * Luz) + 0.5f * bhz;
+}
+
 // The adjoint carries nu^n = dL/df(n), the adjoint of the pre-collision state
 // f(n) = P f*(n-1) (P: the pull with half-way bounce-back).  With
 // lambda^n = dL/df*(n) = P^T nu^{n+1}, one reverse step in pull form is
@@ -1606,13 +1662,7 @@ __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
       }
     }
     const bool forced = !(fl & FLAG_NOFORCE);
-    const float Fx = forced ? ph.F[0] : 0.0f, Fy = forced ? ph.F[1] : 0.0f,
-                Fz = forced ? ph.F[2] : 0.0f;
-    const bool inc = ph.incomp != 0;
-    const float rho = inc ? 1.0f : 1.0f + drho;  // the density dividing j' in u
-    const float inv_rho = inc ? 1.0f : 1.0f / rho;
-    const float ux = (jx + 0.5f * Fx) * inv_rho, uy = (jy + 0.5f * Fy) * inv_rho,
-                uz = (jz + 0.5f * Fz) * inv_rho;
+    const AdjState st = adj_state(drho, jx, jy, jz, forced, ph);
     if (SEED) {
       // lambda^T_i = dL/drho + dL/du . (c_i - u)/rho  (dL/du . c_i when incompressible);
       // u = (j + F/2)/rho of f(T) equals the velocity read from f*(T)
@@ -1620,11 +1670,11 @@ __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
       float hx = 0.0f, hy = 0.0f, hz = 0.0f;
       if (gu) {
         const size_t ncell = size_t(g.nx) * g.ny * g.nz;
-        hx = gu[n.fown] * inv_rho;
-        hy = gu[ncell + n.fown] * inv_rho;
-        hz = gu[2 * ncell + n.fown] * inv_rho;
+        hx = gu[n.fown] * st.inv_rho;
+        hy = gu[ncell + n.fown] * st.inv_rho;
+        hz = gu[2 * ncell + n.fown] * st.inv_rho;
       }
-      const float base = inc ? G : G - (hx * ux + hy * uy + hz * uz);
+      const float base = st.inc ? G : G - (hx * st.ux + hy * st.uy + hz * st.uz);
 #pragma unroll
       for (int i = 0; i < Q; ++i) lam[i] = base + cdot<float>(i, hx, hy, hz);
       if (forced && !solid) {
@@ -1633,37 +1683,15 @@ __device__ __forceinline__ void adj_body(const float* __restrict__ fprev,
         d[2] = -double(hz) / 2.0;
       }
     }
-    const float om = ph.omega, om1 = 1.0f - om, fpre = 1.0f - 0.5f * om;
-    const LamMoments m = lam_moments(lam);
-    const float Lux = m.Lxx * ux + m.Lxy * uy + m.Lxz * uz;
-    const float Luy = m.Lxy * ux + m.Lyy * uy + m.Lyz * uz;
-    const float Luz = m.Lxz * ux + m.Lyz * uy + m.Lzz * uz;
-    const float LFx = m.Lxx * Fx + m.Lxy * Fy + m.Lxz * Fz;
-    const float LFy = m.Lxy * Fx + m.Lyy * Fy + m.Lyz * Fz;
-    const float LFz = m.Lxz * Fx + m.Lyz * Fy + m.Lzz * Fz;
-    const float uu = ux * ux + uy * uy + uz * uz;
-    const float a = inc ? om * m.L0
-                        : om * (m.L0 + 3.0f * (m.L1x * ux + m.L1y * uy + m.L1z * uz) +
-                                4.5f * (ux * Lux + uy * Luy + uz * Luz) - 1.5f * uu * m.L0);
-    const float orho = om * rho;
-    const float bx = orho * (3.0f * m.L1x + 9.0f * Lux - 3.0f * ux * m.L0) +
-                     fpre * (9.0f * LFx - 3.0f * Fx * m.L0);
-    const float by = orho * (3.0f * m.L1y + 9.0f * Luy - 3.0f * uy * m.L0) +
-                     fpre * (9.0f * LFy - 3.0f * Fy * m.L0);
-    const float bz = orho * (3.0f * m.L1z + 9.0f * Luz - 3.0f * uz * m.L0) +
-                     fpre * (9.0f * LFz - 3.0f * Fz * m.L0);
-    const float bhx = bx * inv_rho, bhy = by * inv_rho, bhz = bz * inv_rho;
-    const float a0 = inc ? a : a - (bhx * ux + bhy * uy + bhz * uz);
+    float dF[3];
+    adj_collide(lam, st, ph, dF);
     const float marker = from_bits<ST_F32>(Storage<ST_F32>::kRest);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      const float mu = om1 * lam[i] + a0 + cdot<float>(i, bhx, bhy, bhz);
-      store_kind<NT>(elem_rx(nu0, pb, i, n.row[1][1], n.xn[1]), solid ? marker : mu);
-    }
+    for (int i = 0; i < Q; ++i)
+      store_kind<NT>(elem_rx(nu0, pb, i, n.row[1][1], n.xn[1]), solid ? marker : lam[i]);
     if (forced && !solid) {
-      d[0] += double(fpre * (3.0f * m.L1x - 3.0f * ux * m.L0 + 9.0f * Lux) + 0.5f * bhx);
-      d[1] += double(fpre * (3.0f * m.L1y - 3.0f * uy * m.L0 + 9.0f * Luy) + 0.5f * bhy);
-      d[2] += double(fpre * (3.0f * m.L1z - 3.0f * uz * m.L0 + 9.0f * Luz) + 0.5f * bhz);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d[k] += double(dF[k]);
     }
   }
   block_sum<3>(d, sh);
@@ -1696,6 +1724,194 @@ __global__ __launch_bounds__(kBlock) void k_adj_mom(const float* __restrict__ mo
                                                     double* __restrict__ partials, Geo g,
                                                     Phys<float> ph) {
   adj_body<SOLIDS, false, SEED, true, NT>(mom, nu1, nu0, flags, gr, gu, partials, g, ph);
+}
+
+// Two reverse steps in one pass over the grid, from stored moments: the two-step
+// kernel's tiles, ring and z march (k_step2, which see), with the transposed
+// collision in the place of the collision.  A reverse step pulls
+// lambda_i(x) = nu_i(x + c_i), so slot j of the pass holds direction opp j: it is
+// pulled from x - c_j as in the forward pass, a link blocked on that side takes
+// nu_j of the own cell, and the link mask reads the same both ways.  mom1 are
+// the moments of the first reverse step's state (the later one), mom2 the
+// second's.  184 B per cell and two steps (16 B of moments each) in place of
+// 336, bound by memory: 128^3 64 us a step -> 43, 256^3 501 -> 327 and with solids
+// 640 -> 383 (their blocked pulls cost the single step a dependent reload).
+// Non-temporal stores also where the grids fit the cache: 112^3 39 -> 32 us, 64
+// x 64 x 64 9.9 -> 9.4, porous 100^3 33 -> 34.  dL/dF is summed per thread over the
+// march, then over the block, and added to partials[block].
+template <bool SOLIDS, int TY>
+__global__ __launch_bounds__(64 * (TY + 3)) void k_adj2(
+    const float* __restrict__ mom1, const float* __restrict__ mom2, const float* __restrict__ nu2,
+    float* __restrict__ nu0, const uint32_t* __restrict__ lmask, double* __restrict__ partials,
+    Geo2 g, Phys<float> ph) {
+  constexpr int TX = 64, EX = TX + 2, EY = TY + 2;
+  constexpr uint32_t SZ = sizeof(float);
+  constexpr uint32_t PLB = uint32_t(EY * EX) * SZ;
+  static_assert(sizeof(float) * kTB2Arrays * EY * EX + 24 * (TY + 3) <= 160 * 1024,
+                "ring exceeds the LDS of a CU");
+  __shared__ float ring[kTB2Arrays * EY * EX];
+  __shared__ double wsum[TY + 3][3];
+  const int b = blockIdx.x;
+  const int lb = (b < g.nb8) ? ((b & 7) * (g.nb8 >> 3) + (b >> 3)) : b;
+  const int x0 = (lb % g.ntx) * TX;
+  const int y0 = ((lb / g.ntx) % g.nty) * TY;
+  const int z0 = (lb / (g.ntx * g.nty)) * g.zc;
+  const int zend = min(z0 + g.zc, g.nz);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = int(threadIdx.x & 63);
+  int ex = lane, ey = wave - 1;
+  if (wave == TY + 2) {  // the halo columns, as in k_step2
+    ey = lane < 2 * EY ? (lane >> 1) - 1 : TY;
+    ex = (lane & 1) ? TX : -1;
+  }
+  const int gx = wrap_mod(x0 + ex, g.nx), gy = wrap_mod(y0 + ey, g.ny);
+  const bool interior = wave >= 1 && wave <= TY;
+  const bool out_ok = interior && x0 + ex < g.nx && y0 + ey < g.ny;
+  const uint32_t rowb = uint32_t(g.xs) * SZ;
+  const uint32_t xb_[3] = {uint32_t(gx + 1 == g.nx ? 0 : gx + 1) * SZ, uint32_t(gx) * SZ,
+                           uint32_t(gx == 0 ? g.nx - 1 : gx - 1) * SZ};
+  const uint32_t yb_[3] = {uint32_t(gy + 1 == g.ny ? 0 : gy + 1) * rowb, uint32_t(gy) * rowb,
+                           uint32_t(gy == 0 ? g.ny - 1 : gy - 1) * rowb};
+  const uint32_t zstride = uint32_t(g.ny) * rowb;
+  const uint32_t own_yx = yb_[1] + xb_[1];
+  const uint32_t fl_yx = uint32_t(gy) * uint32_t(g.nx) + uint32_t(gx);
+  const uint32_t fl_z = uint32_t(g.ny) * uint32_t(g.nx);
+  const uint64_t src_u = reinterpret_cast<uint64_t>(nu2), dst_u = reinterpret_cast<uint64_t>(nu0);
+  const uint64_t m1_u = reinterpret_cast<uint64_t>(mom1), m2_u = reinterpret_cast<uint64_t>(mom2);
+  const uint64_t pb = uint64_t(g.plane) * SZ;
+  const uint32_t lane_b = uint32_t((ey + 1) * EX + ex + 1) * SZ;
+  auto ring_at = [&](uint32_t base, int i, int dy, int dx) -> float& {
+    return *reinterpret_cast<float*>(reinterpret_cast<char*>(ring) + base +
+                                     (uint32_t(tb2_base(i)) * PLB + uint32_t((dy * EX + dx) * int(SZ))));
+  };
+  auto phase_base = [&](int p, int ns) { return lane_opaque(lane_b + uint32_t(wrap_mod(p, ns)) * PLB); };
+  float nv[Q], n1[4], n2[4];  // the next plane's pulls and moments, and step 2's moments
+  uint32_t m0 = 0, m1 = 0, m2 = 0;
+  auto mask_at = [&](int p) { return lmask[uint32_t(wrap_mod(p, g.nz)) * fl_z + fl_yx]; };
+  auto moments_at = [&](float* m, uint64_t mom, uint32_t own) {
+    uint64_t base = uniform_opaque(mom);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      m[i] = load_at<float>(base, own);
+      if (i < 3) base = uniform_opaque(base + pb);
+    }
+  };
+  auto issue = [&](int p) {
+    const int pz = wrap_mod(p, g.nz);
+    const uint32_t zb_[3] = {uint32_t(pz + 1 == g.nz ? 0 : pz + 1) * zstride, uint32_t(pz) * zstride,
+                             uint32_t(pz == 0 ? g.nz - 1 : pz - 1) * zstride};
+    const uint32_t m = m1, own = zb_[1] + own_yx, pb32 = uint32_t(pb);
+    uint64_t base = uniform_opaque(src_u);
+    nv[0] = load_at<float>(base, own);
+    base = uniform_opaque(base + pb);
+    // pairs (i, i + 1) = (c, -c): slot i reads array i + 1 and slot i + 1 array i
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) {
+      const uint32_t ni = zb_[1 + D3Q19::cz[i]] + yb_[1 + D3Q19::cy[i]] + xb_[1 + D3Q19::cx[i]];
+      const uint32_t nj =
+          zb_[1 + D3Q19::cz[i + 1]] + yb_[1 + D3Q19::cy[i + 1]] + xb_[1 + D3Q19::cx[i + 1]];
+      if constexpr (SOLIDS) {  // 32-bit offsets over two arrays, checked on the host
+        nv[i] = load_at<float>(base, pick(link_sel(m, i), own, pb32 + ni));
+        nv[i + 1] = load_at<float>(base, pick(link_sel(m, i + 1), pb32 + own, nj));
+        if (i + 2 < Q) base = uniform_opaque(base + 2 * pb);
+      } else {
+        nv[i + 1] = load_at<float>(base, nj);
+        base = uniform_opaque(base + pb);
+        nv[i] = load_at<float>(base, ni);
+        if (i + 2 < Q) base = uniform_opaque(base + pb);
+      }
+    }
+    moments_at(n1, m1_u, own);
+    if constexpr (SOLIDS) m2 = mask_at(p + 1);
+  };
+  float prevv[Q], pp5 = 0.0f;  // own column's first results: planes p - 1 and p - 2 (slot 5)
+#pragma unroll
+  for (int i = 0; i < Q; ++i) prevv[i] = 0.0f;
+  uint32_t m_prev = 0;
+  double d[3] = {0.0, 0.0, 0.0};
+  if constexpr (SOLIDS) m1 = mask_at(z0 - 1);
+  issue(z0 - 1);
+  for (int p = z0 - 1; p <= zend; ++p) {
+    if constexpr (SOLIDS) {
+      m0 = m1;
+      m1 = m2;
+    }
+    const int q = p - 1;
+    const uint32_t qownb = uint32_t(wrap_mod(q, g.nz)) * zstride + own_yx;
+    const bool solid = SOLIDS && (m0 & kLinkSolid), forced = !SOLIDS || !(m0 & kLinkNoforce);
+    float lam[Q], dF[3];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) lam[D3Q19::opp[i]] = nv[i];
+    adj_collide(lam, adj_state(n1[0], n1[1], n1[2], n1[3], forced, ph), ph, dF);
+    if (out_ok && p >= z0 && p < zend && forced && !solid) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d[k] += double(dF[k]);
+    }
+    const uint32_t w1 = lane_opaque(lane_b), w2 = phase_base(p, 2), w3 = phase_base(p, 3);
+    float cur[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      cur[i] = lam[D3Q19::opp[i]];
+      if (i != 0 && i != 5 && i != 6) {
+        const int tx = ex + D3Q19::cx[i], ty = ey + D3Q19::cy[i];
+        if (tx >= -1 && tx <= TX && ty >= -1 && ty <= TY)
+          ring_at(tb2_nslot(i) == 3 ? w3 : (tb2_nslot(i) == 2 ? w2 : w1), i, D3Q19::cy[i],
+                  D3Q19::cx[i]) = cur[i];
+      }
+    }
+    if (q >= z0) moments_at(n2, m2_u, qownb);
+    if (p < zend) issue(p + 1);
+    __syncthreads();
+    if (interior && q >= z0) {
+      const bool solid2 = SOLIDS && (m_prev & kLinkSolid), forced2 = !SOLIDS || !(m_prev & kLinkNoforce);
+      const uint32_t m_step2 = solid2 ? 0u : m_prev;
+      const uint32_t r3 = phase_base(p - 2, 3), r2 = phase_base(q, 2);
+      float h[Q];
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        float w;
+        if (i == 0) w = prevv[0];
+        else if (i == 5) w = pp5;
+        else if (i == 6) w = cur[6];
+        else w = ring_at(D3Q19::cz[i] > 0 ? r3 : (D3Q19::cz[i] == 0 ? r2 : w1), i, 0, 0);
+        if (SOLIDS && i != 0)
+          w = from_bits<ST_F32>(pick<uint32_t>(link_sel(m_step2, i),
+                                               raw_bits<ST_F32>(prevv[D3Q19::opp[i]]),
+                                               raw_bits<ST_F32>(w)));
+        h[D3Q19::opp[i]] = w;
+      }
+      adj_collide(h, adj_state(n2[0], n2[1], n2[2], n2[3], forced2, ph), ph, dF);
+      if (out_ok) {
+        if (forced2 && !solid2) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) d[k] += double(dF[k]);
+        }
+        const float marker = from_bits<ST_F32>(Storage<ST_F32>::kRest);
+        uint64_t base = uniform_opaque(dst_u);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          store_at<true, float>(base, qownb, solid2 ? marker : h[i]);
+          if (i + 1 < Q) base = uniform_opaque(base + pb);
+        }
+      }
+    }
+    __syncthreads();
+    pp5 = prevv[5];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) prevv[i] = cur[i];
+    m_prev = m0;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    for (int s = 32; s > 0; s >>= 1) d[k] += __shfl_down(d[k], s, 64);
+    if (lane == 0) wsum[wave][k] = d[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    double sum = 0.0;
+    for (int w = 0; w < TY + 3; ++w) sum += wsum[w][threadIdx.x];
+    partials[size_t(lb) * 3 + threadIdx.x] += sum;
+  }
 }
 
 // dL/du0 = sum_i lam0_i w_i rho0 (3 c_i + 9 (c_i.u0) c_i - 3 u0) = rho0 (3 L1 + 9 L2 u0 - 3 u0 L0),
@@ -2501,6 +2717,39 @@ hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const
     else nu1 ? go(k_adj_mom<false, false, nt.value>) : go(k_adj_mom<false, true, nt.value>);
   };
   h.stream2 ? pick_nt(std::true_type{}) : pick_nt(std::false_type{});
+  return hipGetLastError();
+}
+
+// Two reverse steps from stored moments (k_adj2) with the tile rows of the
+// forward pass; with solids the link mask is needed.
+template <int CHOICE>
+static void adj2_go(const Geo& g, const PhysParams& ph, const float* mom1, const float* mom2,
+                    const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
+                    hipStream_t s) {
+  constexpr int rows = Tb2<ST_F32>::choice[CHOICE].rows;
+  int64_t cost;
+  const Geo2 h = make_geo2(g, rows, &cost);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(64 * (rows + 3)), 0, s, mom1, mom2, nu2, nu0,
+                       lmask, partials, h, to_phys<float>(ph));
+  };
+  lmask ? go(k_adj2<true, rows>) : go(k_adj2<false, rows>);
+}
+
+bool adj_pair_fits(const Geo& g) {
+  int64_t cost;  // one record of partials per block
+  return make_geo2(g, Tb2<ST_F32>::choice[tb2_choice<ST_F32>(g)].rows, &cost).nblocks <= g.nblocks;
+}
+
+hipError_t launch_adj_pair(const Geo& g, const PhysParams& ph, const float* mom1, const float* mom2,
+                           const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
+                           hipStream_t s) {
+  static_assert(Tb2<ST_F32>::N == 3, "tile rows");
+  switch (tb2_choice<ST_F32>(g)) {
+    case 1: adj2_go<1>(g, ph, mom1, mom2, nu2, nu0, lmask, partials, s); break;
+    case 2: adj2_go<2>(g, ph, mom1, mom2, nu2, nu0, lmask, partials, s); break;
+    default: adj2_go<0>(g, ph, mom1, mom2, nu2, nu0, lmask, partials, s); break;
+  }
   return hipGetLastError();
 }
 

@@ -291,6 +291,14 @@ class _Rollout(torch.autograd.Function):
         return min(last, max(0, -((fit - steps) // k)))
 
     @staticmethod
+    def adjoint_pairs(sim):
+        """Whether the reverse sweep runs in pairs of steps, paired by their distance
+        from the end alone (so that dL/dF, summed pass by pass, does not depend on
+        the checkpoints).  Measured, us a step, single / pairs: 48^3 7.4 / 9.0, 64^3
+        11.0 / 10.4, 100^3 38 / 30, 128^3 64 / 43, 256^3 501 / 327."""
+        return math.prod(sim.shape) >= FUSED_RECOMPUTE_MIN_CELLS and A.lbm_adjoint_pairs(sim.ctx)
+
+    @staticmethod
     def moments(sim, n):
         return torch.empty(n * 4 * sim.dir_stride, dtype=torch.float32, device=sim.device)
 
@@ -307,19 +315,41 @@ class _Rollout(torch.autograd.Function):
         partials = torch.empty(sim.adj_partials_bytes // 8, dtype=torch.float64, device=dev)
         gr = None if g_rho is None else g_rho.to(torch.float32).contiguous()
         gu = None if g_u is None else g_u.to(torch.float32).contiguous()
-        cur, mom = 0, None
+        record = 4 * sim.dir_stride
+        pairs = _Rollout.adjoint_pairs(sim)
+        cur, mom, left = 0, None, None  # left: a state whose reverse step waits for the next pair
         for s in range(len(moms) - 1, -1, -1):
             seed = s == len(moms) - 1
             n = min(k, steps - s * k)
             seg = moms[s]
             if seg is None:
-                mom = _Rollout.moments(sim, k) if mom is None else mom
+                if mom is None:
+                    mom = _Rollout.moments(sim, k)
+                elif left is not None:
+                    left = left.clone()
                 seg = mom
                 A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(ctx.tmp), _ptr(sim.grids[1]), n,
                               ctx.fused, _ptr(seg), False)
-            A.lbm_adjoint_segment(sim.ctx, _ptr(seg), n, seed, _ptr(gr), _ptr(gu), _ptr(nu[cur]),
+            if not pairs:
+                A.lbm_adjoint_segment(sim.ctx, _ptr(seg), n, seed, _ptr(gr), _ptr(gu),
+                                      _ptr(nu[cur]), _ptr(nu[cur ^ 1]), _ptr(partials))
+                cur ^= (n - seed) & 1
+                continue
+            states = [seg[j * record:(j + 1) * record] for j in range(n - 1, -1, -1)]
+            if seed:
+                A.lbm_adjoint_segment(sim.ctx, _ptr(states.pop(0)), 1, True, _ptr(gr), _ptr(gu),
+                                      _ptr(nu[0]), None, _ptr(partials))
+            for state in states:
+                if left is None:
+                    left = state
+                    continue
+                A.lbm_adjoint_pair(sim.ctx, _ptr(left), _ptr(state), _ptr(nu[cur]),
+                                   _ptr(nu[cur ^ 1]), _ptr(partials))
+                cur, left = cur ^ 1, None
+        if left is not None:
+            A.lbm_adjoint_segment(sim.ctx, _ptr(left), 1, False, None, None, _ptr(nu[cur]),
                                   _ptr(nu[cur ^ 1]), _ptr(partials))
-            cur ^= (n - seed) & 1
+            cur ^= 1
         du0 = torch.empty((3,) + sim.shape, dtype=torch.float32, device=dev)
         A.lbm_adjoint_init(sim.ctx, _ptr(nu[cur]), _ptr(sim.rho0), _ptr(sim.u0), _ptr(du0))
         dF = torch.empty(3, dtype=torch.float64, device=dev)

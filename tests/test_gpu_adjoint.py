@@ -327,3 +327,89 @@ def test_kept_moments_give_the_recomputed_gradients(shape, every, monkeypatch):
     for run in runs[1:]:
         for a, b in zip(run, runs[0]):
             assert torch.equal(a, b), every
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 13, 64), (6, 15, 70), (3, 9, 130), (40, 21, 33),
+                                   (64, 64, 64), (6, 520, 520), (1, 1, 300)])
+@pytest.mark.parametrize("geo", ["box", "porous", "moving", "incompressible"])
+def test_adjoint_pair_equals_two_steps(shape, geo):
+    """lbm_adjoint_pair against two reverse steps from the same moments: nu bit
+    for bit, dL/dF to the rounding of FP64 sums of at most 2^22 terms (their
+    magnitudes' sum times 2^-53 and the depth of the sum, below 1e-12)."""
+    say("adjoint pair", shape, geo)
+    rng = np.random.default_rng(9)
+    kw = {"u0": torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float()}
+    if geo in ("porous", "moving"):
+        fl = I.random_flags(shape, 52, solid_fraction=0.2, noforce_fraction=0.1)
+        if geo == "moving":
+            fl |= I.cavity_flags(shape)
+            kw["wall_u"] = (0.03, 0.01, -0.02)
+        kw["u0"][:, torch.from_numpy(fl & 1 == 1)] = 0
+        kw["flags"] = fl
+    elif geo == "incompressible":
+        kw["equilibrium"] = geo
+    sim = LBM(shape, 0.6, (2e-5, -1e-5, 1e-5), "f32", steps_per_pass=2, **kw)
+    gr = torch.from_numpy(rng.standard_normal(shape)).float().cuda()
+    gu = torch.from_numpy(rng.standard_normal((3,) + shape)).float().cuda()
+    record = 4 * sim.dir_stride
+    mom = torch.zeros(3 * record, dtype=torch.float32, device="cuda")
+    tmp, dst = sim.new_grid(), sim.new_grid()
+    A.lbm_segment(sim.ctx, P(sim.grids[0]), P(tmp), P(dst), 3, 0, P(mom), True)
+    nfl = sim.grid_bytes // 4
+    seed, a, b, pair = (torch.zeros(nfl, device="cuda") for _ in range(4))
+    parts = [torch.zeros(sim.adj_partials_bytes // 8, dtype=torch.float64, device="cuda")
+             for _ in range(2)]
+    for part in parts:
+        A.lbm_adjoint_segment(sim.ctx, P(mom[2 * record:]), 1, True, P(gr), P(gu), P(seed), None,
+                              P(part))
+    a.copy_(seed)
+    args = (P(mom[record:]), P(mom), P(seed), P(pair), P(parts[1]))
+    if shape == (1, 1, 300):
+        assert not A.lbm_adjoint_pairs(sim.ctx)
+        with pytest.raises(A.LBMError):  # more tiles than records of partials
+            A.lbm_adjoint_pair(sim.ctx, *args)
+        return
+    A.lbm_adjoint_segment(sim.ctx, P(mom), 2, False, None, None, P(a), P(b), P(parts[0]))
+    A.lbm_adjoint_pair(sim.ctx, *args)
+    keep = torch.zeros(sim.dir_stride, dtype=torch.bool, device="cuda")
+    xs = sim.x_stride
+    keep[:shape[0] * shape[1] * xs].view(shape[0], shape[1], xs)[:, :, :shape[2]] = True
+    x, y = (v[:19 * sim.dir_stride].view(19, -1)[:, keep].view(torch.int32) for v in (a, pair))
+    assert torch.equal(x, y)
+    d0, d1 = (part.view(-1, 3) for part in parts)
+    scale = d0.abs().sum(0).clamp_min(1e-30)
+    assert float(((d0.sum(0) - d1.sum(0)).abs() / scale).max()) < 1e-12
+    for bad in ((None,) + args[1:], args[:3] + (P(seed),) + args[4:]):
+        with pytest.raises(A.LBMError):
+            A.lbm_adjoint_pair(sim.ctx, *bad)
+
+
+@pytest.mark.parametrize("steps,shape", [(1, (64, 64, 70)), (2, (64, 64, 70)), (6, (64, 64, 70)),
+                                         (7, (64, 64, 70)), (5, (1, 1, 1 << 18))])
+def test_reverse_pairs_do_not_depend_on_the_checkpoints(steps, shape, monkeypatch):
+    """Rollouts of the size that runs its reverse sweep in pairs (and one too flat
+    for them): the same bits with every spacing and with and without kept
+    moments, and the gradients of a sweep of single steps (dL/dF to FP64
+    rounding)."""
+    say("reverse pairs", steps, shape)
+    rng = np.random.default_rng(13)
+    start = torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float().cuda()
+    flags = I.random_flags(shape, 62, solid_fraction=0.1)
+
+    def run(every, share):
+        monkeypatch.setattr(lbm, "KEPT_MOMENTS_SHARE", share)
+        u0 = start.clone().requires_grad_(True)
+        g = torch.tensor([2e-5, -1e-5, 1e-5], dtype=torch.float64, requires_grad=True)
+        rho, u = rollout(u0, g, steps=steps, tau=0.7, flags=flags, checkpoint_every=every)
+        ((u * u).sum() + 0.3 * (rho * rho).sum()).backward()
+        return u0.grad, g.grad
+
+    ref = run(steps, 1 / 64)
+    for every in (1, 2, 3):
+        for share in (0.0, 1 / 64):
+            got = run(every, share)
+            assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), (every, share)
+    monkeypatch.setattr(lbm._Rollout, "adjoint_pairs", staticmethod(lambda sim: False))
+    got = run(steps, 1 / 64)
+    assert torch.equal(got[0], ref[0])
+    assert float((got[1] - ref[1]).abs().max()) <= 1e-11 * float(ref[1].abs().max())
