@@ -161,8 +161,9 @@ typedef struct {
                              remainder is one single step.  Not with
                              obstacle_kernel = 1 (LBM_E_UNSUPPORTED).
                              LBM_STEPS_AUTO: pairs where they are faster (small
-                             boxes up to about 34^3 cells in FP32 and 50^3 in
-                             the other storages, and boxes from about 64^3 on),
+                             boxes up to about 32^3 cells, and boxes from 64^3 on
+                             in FP32 and FP64, about 74^3 with 16-bit storage and
+                             102^3 in F32X),
                              single steps elsewhere and with the split design --
                              the fastest schedule measured, the same bits either
                              way. */

@@ -2433,7 +2433,6 @@ extern template void step2_k<ST_F64>(bool, bool, const Geo&, const PhysParams&, 
 extern template void step2_k<ST_F32X>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
 
-constexpr int64_t kTilePairCellsF32 = 40000;
 
 // Blocks of a z-marching launch with the storage's first choice of tile rows.
 template <int K>
@@ -2442,13 +2441,25 @@ static int step2_blocks_k(const Geo& g) {
   return make_geo2(g, Tb2<K>::choice[0].rows, &cost).nblocks;
 }
 
-// Single steps / pairs, us a step: in the small-box kernel FP32 24^3 3.4 / 2.8,
-// 32^3 3.5 / 2.9, 40^3 4.3 / 4.3, porous 40^3 5.2 / 5.6; FP16 porous 48^3 7.0 /
-// 5.6; FP64 40^3 5.9 / 4.6.  In the z-marching kernel fewer blocks than 128
-// leave most CUs idle: FP32 64^3, 160 blocks, 7.4 / 7.1, 96^3 18.6 / 17.8.
+// Single steps / pairs, us a step.  In the small-box kernel pairs win where one
+// round of blocks with tiles of at most 128 cells covers the box: FP32 24^3 3.4 /
+// 2.5, 32^3 3.6 / 3.2 (porous 4.2 / 3.9), FP16 32^3 3.2 / 2.5, FP64 5.3 / 3.5;
+// past that only some do (29 x 26 x 46 porous FP32 4.4 / 5.2, box F32X 3.6 / 3.8,
+// FP64 5.2 / 4.2).  In the z-marching kernel fewer
+// blocks than 128 leave most CUs idle, and a pass of few planes per block fills
+// the ring more than it uses it; by storage from the size where no kind of
+// wall loses more than 2%: FP32 56 x 60 x 72 porous 10.7 / 11.9, 64^3 8.9 / 8.8,
+// 96^3 24.0 / 23.7; FP64 14.8 / 15.7, 13.2 / 12.8, 57 / 46; BF16 64^3 cavity 7.6
+// / 8.4, 80^3 18.1 / 14.6; F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33.
 bool step2_pays(int storage, const Geo& g) {
-  if (step2_tiles(g))
-    return storage != ST_F32 || int64_t(g.nx) * g.ny * g.nz <= kTilePairCellsF32;
+  if (step2_tiles(g)) {
+    const GeoT h = make_geot(g);
+    return h.nblocks <= kCUs && h.tx * h.ty * h.tz <= 128;
+  }
+  const int64_t least = storage == ST_F32X                          ? 1 << 20
+                        : storage == ST_F32 || storage == ST_F64 ? 1 << 18
+                                                                  : 400000;
+  if (int64_t(g.nx) * g.ny * g.nz < least) return false;
   int blocks = 0;
   switch (storage) {
     case ST_F32: blocks = step2_blocks_k<ST_F32>(g); break;

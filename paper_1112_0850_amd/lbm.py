@@ -209,7 +209,7 @@ def copy_probe(dst, src, vec_per_thread=1, nontemporal=False, blocks=0, stream=N
 # step, 24^3 3.4 / 2.8, 32^3 3.5 / 2.9, 48^3 5.3 / 5.2, 64^3 7.4 / 7.1, 128^3 57 / 41,
 # 256^3 457 / 271.
 FUSED_RECOMPUTE_MIN_CELLS = 1 << 18
-FUSED_SMALL_CELLS = 40000
+FUSED_SMALL_CELLS = 1 << 15
 
 # How much of the device's memory a rollout may take for the moments that its
 # forward sweep keeps beyond the last segment's (288 GB: 4.5 GB, 134 steps of
