@@ -212,7 +212,7 @@ FUSED_RECOMPUTE_MIN_CELLS = 1 << 18
 FUSED_SMALL_CELLS = 1 << 15
 
 # How much of the device's memory a rollout may take for the moments that its
-# forward sweep keeps beyond the last segment's (288 GB: 4.5 GB, 134 steps of
+# forward sweep keeps beyond the last segment's (288 GB: 4.5 GB, about 140 steps of
 # 128^3).  Kept, a step's moments cost the pass that runs anyway 5 us at 128^3;
 # recomputed, half of a 95 us pass.
 KEPT_MOMENTS_SHARE = 1 / 64
