@@ -724,6 +724,9 @@ __device__ __forceinline__ U pick(uint32_t sel, U a, U b) {
   }
 }
 constexpr int kTB2MinChunk = 2;  // shortest z chunk (planes per block)
+// The longest: blocks that march further drift apart and find less of their
+// halos in L2 (640^3 FP16 with chunks of 640 planes 76.5k MLUPS, of 128 83k).
+constexpr int kTB2MaxChunk = 128;
 constexpr int kCUs = 256;
 
 // Tile rows per block, the first the one that large grids take: 13 (16 waves,
@@ -2265,7 +2268,7 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
   const int64_t tiles = int64_t(h.ntx) * h.nty;
   *cost = INT64_MAX;
   h.zc = g.nz;
-  for (int n = 1; n <= g.nz; ++n) {
+  for (int n = (g.nz + kTB2MaxChunk - 1) / kTB2MaxChunk; n <= g.nz; ++n) {
     const int zc = (g.nz + n - 1) / n;
     if (zc < kTB2MinChunk && n > 1) break;
     const int64_t rounds = (tiles * ((g.nz + zc - 1) / zc) + kCUs - 1) / kCUs;
@@ -2281,11 +2284,12 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
 }
 
 // The choice of tile rows for a grid: the first unless another one's time, by
-// the same measure, is 6% less (the halo rows of smaller tiles cost memory
-// traffic that the measure leaves out).  Measured, us a pass, 13 rows against
-// the chosen: FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256
-// 171 / 157 (8), 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4); 200^3 and from
-// 256^3 on keep the first.
+// the same measure, is 6% less, in boxes of more than 2^23 cells 12% (the halo
+// rows of smaller tiles cost memory traffic that the measure leaves out, and the
+// more so the longer the pass runs: 640^3 with 10 rows, 7% less by the measure,
+// FP16 78k MLUPS against 84k with 13).  Measured, us a pass, 13 rows against the
+// chosen: FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256 171 /
+// 157 (8), 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4).
 template <int K>
 static int tb2_choice(const Geo& g) {
   int best = 0;
@@ -2294,7 +2298,7 @@ static int tb2_choice(const Geo& g) {
     int64_t planes;
     make_geo2(g, Tb2<K>::choice[i].rows, &planes);
     const double c = double(planes) * Tb2<K>::choice[i].cost;
-    if (i == 0) least = 0.94 * c;
+    if (i == 0) least = (int64_t(g.nx) * g.ny * g.nz > (1 << 23) ? 0.88 : 0.94) * c;
     else if (c < least) {
       least = c;
       best = i;
