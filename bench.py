@@ -564,21 +564,23 @@ def launch_threads(name, n):
     """Threads a launch of the named kernel has on an n^3 box (64 * M-cell
     segments per row, four per block, M = 4 for the 16-bit step kernels; the
     two-step kernel: 64 x TY tiles, TY its sixth template argument, z chunks
-    of the length with the least rounds of 256 blocks times planes plus four,
-    64 (TY + 3) threads per block).  Recorded traces whose two-step kernel
+    of the length up to 128 planes with the least rounds of 256 blocks times
+    planes plus four, 64 (TY + 3) threads per block; the adjoint's pair kernel
+    the same with TY its second).  Recorded traces whose two-step kernel
     ends in a truth value had TY = 13 (5 for FP64, 8 for F32X) and z chunks
     of 128 planes halved down to 16 until there were 1280 blocks."""
-    if name.startswith("void lbm::k_step2<"):
+    if name.startswith(("void lbm::k_step2<", "void lbm::k_adj2<")):
         args = [a.strip() for a in name.split("<")[1].split(">")[0].split(",")]
-        old = args[4] in ("true", "false")
-        ty = {"3": 5, "4": 8}.get(args[0], 13) if old else int(args[5])
+        old = len(args) > 4 and args[4] in ("true", "false")
+        ty = {"3": 5, "4": 8}.get(args[0], 13) if old else int(args[5 if len(args) > 2 else 1])
         tiles = -(-n // 64) * -(-n // ty)
         if old:
             zc = min(n, 128)
             while zc > 16 and tiles * -(-n // zc) < 1280:
                 zc = max(zc // 2, 16)
         else:
-            lengths = sorted({-(-n // c) for c in range(1, n + 1)} - {1} or {1}, reverse=True)
+            lengths = sorted({-(-n // c) for c in range(-(-n // 128), n + 1)} - {1} or {1},
+                             reverse=True)
             zc = min(lengths, key=lambda z: -(-(tiles * -(-n // z)) // 256) * (z + 4))
         return tiles * -(-n // zc) * 64 * (ty + 3)
     m = 4 if name.startswith("void lbm::k_step<1,") or name.startswith("void lbm::k_step<2,") else 1
@@ -590,10 +592,13 @@ def box_of(name, grid):
     """The box edge of a launch from its grid size, trying the bench's own
     sizes first: two boxes can give the two-step kernel launches of the same
     size, and the bench runs it at 512^3 (and 768^3) on
-    the porous box and at 256^3 (and 128^3) on the adjoint's periodic box,
-    without solids (walls = 0)."""
-    periodic2 = name.startswith("void lbm::k_step2<") and name.split("<")[1].split(",")[1].strip() == "0"
+    the porous box and at 256^3 (and 128^3, with its 8-row tiles) on the
+    adjoint's periodic box, without solids (walls = 0)."""
+    args = [a.strip() for a in name.split("<")[1].split(">")[0].split(",")] if "<" in name else []
+    periodic2 = name.startswith("void lbm::k_step2<") and args[1] == "0"
     order = (256, 128, 512, 768, 640) if periodic2 else (512, 768, 640, 256, 128)
+    if name.startswith("void lbm::k_adj2<") or (periodic2 and args[5:6] == ["8"]):
+        order = (128, 256) if args[-1 if "adj2" in name else 5] == "8" else (256, 128)
     return next((n for n in order if launch_threads(name, n) == grid), None)
 
 
