@@ -245,8 +245,7 @@ lbm_status lbm_step_from(lbm_ctx* ctx, const void* src, void* dst);
  * (the steps of lbm_step_from twice, bit for bit): `mid` receives f*(t+1)
  * and `dst` f*(t+2); the context's own grids and time are untouched.  src,
  * mid and dst must be distinct, 256-byte aligned grids of the context's
- * layout.  Used by the adjoint's recomputation of the forward states
- * between checkpoints (one read of f* per two states).  Errors: LBM_E_ARG,
+ * layout (one read of f* per two states).  Errors: LBM_E_ARG,
  * LBM_E_UNSUPPORTED (storage other than LBM_F32, or obstacle_kernel = 1),
  * LBM_E_HIP. */
 lbm_status lbm_step2_from(lbm_ctx* ctx, const void* src, void* mid, void* dst);

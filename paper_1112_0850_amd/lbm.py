@@ -366,7 +366,10 @@ def rollout(u0, g, *, steps, tau, flags=None, checkpoint_every=20, wall_u=(0.0, 
     equilibrium are supported (no gradient for the wall velocity).
     ``steps_per_pass=2`` runs the forward sweep in fused pairs of steps on
     every box, not only where they are faster (the same states bit for bit, so
-    the same gradients)."""
+    the same gradients).  The reverse sweep needs 16 B per cell of every state:
+    those of the latest steps are kept, up to 1/64 of the device's memory while
+    half of it is free, the others recomputed from checkpoints every
+    ``checkpoint_every`` steps (the gradients are the same for any spacing)."""
     if u0.dim() != 4 or u0.shape[0] != 3:
         raise ValueError("u0 must be [3, nz, ny, nx]")
     if g.numel() != 3:
