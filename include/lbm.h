@@ -68,11 +68,11 @@
  *                    (+ 6 w_i (c_i . u_w) if x - c_i is a moving wall).
  *  - Velocity: u = (j + F/2)/rho with Qian's equilibrium, u = j + F/2 with
  *    the incompressible one (rho0 = 1), j = sum f_i c_i.
- *  - Every pointer is device memory owned by the caller, 256-byte aligned,
- *    and must stay valid while work that uses it is queued.  Calls enqueue
- *    on the context's stream and return without synchronising; nothing in
- *    this library allocates device memory (the optional step graphs of
- *    lbm_use_graphs are the HIP runtime's).
+ *  - Every pointer is device memory owned by the caller, 256-byte aligned
+ *    where a call does not say otherwise, and must stay valid while work that
+ *    uses it is queued.  Calls enqueue on the context's stream and return
+ *    without synchronising; nothing in this library allocates device memory
+ *    (the optional step graphs of lbm_use_graphs are the HIP runtime's).
  *  - Errors: every call returns lbm_status; LBM_OK = 0.  Invalid arguments
  *    are detected on the host before anything is enqueued (LBM_E_ARG) and
  *    leave the context unchanged.  lbm_last_error() gives a message for the
@@ -258,7 +258,7 @@ lbm_status lbm_step2_from(lbm_ctx* ctx, const void* src, void* mid, void* dst);
  * its pre-collision state f(t+k+1) = P f*(t+k): delta_rho, j_x, j_y, j_z, four
  * FP32 arrays of dir_stride elements in the grid layout.  keep_last = 0: dst is
  * scratch only and f*(t+n) is not stored.  src, tmp and dst are distinct,
- * 256-byte aligned grids, moments is 256-byte aligned.  Errors: LBM_E_ARG,
+ * 256-byte aligned grids; moments is 4-byte aligned.  Errors: LBM_E_ARG,
  * LBM_E_UNSUPPORTED (storage other than LBM_F32, or obstacle_kernel = 1),
  * LBM_E_HIP. */
 lbm_status lbm_segment(lbm_ctx* ctx, const void* src, void* tmp, void* dst, int32_t n,
@@ -359,14 +359,17 @@ lbm_status lbm_adjoint_step(lbm_ctx* ctx, const void* fstar_prev, const float* n
  * f(m+n), latest first: seed != 0 makes the first a seed (into nu_a), the
  * others are reverse steps, alternating from nu_a to nu_b and back (nu_b NULL
  * only for a seed alone).  The same nu and partials as lbm_adjoint_seed and
- * lbm_adjoint_step, bit for bit, without their 19 pulls of f* per cell. */
+ * lbm_adjoint_step, bit for bit, without their 19 pulls of f* per cell.
+ * moments is 4-byte aligned, so that any record of a segment can be passed: a
+ * record is 4 * dir_stride floats, which small x_align leave off every larger
+ * boundary. */
 lbm_status lbm_adjoint_segment(lbm_ctx* ctx, const float* moments, int32_t n, int32_t seed,
                                const float* dL_drho, const float* dL_du, float* nu_a, float* nu_b,
                                double* dLdF_partials);
 
 /* Two reverse steps in one pass over the grid, nu^{m+2} -> nu^m, from the
  * moments of f(m+1) (mom_later) and of f(m) (mom_earlier), records as
- * lbm_segment stores them.  The same nu as two reverse steps, bit for bit;
+ * lbm_segment stores them (4-byte aligned).  The same nu as two reverse steps, bit for bit;
  * dL/dF is summed in another order (FP64).  nu_in and nu_out must differ.
  * LBM_E_UNSUPPORTED where lbm_adjoint_pairs returns 0: with solid cells when the
  * context has no link mask (steps_per_pass 2 or LBM_STEPS_AUTO, two direction

@@ -61,6 +61,7 @@ size_t elem_size(int32_t storage) {
 }
 
 bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) == 0; }
+bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 
 // Padding between consecutive direction arrays: at the power-of-two sizes
 // of cubic boxes the 19 arrays would otherwise sit at multiples of a large
@@ -507,8 +508,9 @@ lbm_status lbm_segment(lbm_ctx* c, const void* src, void* tmp, void* dst, int32_
   if (passes > 1 && !tmp) return fail(LBM_E_ARG, "tmp must not be NULL for more than one pass");
   if (src == dst || (tmp && (src == tmp || tmp == dst)))
     return fail(LBM_E_ARG, "src, tmp and dst must differ");
-  if (!aligned256(src) || !aligned256(tmp) || !aligned256(dst) || !aligned256(moments))
-    return fail(LBM_E_ARG, "src/tmp/dst/moments must be 256-byte aligned");
+  if (!aligned256(src) || !aligned256(tmp) || !aligned256(dst))
+    return fail(LBM_E_ARG, "src/tmp/dst must be 256-byte aligned");
+  if (!aligned4(moments)) return fail(LBM_E_ARG, "moments must be 4-byte aligned");
   const bool solids = c->flags != nullptr;
   const size_t record = size_t(4) * c->sz.dir;
   const void* from = src;
@@ -678,8 +680,10 @@ lbm_status lbm_adjoint_segment(lbm_ctx* c, const float* moments, int32_t n, int3
   if (!nu_b && n > (seed ? 1 : 0)) return fail(LBM_E_ARG, "nu_b must not be NULL for a reverse step");
   if (nu_a == nu_b || moments == nu_a || moments == nu_b)
     return fail(LBM_E_ARG, "moments, nu_a and nu_b must differ");
-  if (!aligned256(moments) || !aligned256(nu_a) || !aligned256(nu_b))
-    return fail(LBM_E_ARG, "moments, nu_a and nu_b must be 256-byte aligned");
+  if (!aligned256(nu_a) || !aligned256(nu_b))
+    return fail(LBM_E_ARG, "nu_a and nu_b must be 256-byte aligned");
+  // a record of a grid with x_align < 16 starts anywhere: 16 * dir_stride bytes
+  if (!aligned4(moments)) return fail(LBM_E_ARG, "the moments must be 4-byte aligned");
   const size_t record = size_t(4) * c->sz.dir;
   float *from = nu_a, *to = nu_b;
   for (int32_t m = n - 1; m >= 0; --m) {
@@ -712,7 +716,7 @@ lbm_status lbm_adjoint_pair(lbm_ctx* c, const float* mom_later, const float* mom
   if (nu_in == nu_out) return fail(LBM_E_ARG, "nu_in and nu_out must differ");
   if (!aligned256(nu_in) || !aligned256(nu_out))
     return fail(LBM_E_ARG, "nu_in and nu_out must be 256-byte aligned");
-  if ((reinterpret_cast<uintptr_t>(mom_later) | reinterpret_cast<uintptr_t>(mom_earlier)) & 3u)
+  if (!aligned4(mom_later) || !aligned4(mom_earlier))
     return fail(LBM_E_ARG, "the moments must be 4-byte aligned");
   if (!lbm_adjoint_pairs(c))
     return fail(LBM_E_UNSUPPORTED, "two reverse steps per pass need the link mask of two steps "

@@ -413,3 +413,37 @@ def test_reverse_pairs_do_not_depend_on_the_checkpoints(steps, shape, monkeypatc
     got = run(steps, 1 / 64)
     assert torch.equal(got[0], ref[0])
     assert float((got[1] - ref[1]).abs().max()) <= 1e-11 * float(ref[1].abs().max())
+
+
+@pytest.mark.parametrize("shape", [(63, 65, 65), (70, 81, 100), (79, 71, 81), (101, 101, 101)])
+def test_reverse_pairs_with_records_off_256_bytes(shape, monkeypatch):
+    """Rollouts whose 16-byte rows put the records of moments off 256-byte
+    boundaries: odd and even numbers of steps, spacings that cut the segments
+    anywhere, moments kept and recomputed all give the same bits, and the
+    gradients of a sweep of single steps (dL/dF to FP64 rounding)."""
+    sim = LBM(shape, 0.7, storage="f32", x_align=lbm._Rollout.row_align(shape))
+    assert 16 * sim.dir_stride % 256 and A.lbm_adjoint_pairs(sim.ctx)
+    rng = np.random.default_rng(14)
+    start = torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float().cuda()
+    flags = torch.from_numpy(I.random_flags(shape, 63, solid_fraction=0.1)).cuda()
+
+    def run(steps, every, share):
+        monkeypatch.setattr(lbm, "KEPT_MOMENTS_SHARE", share)
+        u0 = start.clone().requires_grad_(True)
+        g = torch.tensor([2e-5, -1e-5, 1e-5], dtype=torch.float64, requires_grad=True)
+        rho, u = rollout(u0, g, steps=steps, tau=0.7, flags=flags, checkpoint_every=every)
+        ((u * u).sum() + 0.3 * (rho * rho).sum()).backward()
+        return u0.grad, g.grad
+
+    for steps in (6, 7, 22):
+        say("records off 256 bytes", shape, steps)
+        with monkeypatch.context() as single:
+            single.setattr(lbm._Rollout, "adjoint_pairs", staticmethod(lambda sim: False))
+            ref = run(steps, steps, 1 / 64)
+        sums = None
+        for every in (1, 2, 3, 20):
+            for share in (0.0, 1 / 64):
+                got = run(steps, every, share)
+                sums = got[1] if sums is None else sums
+                assert torch.equal(got[0], ref[0]) and torch.equal(got[1], sums), (steps, every, share)
+        assert float((sums - ref[1]).abs().max()) <= 1e-11 * float(ref[1].abs().max())
