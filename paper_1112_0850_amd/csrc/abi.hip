@@ -115,7 +115,7 @@ lbm_status check_params(const lbm_params* p, Sizes* sz) {
                 "grid too large: one direction array needs %llu bytes (limit 4 GiB - 1)",
                 (unsigned long long)(plane * es));
   const uint64_t dir = plane + kDirPadBytes / es;
-  const lbm::Geo g = lbm::make_geo(p->nx, p->ny, p->nz, int(xs), dir);
+  const lbm::Plan g = lbm::make_plan(p->nx, p->ny, p->nz, int(xs), dir);
   if (sz) {
     sz->xs = xs;
     sz->plane = plane;
@@ -186,7 +186,7 @@ lbm_status noalloc_scratch_here(int* dev_out, double** out) {
 // ahead of their pulls) half as much; the pair pass is not bound by its stores,
 // lost 1-2% and does not fill.
 constexpr size_t kSector = 64;
-int32_t row_fill(const lbm::Geo& g, size_t es) {
+int32_t row_fill(const lbm::Plan& g, size_t es) {
   if (!g.stream) return g.nx;
   const int32_t n = int32_t(kSector / es);
   const int32_t up = (g.nx + n - 1) / n * n;
@@ -201,7 +201,7 @@ int32_t row_fill(const lbm::Geo& g, size_t es) {
 // pairs 186 MB (100^3 FP32) 28 / 21, 304 MB 41 / 43, 371 MB 43 / 46; the
 // adjoint from moments 304 MB 60 / 66 (72 x 80 x 100 FP32, 137 MB: 29 / 20).
 constexpr size_t kCached1 = size_t(340) << 20, kCached2 = size_t(256) << 20;
-void store_policy(lbm::Geo* g, size_t grid_bytes) {
+void store_policy(lbm::Plan* g, size_t grid_bytes) {
   g->stream = 2 * grid_bytes > kCached1;
   g->stream2 = 2 * grid_bytes > kCached2;
 }
@@ -209,8 +209,8 @@ void store_policy(lbm::Geo* g, size_t grid_bytes) {
 struct lbm_ctx {
   lbm_params p;
   Sizes sz;
-  lbm::Geo geo;
-  lbm::Geo geo_own;  // for single steps between the context's own grids (row_fill)
+  lbm::Plan geo;
+  lbm::Plan geo_own;  // for single steps between the context's own grids (row_fill)
   lbm::PhysParams ph;
   void* grid[2];
   const uint8_t* flags;
@@ -237,7 +237,7 @@ lbm_status check_ctx(const lbm_ctx* c) {
   return LBM_OK;
 }
 
-lbm_status launch_steps_on(lbm_ctx* c, const lbm::Geo& geo, const void* src, void* dst,
+lbm_status launch_steps_on(lbm_ctx* c, const lbm::Plan& geo, const void* src, void* dst,
                            hipStream_t s) {
   if (c->flags && c->ph.split) {
     // the split design: bounce-back values into the solid slots of src first
@@ -400,7 +400,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
   c->noalloc = noalloc;
   c->p = *p;
   c->sz = sz;
-  c->geo = lbm::make_geo(p->nx, p->ny, p->nz, int(sz.xs), sz.dir);
+  c->geo = lbm::make_plan(p->nx, p->ny, p->nz, int(sz.xs), sz.dir);
   store_policy(&c->geo, sz.grid_bytes);
   c->geo_own = c->geo;
   c->geo_own.xfill = row_fill(c->geo, elem_size(p->storage));

@@ -12,20 +12,30 @@ namespace lbm {
 // segments in (z, y, segment) order.  Blocks are remapped so that each of
 // the 8 XCDs (which receive hardware block ids round-robin) works on one
 // contiguous eighth of the domain, keeping neighbouring rows in one L2.
+//
+// Kernels receive Geo and no more than it.  With the fields that only the host
+// reads ahead of yb and upw a wave waited for two more scalar loads before its
+// first pull (graph replays, us a step: FP32 48^3 channel 6.23, now 6.01; 40^3
+// 4.35, now 4.19), and a launch cost more host time (bursts of 40 steps, us a
+// step: FP16 40^3 4.90 with 320 bytes of arguments, 4.09 with these 304).
 struct Geo {
   int32_t nx, ny, nz;
   int32_t xs;       // x stride of a population row, in cells
   uint32_t plane;   // elements from one direction array to the next (nz * ny * xs + padding)
   int32_t nseg;     // 64-cell segments per row
   int32_t nrows;    // ny * nz
-  int32_t nblocks;  // blocks launched (4 segments each)
-  int32_t nb8;      // nblocks rounded down to a multiple of 8
-  int32_t units;    // step kernel: 64-cell units per row,
-  int32_t upw;      //   and the most of them that a segment holds
-  int32_t xfill;    // columns of a row that a single step stores: nx, or more (zeros past nx)
-  int32_t stream;   // non-temporal stores in the single step,
-  int32_t stream2;  //   and in the pair pass and the adjoint (see store_policy)
+  int32_t upw;      // step kernel: the most 64-cell units of a row that a segment holds
+  int32_t nb8;      // blocks launched, rounded down to a multiple of 8
   int32_t yb;       // step kernel: rows are visited in bands of yb rows of y, z fastest
+};
+static_assert(sizeof(Geo) == 40, "Geo grew: see above");
+
+// The same with what the launchers need.
+struct Plan : Geo {
+  int32_t nblocks;  // blocks launched (4 segments each)
+  int32_t xfill;    // columns of a row that a single step stores: nx, or more (zeros past nx)
+  bool stream;      // non-temporal stores in the single step,
+  bool stream2;     //   and in the pair pass and the adjoint (see store_policy)
 };
 
 // Launch geometry of the two-step kernel: 64 x TY tiles in (x, y), z chunks.
@@ -58,78 +68,78 @@ struct PhysParams {
   bool split;        // bounce-back by the separate obstacle kernel (the paper's split design)
 };
 
-Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride);
+Plan make_plan(int nx, int ny, int nz, int xs, uint64_t dir_stride);
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
-hipError_t launch_init(int storage, const Geo& g, const PhysParams& ph, void* grid,
+hipError_t launch_init(int storage, const Plan& g, const PhysParams& ph, void* grid,
                        const uint8_t* flags, const float* rho0, const float* u0, hipStream_t s);
-hipError_t launch_mark_solids(int storage, const Geo& g, const PhysParams& ph, void* grid,
+hipError_t launch_mark_solids(int storage, const Plan& g, const PhysParams& ph, void* grid,
                               const uint8_t* flags, hipStream_t s);
-hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step(int storage, bool solids, bool force, const Plan& g, const PhysParams& ph,
                        const void* src, void* dst, const uint8_t* flags, hipStream_t s);
 // Two fused steps src = f*(t) -> dst = f*(t+2) (bit-identical to two launch_step calls;
 // not for the split design).
 // lmask: the link mask of launch_link_mask, or NULL (the walls then use the
 // markers).
-hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step2(int storage, bool solids, bool force, const Plan& g, const PhysParams& ph,
                         const void* src, void* dst, const uint8_t* flags, const uint32_t* lmask,
                         hipStream_t s);
 // Whether two fused steps are faster than two single ones on this grid (they
 // give the same bits).
-bool step2_pays(int storage, const Geo& g);
+bool step2_pays(int storage, const Plan& g);
 // Whether they go through the small-box kernel: us a step, small-box / z-marching
 // kernel, FP32 48^3 4.9 / 6.3, 64^3 7.7 / 7.1; FP64 48^3 5.8 / 6.8, 64^3 10.8 / 10.8.
-inline bool step2_tiles(const Geo& g) {
+inline bool step2_tiles(const Plan& g) {
   return int64_t(g.nx) * g.ny * g.nz <= (int64_t(1) << 17);
 }
 // The same two steps storing the intermediate level too: mid = f*(t+1)
 // (FP32 storage only: hipErrorInvalidValue otherwise).
-hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,
+hipError_t launch_step2_mid(int storage, bool solids, bool force, const Plan& g,
                             const PhysParams& ph, const void* src, void* mid, void* dst,
                             const uint8_t* flags, const uint32_t* lmask, hipStream_t s);
 // One or two FP32 steps (not for the split design) that also store the moments
 // of the pre-collision states: four arrays in the grid layout per state.  A
 // null dst stores the moments only.
-hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step_mom(bool solids, bool force, const Plan& g, const PhysParams& ph,
                            const float* src, float* dst, float* mom, const uint8_t* flags,
                            hipStream_t s);
-hipError_t launch_step2_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step2_mom(bool solids, bool force, const Plan& g, const PhysParams& ph,
                             const float* src, float* dst, float* mom1, float* mom2,
                             const uint8_t* flags, const uint32_t* lmask, hipStream_t s);
 // The two-step kernel's link mask of every cell ([nz][ny][nx] uint32) from the
 // flags: bit i (1..18) for a blocked pull along c_i, bits 19 and 20 for the
 // cell's own SOLID and NOFORCE flags; with moving walls bit 21 for a link to a
 // moving wall and bit 22 for a moving-wall cell.
-hipError_t launch_link_mask(const Geo& g, bool moving, const uint8_t* flags, uint32_t* mask,
+hipError_t launch_link_mask(const Plan& g, bool moving, const uint8_t* flags, uint32_t* mask,
                             hipStream_t s);
-hipError_t launch_obstacle(int storage, const Geo& g, const PhysParams& ph, void* grid,
+hipError_t launch_obstacle(int storage, const Plan& g, const PhysParams& ph, void* grid,
                            const uint8_t* flags, hipStream_t s);
-hipError_t launch_macro(int storage, bool out_f64, const Geo& g, const PhysParams& ph,
+hipError_t launch_macro(int storage, bool out_f64, const Plan& g, const PhysParams& ph,
                         const void* grid, const uint8_t* flags, void* rho, void* u, hipStream_t s);
-hipError_t launch_reduce(int storage, const Geo& g, const PhysParams& ph, const void* grid,
+hipError_t launch_reduce(int storage, const Plan& g, const PhysParams& ph, const void* grid,
                          const uint8_t* flags, double* scratch, double* out5, hipStream_t s);
 // Discrete adjoint in pull form (nu = dL/df, the pre-collision adjoint):
 // seed nu^T from dL/drho_T, dL/du_T and f*(T-1); step nu^{n+1} -> nu^n with
 // f*(n-1); init dL/du0 from nu^1.
-hipError_t launch_adj_seed(bool solids, const Geo& g, const PhysParams& ph, const float* fprev,
+hipError_t launch_adj_seed(bool solids, const Plan& g, const PhysParams& ph, const float* fprev,
                            const uint8_t* flags, const float* dL_drho, const float* dL_du,
                            float* nu_T, double* partials, hipStream_t s);
-hipError_t launch_adj_step(bool solids, const Geo& g, const PhysParams& ph, const float* fprev,
+hipError_t launch_adj_step(bool solids, const Plan& g, const PhysParams& ph, const float* fprev,
                            const uint8_t* flags, const float* nu_np1, float* nu_n,
                            double* partials, hipStream_t s);
 // The seed (nu1 null) or one reverse step from stored moments.
-hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const float* mom,
+hipError_t launch_adj_mom(bool solids, const Plan& g, const PhysParams& ph, const float* mom,
                           const uint8_t* flags, const float* dL_drho, const float* dL_du,
                           const float* nu1, float* nu0, double* partials, hipStream_t s);
 // Two reverse steps from stored moments; lmask NULL when there are no solids.
-bool adj_pair_fits(const Geo& g);
-hipError_t launch_adj_pair(const Geo& g, const PhysParams& ph, const float* mom1, const float* mom2,
+bool adj_pair_fits(const Plan& g);
+hipError_t launch_adj_pair(const Plan& g, const PhysParams& ph, const float* mom1, const float* mom2,
                            const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
                            hipStream_t s);
-hipError_t launch_adj_init(bool solids, const Geo& g, const PhysParams& ph, const uint8_t* flags,
+hipError_t launch_adj_init(bool solids, const Plan& g, const PhysParams& ph, const uint8_t* flags,
                            const float* nu1, const float* rho0, const float* u0, float* dL_du0,
                            hipStream_t s);
-hipError_t launch_adj_finish(const Geo& g, const double* partials, double* out3, hipStream_t s);
+hipError_t launch_adj_finish(const Plan& g, const double* partials, double* out3, hipStream_t s);
 hipError_t launch_copy(void* c, const void* a, size_t n16, hipStream_t s);
 // Copy variants for the bandwidth sweep: vec in {1, 2, 4} 16-byte elements per
 // thread, non-temporal or not, `blocks` blocks (0 = one pass over the array).
@@ -137,6 +147,6 @@ hipError_t launch_copy_variant(void* c, const void* a, size_t n16, int vec, bool
                                hipStream_t s);
 // Pull-copy probe: one pure-streaming pass dst_i(x) = src_i(x - c_i) (periodic,
 // no geometry, no collision) with the step kernel's launch and access pattern.
-hipError_t launch_pull_copy(int storage, const Geo& g, const void* src, void* dst, hipStream_t s);
+hipError_t launch_pull_copy(int storage, const Plan& g, const void* src, void* dst, hipStream_t s);
 
 }  // namespace lbm

@@ -37,8 +37,8 @@
 namespace lbm {
 
 #if LBM_PART == 0
-Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
-  Geo g;
+Plan make_plan(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
+  Plan g;
   g.nx = nx;
   g.ny = ny;
   g.nz = nz;
@@ -49,10 +49,9 @@ Geo make_geo(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
   const int64_t segs = int64_t(g.nseg) * g.nrows;
   g.nblocks = int32_t((segs + 3) / 4);
   g.nb8 = (g.nblocks / 8) * 8;
-  g.units = g.nseg;
   g.upw = 1;
   g.xfill = nx;
-  g.stream = g.stream2 = 1;
+  g.stream = g.stream2 = true;
   g.yb = g.ny;
   return g;
 }
@@ -506,7 +505,8 @@ __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restr
                                            typename Storage<K>::T* __restrict__ dst,
                                            const uint8_t* __restrict__ flags,
                                            float* __restrict__ mom, const Geo& g,
-                                           const StepK<typename Storage<K>::C>& k, Loc l, int x0) {
+                                           const StepK<typename Storage<K>::C>& k, Loc l, int x0,
+                                           int xfill) {
   using C = typename Storage<K>::C;
   using T = typename Storage<K>::T;
   constexpr bool SCALED = (K == ST_F16);
@@ -522,7 +522,7 @@ __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restr
     l.x = valid[m] ? x : g.nx - 1;  // past the row end: load in bounds, store nothing
     n[m] = neighbourhood(g, l);
   }
-  if (FILL ? x0 >= g.xfill : !valid[0]) return;
+  if (FILL ? x0 >= xfill : !valid[0]) return;
   const size_t pb = size_t(g.plane) * sizeof(T);
   uint8_t fl[M];
 #pragma unroll
@@ -575,7 +575,7 @@ __device__ __forceinline__ void step_cells(const typename Storage<K>::T* __restr
       }
     }
     const uint32_t xs = FILL ? uint32_t(x0 + 64 * m) : n[m].xn[1];
-    if (FILL ? x0 + 64 * m < g.xfill : valid[m]) {
+    if (FILL ? x0 + 64 * m < xfill : valid[m]) {
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
         C out = f[m][i];
@@ -592,8 +592,8 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
                                           typename Storage<K>::T* __restrict__ dst,
                                           const uint8_t* __restrict__ flags,
                                           float* __restrict__ mom, const Geo& g,
-                                          const StepK<typename Storage<K>::C>& k) {
-  // g describes the segments (step_geo); same block remap as locate().
+                                          const StepK<typename Storage<K>::C>& k, int xfill = 0) {
+  // g describes the segments (step_plan); same block remap as locate().
   const int b = blockIdx.x;
   const int lb = (b < g.nb8) ? ((b & 7) * (g.nb8 >> 3) + (b >> 3)) : b;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -616,16 +616,16 @@ __device__ __forceinline__ void step_body(const typename Storage<K>::T* __restri
     l.z = idx / h;
     l.y = y0 + (idx - l.z * h);
   }
-  const int u0 = (seg - row * g.nseg) * g.upw;
+  const int u0 = (seg - row * g.nseg) * (M ? M : g.upw);
   const int x0 = u0 * 64 + int(threadIdx.x & 63);
   if constexpr (M != 0) {
-    step_cells<K, WALLS, FORCE, INC, M, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0);
+    step_cells<K, WALLS, FORCE, INC, M, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0, xfill);
   } else {
-    switch (min(g.upw, g.units - u0)) {
-      case 1: step_cells<K, WALLS, FORCE, INC, 1, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
-      case 2: step_cells<K, WALLS, FORCE, INC, 2, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
-      case 3: step_cells<K, WALLS, FORCE, INC, 3, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
-      case 4: step_cells<K, WALLS, FORCE, INC, 4, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0); break;
+    switch (min(g.upw, (g.nx + 63) / 64 - u0)) {
+      case 1: step_cells<K, WALLS, FORCE, INC, 1, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0, xfill); break;
+      case 2: step_cells<K, WALLS, FORCE, INC, 2, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0, xfill); break;
+      case 3: step_cells<K, WALLS, FORCE, INC, 3, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0, xfill); break;
+      case 4: step_cells<K, WALLS, FORCE, INC, 4, MOM, FILL, NT>(src, dst, flags, mom, g, k, l, x0, xfill); break;
     }
   }
 }
@@ -646,12 +646,12 @@ __global__ __launch_bounds__(kBlock) void k_step_cached(
   step_body<K, WALLS, FORCE, INC, M, false, false, false>(src, dst, flags, nullptr, g, k);
 }
 
-// The same storing g.xfill columns of a row, zeros past nx.
+// The same storing xfill columns of a row, zeros past nx.
 template <int K, int WALLS, bool FORCE, bool INC, int M>
 __global__ __launch_bounds__(kBlock) void k_step_fill(
     const typename Storage<K>::T* __restrict__ src, typename Storage<K>::T* __restrict__ dst,
-    const uint8_t* __restrict__ flags, Geo g, StepK<typename Storage<K>::C> k) {
-  step_body<K, WALLS, FORCE, INC, M, false, true, true>(src, dst, flags, nullptr, g, k);
+    const uint8_t* __restrict__ flags, Geo g, StepK<typename Storage<K>::C> k, int xfill) {
+  step_body<K, WALLS, FORCE, INC, M, false, true, true>(src, dst, flags, nullptr, g, k, xfill);
 }
 
 template <int WALLS, bool FORCE, bool INC, bool NT>
@@ -2037,7 +2037,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 }
 
 template <int K>
-static void init_t(const Geo& g, const PhysParams& ph, void* grid, const uint8_t* flags,
+static void init_t(const Plan& g, const PhysParams& ph, void* grid, const uint8_t* flags,
                    const float* rho0, const float* u0, hipStream_t s) {
   using S = Storage<K>;
   hipLaunchKernelGGL(k_init<K>, dim3(g.nblocks), dim3(kBlock), 0, s,
@@ -2045,7 +2045,7 @@ static void init_t(const Geo& g, const PhysParams& ph, void* grid, const uint8_t
                      to_phys<typename S::C>(ph));
 }
 
-hipError_t launch_init(int storage, const Geo& g, const PhysParams& ph, void* grid,
+hipError_t launch_init(int storage, const Plan& g, const PhysParams& ph, void* grid,
                        const uint8_t* flags, const float* rho0, const float* u0, hipStream_t s) {
   switch (storage) {
     case ST_F32: init_t<ST_F32>(g, ph, grid, flags, rho0, u0, s); break;
@@ -2059,12 +2059,12 @@ hipError_t launch_init(int storage, const Geo& g, const PhysParams& ph, void* gr
 }
 
 template <int K>
-static void mark_t(const Geo& g, bool moving, void* grid, const uint8_t* flags, hipStream_t s) {
+static void mark_t(const Plan& g, bool moving, void* grid, const uint8_t* flags, hipStream_t s) {
   hipLaunchKernelGGL(k_mark_solids<K>, dim3(g.nblocks), dim3(kBlock), 0, s,
                      reinterpret_cast<typename Storage<K>::T*>(grid), flags, g, moving ? 1 : 0);
 }
 
-hipError_t launch_mark_solids(int storage, const Geo& g, const PhysParams& ph, void* grid,
+hipError_t launch_mark_solids(int storage, const Plan& g, const PhysParams& ph, void* grid,
                               const uint8_t* flags, hipStream_t s) {
   const bool mv = ph.moving;
   switch (storage) {
@@ -2117,12 +2117,12 @@ static StepK<C> make_stepk(const PhysParams& p) {
 constexpr int band_rows(int M) { return M >= 4 ? 16 : 32; }
 
 // Geometry of segments of up to M 64-cell units for the step kernel.
-[[maybe_unused]] static Geo step_geo(const Geo& g, int M) {
-  Geo h = g;
+[[maybe_unused]] static Plan step_plan(const Plan& g, int M) {
+  Plan h = g;
   h.yb = band_rows(M) < g.ny ? band_rows(M) : g.ny;
-  h.units = (g.nx + 63) / 64;
-  h.nseg = (h.units + M - 1) / M;
-  h.upw = (h.units + h.nseg - 1) / h.nseg;
+  const int units = (g.nx + 63) / 64;
+  h.nseg = (units + M - 1) / M;
+  h.upw = (units + h.nseg - 1) / h.nseg;
   const int64_t segs = int64_t(h.nseg) * g.nrows;
   h.nblocks = int32_t((segs + 3) / 4);
   h.nb8 = (h.nblocks / 8) * 8;
@@ -2136,40 +2136,41 @@ constexpr int band_rows(int M) { return M >= 4 ? 16 : 32; }
 // (porous).  The kernel for exactly 4 stays, being 3% faster than the switch at
 // 256^3 (271 / 281) and 1% at 512^3.
 template <int K, int WALLS, bool FORCE, bool INC>
-static void step_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
+static void step_t(const Plan& g, const PhysParams& ph, const void* src, void* dst,
                    const uint8_t* flags, hipStream_t s) {
   using S = Storage<K>;
   constexpr int M = StepCells<K>::M;
-  const Geo h = step_geo(g, M);
-  auto go = [&](auto kernel) {
+  const Plan h = step_plan(g, M);
+  auto go = [&](auto kernel, auto... more) {
     hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s,
                        reinterpret_cast<const typename S::T*>(src),
                        reinterpret_cast<typename S::T*>(dst), flags, h,
-                       make_stepk<typename S::C>(ph));
+                       make_stepk<typename S::C>(ph), more...);
   };
   constexpr int ANY = M > 1 ? 0 : 1;
+  const bool some = (g.nx + 63) / 64 % M != 0;  // waves of fewer units than M
   if (!h.stream) {
-    if (M > 1 && h.units % M) return go(k_step_cached<K, WALLS, FORCE, INC, ANY>);
+    if (M > 1 && some) return go(k_step_cached<K, WALLS, FORCE, INC, ANY>);
     return go(k_step_cached<K, WALLS, FORCE, INC, M>);
   }
   if constexpr (WALLS != 4) {
-    if (h.xfill > h.nx) return go(k_step_fill<K, WALLS, FORCE, INC, ANY>);
+    if (h.xfill > h.nx) return go(k_step_fill<K, WALLS, FORCE, INC, ANY>, h.xfill);
   }
   if constexpr (M > 1) {
-    if (h.units % M) return go(k_step<K, WALLS, FORCE, INC, ANY>);
+    if (some) return go(k_step<K, WALLS, FORCE, INC, ANY>);
   }
   go(k_step<K, WALLS, FORCE, INC, M>);
 }
 
 template <int K, int WALLS, bool INC>
-static void step_f(bool force, const Geo& g, const PhysParams& ph, const void* src, void* dst,
+static void step_f(bool force, const Plan& g, const PhysParams& ph, const void* src, void* dst,
                    const uint8_t* flags, hipStream_t s) {
   if (force) step_t<K, WALLS, true, INC>(g, ph, src, dst, flags, s);
   else step_t<K, WALLS, false, INC>(g, ph, src, dst, flags, s);
 }
 
 template <int K, bool INC>
-static void step_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
+static void step_w(bool solids, bool force, const Plan& g, const PhysParams& ph, const void* src,
                    void* dst, const uint8_t* flags, hipStream_t s) {
   if (!solids) step_f<K, 0, INC>(force, g, ph, src, dst, flags, s);
   else if (ph.split) step_f<K, 3, INC>(force, g, ph, src, dst, flags, s);
@@ -2179,9 +2180,9 @@ static void step_w(bool solids, bool force, const Geo& g, const PhysParams& ph, 
 
 // One FP32 step storing the moments of its pre-collision state as well.
 template <int WALLS, bool INC>
-static void step_mom_f(bool force, const Geo& g, const PhysParams& ph, const float* src, float* dst,
+static void step_mom_f(bool force, const Plan& g, const PhysParams& ph, const float* src, float* dst,
                        float* mom, const uint8_t* flags, hipStream_t s) {
-  const Geo h = step_geo(g, 1);
+  const Plan h = step_plan(g, 1);
   const StepK<float> k = make_stepk<float>(ph);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s, src, dst, flags, mom, h, k);
@@ -2191,7 +2192,7 @@ static void step_mom_f(bool force, const Geo& g, const PhysParams& ph, const flo
 }
 
 template <bool INC>
-void step_mom_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const float* src,
+void step_mom_w(bool solids, bool force, const Plan& g, const PhysParams& ph, const float* src,
                        float* dst, float* mom, const uint8_t* flags, hipStream_t s) {
   if (!solids) step_mom_f<0, INC>(force, g, ph, src, dst, mom, flags, s);
   else if (!ph.moving) step_mom_f<1, INC>(force, g, ph, src, dst, mom, flags, s);
@@ -2199,12 +2200,12 @@ void step_mom_w(bool solids, bool force, const Geo& g, const PhysParams& ph, con
 }
 
 #if LBM_PART == 0
-extern template void step_mom_w<false>(bool, bool, const Geo&, const PhysParams&, const float*,
+extern template void step_mom_w<false>(bool, bool, const Plan&, const PhysParams&, const float*,
                                        float*, float*, const uint8_t*, hipStream_t);
-extern template void step_mom_w<true>(bool, bool, const Geo&, const PhysParams&, const float*,
+extern template void step_mom_w<true>(bool, bool, const Plan&, const PhysParams&, const float*,
                                       float*, float*, const uint8_t*, hipStream_t);
 
-hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step_mom(bool solids, bool force, const Plan& g, const PhysParams& ph,
                            const float* src, float* dst, float* mom, const uint8_t* flags,
                            hipStream_t s) {
   if (ph.incomp) step_mom_w<true>(solids, force, g, ph, src, dst, mom, flags, s);
@@ -2214,25 +2215,25 @@ hipError_t launch_step_mom(bool solids, bool force, const Geo& g, const PhysPara
 #endif  // LBM_PART == 0
 
 template <int K>
-void step_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
+void step_k(bool solids, bool force, const Plan& g, const PhysParams& ph, const void* src,
                    void* dst, const uint8_t* flags, hipStream_t s) {
   if (ph.incomp) step_w<K, true>(solids, force, g, ph, src, dst, flags, s);
   else step_w<K, false>(solids, force, g, ph, src, dst, flags, s);
 }
 
 #if LBM_PART == 0
-extern template void step_k<ST_F32>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step_k<ST_F32>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                   const uint8_t*, hipStream_t);
-extern template void step_k<ST_F16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step_k<ST_F16>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                   const uint8_t*, hipStream_t);
-extern template void step_k<ST_BF16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step_k<ST_BF16>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                   const uint8_t*, hipStream_t);
-extern template void step_k<ST_F64>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step_k<ST_F64>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                   const uint8_t*, hipStream_t);
-extern template void step_k<ST_F32X>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step_k<ST_F32X>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                   const uint8_t*, hipStream_t);
 
-hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step(int storage, bool solids, bool force, const Plan& g, const PhysParams& ph,
                        const void* src, void* dst, const uint8_t* flags, hipStream_t s) {
   switch (storage) {
     case ST_F32: step_k<ST_F32>(solids, force, g, ph, src, dst, flags, s); break;
@@ -2256,7 +2257,7 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
 // FP32 103 -> 85 us a pass, 128 x 128 x 256 204 -> 155, 200^3 404 -> 329, 256^3
 // 589 -> 541, 200^3 BF16 289 -> 225, 100^3 FP64 130 -> 84; 512^3 keeps its 128
 // planes.)
-[[maybe_unused]] static Geo2 make_geo2(const Geo& g, int rows, int64_t* cost) {
+[[maybe_unused]] static Geo2 make_geo2(const Plan& g, int rows, int64_t* cost) {
   Geo2 h;
   h.nx = g.nx;
   h.ny = g.ny;
@@ -2291,7 +2292,7 @@ hipError_t launch_step(int storage, bool solids, bool force, const Geo& g, const
 // chosen: FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256 171 /
 // 157 (8), 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4).
 template <int K>
-static int tb2_choice(const Geo& g) {
+static int tb2_choice(const Plan& g) {
   int best = 0;
   double least = 0.0;
   for (int i = 0; i < Tb2<K>::N; ++i) {
@@ -2308,7 +2309,7 @@ static int tb2_choice(const Geo& g) {
 }
 
 template <int K, int WALLS, bool FORCE, bool INC, int OUT, int CHOICE, bool NT>
-static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* dst,
+static void step2_go(const Plan& g, const PhysParams& ph, const void* src, void* dst,
                      const uint8_t* flags, const uint32_t* lmask, hipStream_t s, void* mid,
                      float* mom2) {
   using S = Storage<K>;
@@ -2326,7 +2327,7 @@ static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* 
 // waves of a block's two steps, the rows its pulls touch weighing a tenth of a
 // wave each (32^3 FP32: 16 x 2 x 4 5.8 us a pass, 8 x 4 x 4 and 32 x 2 x 2 6.2,
 // 8 x 4 x 2 6.8).
-[[maybe_unused]] static GeoT make_geot(const Geo& g) {
+[[maybe_unused]] static GeoT make_geot(const Plan& g) {
   static constexpr int dims[][3] = {{8, 4, 2}, {16, 2, 4}, {8, 4, 4}, {8, 8, 4}, {12, 6, 6}};
   GeoT best{};
   double least = 0.0;
@@ -2356,7 +2357,7 @@ static void step2_go(const Geo& g, const PhysParams& ph, const void* src, void* 
 }
 
 template <int K, int WALLS, bool FORCE, bool INC, int OUT>
-static void step2_tile_go(const Geo& g, const PhysParams& ph, const void* src, void* dst,
+static void step2_tile_go(const Plan& g, const PhysParams& ph, const void* src, void* dst,
                           const uint8_t* flags, hipStream_t s, void* mom1, float* mom2) {
   using S = Storage<K>;
   const GeoT h = make_geot(g);
@@ -2368,7 +2369,7 @@ static void step2_tile_go(const Geo& g, const PhysParams& ph, const void* src, v
 }
 
 template <int K, int WALLS, bool FORCE, bool INC, int OUT = kOutLast>
-static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* dst,
+static void step2_t(const Plan& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s,
                     void* mid = nullptr, float* mom2 = nullptr) {
   auto go = [&](auto choice, auto nt) {
@@ -2400,7 +2401,7 @@ static void step2_t(const Geo& g, const PhysParams& ph, const void* src, void* d
 }
 
 template <int K, int WALLS, bool INC>
-static void step2_f(bool force, const Geo& g, const PhysParams& ph, const void* src, void* dst,
+static void step2_f(bool force, const Plan& g, const PhysParams& ph, const void* src, void* dst,
                     const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (force) step2_t<K, WALLS, true, INC>(g, ph, src, dst, flags, lmask, s);
   else step2_t<K, WALLS, false, INC>(g, ph, src, dst, flags, lmask, s);
@@ -2409,7 +2410,7 @@ static void step2_f(bool force, const Geo& g, const PhysParams& ph, const void* 
 // walls: none (0), resting with markers (1) or with the link mask (4), moving with
 // markers (2) or with the mask (5)
 template <int K, bool INC>
-static void step2_w(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
+static void step2_w(bool solids, bool force, const Plan& g, const PhysParams& ph, const void* src,
                     void* dst, const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (!solids) step2_f<K, 0, INC>(force, g, ph, src, dst, flags, lmask, s);
   else if (lmask && !ph.moving) step2_f<K, 4, INC>(force, g, ph, src, dst, flags, lmask, s);
@@ -2419,28 +2420,28 @@ static void step2_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
 }
 
 template <int K>
-void step2_k(bool solids, bool force, const Geo& g, const PhysParams& ph, const void* src,
+void step2_k(bool solids, bool force, const Plan& g, const PhysParams& ph, const void* src,
                     void* dst, const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (ph.incomp) step2_w<K, true>(solids, force, g, ph, src, dst, flags, lmask, s);
   else step2_w<K, false>(solids, force, g, ph, src, dst, flags, lmask, s);
 }
 
 #if LBM_PART == 0
-extern template void step2_k<ST_F32>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step2_k<ST_F32>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
-extern template void step2_k<ST_F16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step2_k<ST_F16>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
-extern template void step2_k<ST_BF16>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step2_k<ST_BF16>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
-extern template void step2_k<ST_F64>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step2_k<ST_F64>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
-extern template void step2_k<ST_F32X>(bool, bool, const Geo&, const PhysParams&, const void*, void*,
+extern template void step2_k<ST_F32X>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
 
 
 // Blocks of a z-marching launch with the storage's first choice of tile rows.
 template <int K>
-static int step2_blocks_k(const Geo& g) {
+static int step2_blocks_k(const Plan& g) {
   int64_t cost;
   return make_geo2(g, Tb2<K>::choice[0].rows, &cost).nblocks;
 }
@@ -2455,7 +2456,7 @@ static int step2_blocks_k(const Geo& g) {
 // wall loses more than 2%: FP32 56 x 60 x 72 porous 10.7 / 11.9, 64^3 8.9 / 8.8,
 // 96^3 24.0 / 23.7; FP64 14.8 / 15.7, 13.2 / 12.8, 57 / 46; BF16 64^3 cavity 7.6
 // / 8.4, 80^3 18.1 / 14.6; F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33.
-bool step2_pays(int storage, const Geo& g) {
+bool step2_pays(int storage, const Plan& g) {
   if (step2_tiles(g)) {
     const GeoT h = make_geot(g);
     return h.nblocks <= kCUs && h.tx * h.ty * h.tz <= 128;
@@ -2475,7 +2476,7 @@ bool step2_pays(int storage, const Geo& g) {
   return blocks >= 128;
 }
 
-hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step2(int storage, bool solids, bool force, const Plan& g, const PhysParams& ph,
                         const void* src, void* dst, const uint8_t* flags, const uint32_t* lmask,
                         hipStream_t s) {
   switch (storage) {
@@ -2494,7 +2495,7 @@ hipError_t launch_step2(int storage, bool solids, bool force, const Geo& g, cons
 // src = f*(t) -> mid = f*(t+1), dst = f*(t+2)) or the moments of both
 // pre-collision states (OUT = kOutMoments: into mid and mom2).
 template <int OUT, int WALLS, bool INC>
-static void step2_out_f(bool force, const Geo& g, const PhysParams& ph, const void* src, void* mid,
+static void step2_out_f(bool force, const Plan& g, const PhysParams& ph, const void* src, void* mid,
                         float* mom2, void* dst, const uint8_t* flags, const uint32_t* lmask,
                         hipStream_t s) {
   if (force) step2_t<ST_F32, WALLS, true, INC, OUT>(g, ph, src, dst, flags, lmask, s, mid, mom2);
@@ -2502,7 +2503,7 @@ static void step2_out_f(bool force, const Geo& g, const PhysParams& ph, const vo
 }
 
 template <int OUT, bool INC>
-void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
+void step2_out_w(bool solids, bool force, const Plan& g, const PhysParams& ph,
                         const void* src, void* mid, float* mom2, void* dst, const uint8_t* flags,
                         const uint32_t* lmask, hipStream_t s) {
   if (!solids) step2_out_f<OUT, 0, INC>(force, g, ph, src, mid, mom2, dst, flags, lmask, s);
@@ -2515,18 +2516,18 @@ void step2_out_w(bool solids, bool force, const Geo& g, const PhysParams& ph,
 
 // The step kernels' instantiations, shared out over the parts.
 #define LBM_STEP_K(K)                                                                            \
-  template void step_k<K>(bool, bool, const Geo&, const PhysParams&, const void*, void*,         \
+  template void step_k<K>(bool, bool, const Plan&, const PhysParams&, const void*, void*,         \
                           const uint8_t*, hipStream_t);
 #define LBM_STEP2_K(K)                                                                           \
-  template void step2_k<K>(bool, bool, const Geo&, const PhysParams&, const void*, void*,        \
+  template void step2_k<K>(bool, bool, const Plan&, const PhysParams&, const void*, void*,        \
                            const uint8_t*, const uint32_t*, hipStream_t);
 #define LBM_STEP_OUT(INC)                                                                        \
-  template void step_mom_w<INC>(bool, bool, const Geo&, const PhysParams&, const float*, float*, \
+  template void step_mom_w<INC>(bool, bool, const Plan&, const PhysParams&, const float*, float*, \
                                 float*, const uint8_t*, hipStream_t);                            \
-  template void step2_out_w<kOutMid, INC>(bool, bool, const Geo&, const PhysParams&, const void*, \
+  template void step2_out_w<kOutMid, INC>(bool, bool, const Plan&, const PhysParams&, const void*, \
                                           void*, float*, void*, const uint8_t*, const uint32_t*, \
                                           hipStream_t);                                          \
-  template void step2_out_w<kOutMoments, INC>(bool, bool, const Geo&, const PhysParams&,         \
+  template void step2_out_w<kOutMoments, INC>(bool, bool, const Plan&, const PhysParams&,         \
                                               const void*, void*, float*, void*, const uint8_t*, \
                                               const uint32_t*, hipStream_t);
 #if LBM_PART == 1
@@ -2554,20 +2555,20 @@ LBM_STEP_K(ST_F32X)
 #endif
 
 #if LBM_PART == 0
-extern template void step2_out_w<kOutMid, false>(bool, bool, const Geo&, const PhysParams&,
+extern template void step2_out_w<kOutMid, false>(bool, bool, const Plan&, const PhysParams&,
                                           const void*, void*, float*, void*, const uint8_t*,
                                           const uint32_t*, hipStream_t);
-extern template void step2_out_w<kOutMid, true>(bool, bool, const Geo&, const PhysParams&,
+extern template void step2_out_w<kOutMid, true>(bool, bool, const Plan&, const PhysParams&,
                                           const void*, void*, float*, void*, const uint8_t*,
                                           const uint32_t*, hipStream_t);
-extern template void step2_out_w<kOutMoments, false>(bool, bool, const Geo&, const PhysParams&,
+extern template void step2_out_w<kOutMoments, false>(bool, bool, const Plan&, const PhysParams&,
                                           const void*, void*, float*, void*, const uint8_t*,
                                           const uint32_t*, hipStream_t);
-extern template void step2_out_w<kOutMoments, true>(bool, bool, const Geo&, const PhysParams&,
+extern template void step2_out_w<kOutMoments, true>(bool, bool, const Plan&, const PhysParams&,
                                           const void*, void*, float*, void*, const uint8_t*,
                                           const uint32_t*, hipStream_t);
 
-hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,
+hipError_t launch_step2_mid(int storage, bool solids, bool force, const Plan& g,
                             const PhysParams& ph, const void* src, void* mid, void* dst,
                             const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (storage != ST_F32) return hipErrorInvalidValue;
@@ -2577,7 +2578,7 @@ hipError_t launch_step2_mid(int storage, bool solids, bool force, const Geo& g,
   return hipGetLastError();
 }
 
-hipError_t launch_step2_mom(bool solids, bool force, const Geo& g, const PhysParams& ph,
+hipError_t launch_step2_mom(bool solids, bool force, const Plan& g, const PhysParams& ph,
                             const float* src, float* dst, float* mom1, float* mom2,
                             const uint8_t* flags, const uint32_t* lmask, hipStream_t s) {
   if (ph.incomp)
@@ -2586,7 +2587,7 @@ hipError_t launch_step2_mom(bool solids, bool force, const Geo& g, const PhysPar
   return hipGetLastError();
 }
 
-hipError_t launch_link_mask(const Geo& g, bool moving, const uint8_t* flags, uint32_t* mask,
+hipError_t launch_link_mask(const Plan& g, bool moving, const uint8_t* flags, uint32_t* mask,
                             hipStream_t s) {
   const size_t n = size_t(g.nx) * g.ny * g.nz;
   hipLaunchKernelGGL(k_link_mask, dim3(unsigned((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
@@ -2595,11 +2596,11 @@ hipError_t launch_link_mask(const Geo& g, bool moving, const uint8_t* flags, uin
 }
 
 template <int K>
-static void pull_t(const Geo& g, const void* src, void* dst, hipStream_t s) {
+static void pull_t(const Plan& g, const void* src, void* dst, hipStream_t s) {
   step_t<K, 4, false, false>(g, PhysParams{}, src, dst, nullptr, s);
 }
 
-hipError_t launch_pull_copy(int storage, const Geo& g, const void* src, void* dst, hipStream_t s) {
+hipError_t launch_pull_copy(int storage, const Plan& g, const void* src, void* dst, hipStream_t s) {
   switch (storage) {
     case ST_F32: pull_t<ST_F32>(g, src, dst, s); break;
     case ST_F16: pull_t<ST_F16>(g, src, dst, s); break;
@@ -2612,7 +2613,7 @@ hipError_t launch_pull_copy(int storage, const Geo& g, const void* src, void* ds
 }
 
 template <int K>
-static void obstacle_t(const Geo& g, const PhysParams& ph, void* grid, const uint8_t* flags,
+static void obstacle_t(const Plan& g, const PhysParams& ph, void* grid, const uint8_t* flags,
                        hipStream_t s) {
   using S = Storage<K>;
   hipLaunchKernelGGL(k_obstacle<K>, dim3(g.nblocks), dim3(kBlock), 0, s,
@@ -2620,7 +2621,7 @@ static void obstacle_t(const Geo& g, const PhysParams& ph, void* grid, const uin
                      to_phys<typename S::C>(ph));
 }
 
-hipError_t launch_obstacle(int storage, const Geo& g, const PhysParams& ph, void* grid,
+hipError_t launch_obstacle(int storage, const Plan& g, const PhysParams& ph, void* grid,
                            const uint8_t* flags, hipStream_t s) {
   switch (storage) {
     case ST_F32: obstacle_t<ST_F32>(g, ph, grid, flags, s); break;
@@ -2634,7 +2635,7 @@ hipError_t launch_obstacle(int storage, const Geo& g, const PhysParams& ph, void
 }
 
 template <int K, typename O>
-static void macro_t(const Geo& g, const PhysParams& ph, const void* grid, const uint8_t* flags,
+static void macro_t(const Plan& g, const PhysParams& ph, const void* grid, const uint8_t* flags,
                     void* rho, void* u, hipStream_t s) {
   hipLaunchKernelGGL((k_macro<K, O>), dim3(g.nblocks), dim3(kBlock), 0, s,
                      reinterpret_cast<const typename Storage<K>::T*>(grid), flags,
@@ -2643,7 +2644,7 @@ static void macro_t(const Geo& g, const PhysParams& ph, const void* grid, const 
 }
 
 template <typename O>
-static hipError_t macro_o(int storage, const Geo& g, const PhysParams& ph, const void* grid,
+static hipError_t macro_o(int storage, const Plan& g, const PhysParams& ph, const void* grid,
                           const uint8_t* flags, void* rho, void* u, hipStream_t s) {
   switch (storage) {
     case ST_F32: macro_t<ST_F32, O>(g, ph, grid, flags, rho, u, s); break;
@@ -2656,21 +2657,21 @@ static hipError_t macro_o(int storage, const Geo& g, const PhysParams& ph, const
   return hipGetLastError();
 }
 
-hipError_t launch_macro(int storage, bool out_f64, const Geo& g, const PhysParams& ph,
+hipError_t launch_macro(int storage, bool out_f64, const Plan& g, const PhysParams& ph,
                         const void* grid, const uint8_t* flags, void* rho, void* u, hipStream_t s) {
   return out_f64 ? macro_o<double>(storage, g, ph, grid, flags, rho, u, s)
                  : macro_o<float>(storage, g, ph, grid, flags, rho, u, s);
 }
 
 template <int K>
-static void reduce_t(const Geo& g, const PhysParams& ph, const void* grid, const uint8_t* flags,
+static void reduce_t(const Plan& g, const PhysParams& ph, const void* grid, const uint8_t* flags,
                      double* scratch, hipStream_t s) {
   hipLaunchKernelGGL(k_reduce_partials<K>, dim3(kReduceBlocks), dim3(kBlock), 0, s,
                      reinterpret_cast<const typename Storage<K>::T*>(grid), flags, g, ph.F[0],
                      ph.F[1], ph.F[2], 1.0 / ph.scale, ph.incomp ? 1 : 0, scratch);
 }
 
-hipError_t launch_reduce(int storage, const Geo& g, const PhysParams& ph, const void* grid,
+hipError_t launch_reduce(int storage, const Plan& g, const PhysParams& ph, const void* grid,
                          const uint8_t* flags, double* scratch, double* out5, hipStream_t s) {
   switch (storage) {
     case ST_F32: reduce_t<ST_F32>(g, ph, grid, flags, scratch, s); break;
@@ -2687,10 +2688,10 @@ hipError_t launch_reduce(int storage, const Geo& g, const PhysParams& ph, const 
 }
 
 template <bool SEED>
-static void adj_t(bool solids, const Geo& g, const PhysParams& ph, const float* fprev,
+static void adj_t(bool solids, const Plan& g, const PhysParams& ph, const float* fprev,
                   const float* nu1, float* nu0, const uint8_t* flags, const float* gr,
                   const float* gu, double* partials, hipStream_t s) {
-  const Geo h = step_geo(g, 1);
+  const Plan h = step_plan(g, 1);
   const Phys<float> p = to_phys<float>(ph);
   if (!solids)
     hipLaunchKernelGGL((k_adj<false, false, SEED>), dim3(h.nblocks), dim3(kBlock), 0, s, fprev, nu1,
@@ -2703,14 +2704,14 @@ static void adj_t(bool solids, const Geo& g, const PhysParams& ph, const float* 
                        nu0, flags, gr, gu, partials, h, p);
 }
 
-hipError_t launch_adj_seed(bool solids, const Geo& g, const PhysParams& ph, const float* fprev,
+hipError_t launch_adj_seed(bool solids, const Plan& g, const PhysParams& ph, const float* fprev,
                            const uint8_t* flags, const float* dL_drho, const float* dL_du,
                            float* nu_T, double* partials, hipStream_t s) {
   adj_t<true>(solids, g, ph, fprev, nullptr, nu_T, flags, dL_drho, dL_du, partials, s);
   return hipGetLastError();
 }
 
-hipError_t launch_adj_step(bool solids, const Geo& g, const PhysParams& ph, const float* fprev,
+hipError_t launch_adj_step(bool solids, const Plan& g, const PhysParams& ph, const float* fprev,
                            const uint8_t* flags, const float* nu_np1, float* nu_n,
                            double* partials, hipStream_t s) {
   adj_t<false>(solids, g, ph, fprev, nu_np1, nu_n, flags, nullptr, nullptr, partials, s);
@@ -2718,10 +2719,10 @@ hipError_t launch_adj_step(bool solids, const Geo& g, const PhysParams& ph, cons
 }
 
 // The same from stored moments (see store_moments): nu1 null for the seed.
-hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const float* mom,
+hipError_t launch_adj_mom(bool solids, const Plan& g, const PhysParams& ph, const float* mom,
                           const uint8_t* flags, const float* dL_drho, const float* dL_du,
                           const float* nu1, float* nu0, double* partials, hipStream_t s) {
-  const Geo h = step_geo(g, 1);
+  const Plan h = step_plan(g, 1);
   const Phys<float> p = to_phys<float>(ph);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(kBlock), 0, s, mom, nu1, nu0, flags, dL_drho,
@@ -2738,7 +2739,7 @@ hipError_t launch_adj_mom(bool solids, const Geo& g, const PhysParams& ph, const
 // Two reverse steps from stored moments (k_adj2) with the tile rows of the
 // forward pass; with solids the link mask is needed.
 template <int CHOICE>
-static void adj2_go(const Geo& g, const PhysParams& ph, const float* mom1, const float* mom2,
+static void adj2_go(const Plan& g, const PhysParams& ph, const float* mom1, const float* mom2,
                     const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
                     hipStream_t s) {
   constexpr int rows = Tb2<ST_F32>::choice[CHOICE].rows;
@@ -2751,12 +2752,12 @@ static void adj2_go(const Geo& g, const PhysParams& ph, const float* mom1, const
   lmask ? go(k_adj2<true, rows>) : go(k_adj2<false, rows>);
 }
 
-bool adj_pair_fits(const Geo& g) {
+bool adj_pair_fits(const Plan& g) {
   int64_t cost;  // one record of partials per block
   return make_geo2(g, Tb2<ST_F32>::choice[tb2_choice<ST_F32>(g)].rows, &cost).nblocks <= g.nblocks;
 }
 
-hipError_t launch_adj_pair(const Geo& g, const PhysParams& ph, const float* mom1, const float* mom2,
+hipError_t launch_adj_pair(const Plan& g, const PhysParams& ph, const float* mom1, const float* mom2,
                            const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
                            hipStream_t s) {
   static_assert(Tb2<ST_F32>::N == 3, "tile rows");
@@ -2768,7 +2769,7 @@ hipError_t launch_adj_pair(const Geo& g, const PhysParams& ph, const float* mom1
   return hipGetLastError();
 }
 
-hipError_t launch_adj_init(bool solids, const Geo& g, const PhysParams& ph, const uint8_t* flags,
+hipError_t launch_adj_init(bool solids, const Plan& g, const PhysParams& ph, const uint8_t* flags,
                            const float* nu1, const float* rho0, const float* u0, float* dL_du0,
                            hipStream_t s) {
   if (solids)
@@ -2780,7 +2781,7 @@ hipError_t launch_adj_init(bool solids, const Geo& g, const PhysParams& ph, cons
   return hipGetLastError();
 }
 
-hipError_t launch_adj_finish(const Geo& g, const double* partials, double* out3, hipStream_t s) {
+hipError_t launch_adj_finish(const Plan& g, const double* partials, double* out3, hipStream_t s) {
   hipLaunchKernelGGL(k_sum_partials<3>, dim3(1), dim3(kBlock), 0, s, partials, g.nblocks, out3);
   return hipGetLastError();
 }
