@@ -144,6 +144,46 @@ def test_rows_of_any_number_of_units(storage, nx):
     assert torch.equal(sim.grids[0], two) and torch.equal(sim.grids[1], one)
 
 
+@pytest.mark.parametrize("storage,nx", [("f32", 250), ("f32", 33), ("f64", 70), ("f32x", 100),
+                                        ("f16", 40), ("f16", 150), ("f16", 300), ("bf16", 100),
+                                        ("bf16", 200)])
+@pytest.mark.parametrize("geo", ["box", "porous", "cavity"])
+def test_filled_rows_above_the_cache(storage, nx, geo):
+    """Ragged rows of grids past the memory-side cache, whose last sector a
+    single step fills with zeros (rows of 1 to 5 units of 64 cells; fluid, solid
+    and moving-wall cells at the row end): the bytes of lbm_step_from into zeroed
+    grids, which fills nothing, padding included."""
+    size, xs, ny = {"f64": 8, "f32": 4, "f32x": 4}.get(storage, 2), -(-nx // 64) * 64, 64
+    lines = -(-nx * size // 128) * 128  # bytes of a row in the cache
+    shape = (-(-(360 << 20) // (2 * 19 * lines * ny)), ny, nx)
+    say("filled rows", storage, shape, geo)
+    u0 = 0.03 * (torch.rand((3,) + shape, generator=torch.Generator().manual_seed(9)) - 0.5)
+    kw = {}
+    if geo != "box":
+        fl = I.random_flags(shape, 64, solid_fraction=0.1, noforce_fraction=0.1)
+        fl[: shape[0] // 2, :, -1] = 1  # half of the rows end in a wall
+        if geo == "cavity":
+            fl |= I.cavity_flags(shape)
+            kw["wall_u"] = (0.03, -0.02, 0.01)
+        u0[:, torch.from_numpy(fl & 1 == 1)] = 0
+        kw["flags"] = fl
+    sim = LBM(shape, 0.7, (1e-4, 0, 0), storage, u0=u0, f16_scale_log2=8 if storage == "f16" else 0,
+              **kw)
+    assert 2 * sim.grid_bytes > 340 << 20
+    one, two = sim.new_grid().zero_(), sim.new_grid().zero_()
+    sim.step_from(sim.grids[0], one)
+    sim.step_from(one, two)
+    sim.grids[1].fill_(3)  # the padding too: the step itself has to store the zeros
+    one_filled = sim.step(1).grids[1]
+    fill = {1: torch.uint8, 2: torch.int16, 4: torch.int32, 8: torch.int64}[sim.dtype.itemsize]
+    up = min(-(-nx * size // 64) * 64 // size, xs)
+    a, b = (sim.grid_view(v, fill)[..., :up] for v in (one, one_filled))
+    assert torch.equal(a, b)
+    sim.step(1)
+    a, b = (sim.grid_view(v, fill)[..., :up] for v in (two, sim.grids[0]))
+    assert torch.equal(a, b)
+
+
 def _run_pair(shape, tau, F, storage, flags, u0, steps, s=0):
     """(GPU LBM after `steps`, oracle f after `steps`) from f^eq(1, u0)."""
     u0 = np.asarray(u0, dtype=np.float32).astype(np.float64) if u0 is not None else None
