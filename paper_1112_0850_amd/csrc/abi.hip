@@ -176,34 +176,77 @@ lbm_status noalloc_scratch_here(int* dev_out, double** out) {
 
 }  // namespace
 
+// Stores of the single step.  Plain ones leave what they write in the 256 MB
+// memory-side cache, from which the next step is fed; non-temporal ones leave the
+// L2 to the pulls.  Measured, us a step, non-temporal / plain, by the 128-byte
+// lines that the rows of both grids take there:
+//  - up to 340 MiB where rows end on a 64-byte sector (128^3 FP32, 319 MB, 65 / 62;
+//    96^3 FP64, 359 MB, 57 / 56; 121 x 170 x 128 F32X, 400 MB, 80 / 83), up to 290
+//    where a row's last sector is written in part (85 x 115 x 181 FP32, 285 MB, 62
+//    / 56; 81 x 171 x 189 F32X, 404 MB, 80 / 103), with solids in 16 bits up to 272
+//    (98 x 211 x 241 FP16 porous, 402 MB, 91 / 110; 147 x 149 x 183, 320 MB, 74 / 85);
+//  - but not in some boxes of about the size of the L2s (8 x 4 MB).  Solids there:
+//    the bounce-back reloads find less of the pulled lines.  Rows of one unit,
+//    F32X channel 69 x 42 x 64 (28 MB) 6.0 / 6.7, FP64 32 x 30 x 58 (19 MB) 4.8 /
+//    5.1; 16-bit rows of more units, whose last sectors can be filled, FP16 35 x 64
+//    x 71 channel (22 MB) 7.9 / 10.0, without solids 28 x 52 x 72 (14 MB) 5.1 /
+//    6.1; moving walls, F32X 33 x 81 x 95 (39 MB) 9.8 / 10.5, FP64 30 x 56 x 64 (33
+//    MB) 8.1 / 8.5, FP32 70 x 41 x 64 (28 MB) 8.0 / 8.5.  Smaller grids gain from
+//    plain stores again (24^3 F32X channel 3.8 / 3.6); inside these limits single
+//    boxes may still gain or lose 5% by the other choice (F32X 64 x 40 x 51
+//    channel 7.0 / 6.6, FP32 31 x 56 x 64 4.3 / 4.5).
+struct Megabytes {
+  double from, to;
+};
+// Megabytes of the 128-byte lines that the rows of both grids take.
+double cache_megabytes(const lbm::Plan& g, size_t es) {
+  return 2e-6 * lbm::Q * double((size_t(g.nx) * es + 127) / 128 * 128) * g.nrows;
+}
+// reloads: solid cells, whose neighbours load their own cell's slots
+bool cached_stores(const lbm::Plan& g, int32_t storage, size_t es, bool reloads, bool moving) {
+  const double mb = cache_megabytes(g, es);
+  Megabytes not_in = {0, 0};
+  if (reloads && moving) {
+    if (storage == LBM_F32) not_in = {22, 34};
+    if (storage == LBM_F32X) not_in = {16, 50};
+    if (storage == LBM_F64) not_in = {16, 34};
+  } else if (es == 2) {
+    if (g.nx > 64) not_in = {11, reloads ? 34.0 : 16.0};
+  } else if (reloads && g.nx <= 64) {
+    if (storage == LBM_F32X) not_in = {10, 32};
+    if (storage == LBM_F64) not_in = {13, 20};
+  }
+  if (mb >= not_in.from && mb < not_in.to) return false;
+  const int most = reloads && es == 2 ? 272 : (size_t(g.nx) * es % 64 ? 290 : 340);
+  return mb <= most * 1.048576;
+}
+
+// The pair pass and the adjoint: plain stores where both grids fit the cache.
+// Non-temporal / plain, us a step: pairs 186 MB (100^3 FP32) 28 / 21, 304 MB 41 /
+// 43, 371 MB 43 / 46; the adjoint from moments 304 MB 60 / 66 (72 x 80 x 100 FP32,
+// 137 MB: 29 / 20).
+constexpr size_t kCachedPairs = size_t(256) << 20;
+
 // Columns of a row that a single step between the context's own grids stores:
 // up to the end of the last 64-byte sector, with zeros in the padding, which is
 // zero there anyway (never for a caller's grid, whose padding stays as it is).
 // A partly written sector costs a read of memory: single steps at 300^3 with it
 // FP16 511 -> 456 us, FP32 880 -> 854, FP64 1702 -> 1631; 250^3 FP16 299 -> 266,
-// FP32 516 -> 470.  Grids that stay in the cache gain nothing.  Filling 128
-// bytes gains less; zeros stored apart from the row (by the lanes past its end,
-// ahead of their pulls) half as much; the pair pass is not bound by its stores,
-// lost 1-2% and does not fill.
+// FP32 516 -> 470.  With plain stores it gains nothing, and in boxes of the L2s'
+// size only in 16 bits (35 x 64 x 71 FP16 channel 9.6 -> 7.9, 43 x 42 x 51 F32X 5.0
+// -> 5.4).  16-bit rows of whole quadruples of units have a kernel of their own,
+// which with solids the filling one beats far past the cache only (83 x 204 x 195
+// FP16 channel, 256 MB, 68.3 us, filled 71.6; 115 x 211 x 217 BF16, 472 MB, 98.3 /
+// 98.6; 191 x 263 x 157, 733 MB, 161 / 147).  Filling 128 bytes gains less; zeros
+// stored apart from the row (by the lanes past its end, ahead of their pulls) half
+// as much; the pair pass is not bound by its stores, lost 1-2% and does not fill.
 constexpr size_t kSector = 64;
-int32_t row_fill(const lbm::Plan& g, size_t es) {
-  if (!g.stream) return g.nx;
+int32_t row_fill(const lbm::Plan& g, size_t es, bool reloads) {
+  if (!g.stream || (es != 2 && !g.stream2)) return g.nx;
+  if (es == 2 && reloads && (g.nx + 63) / 64 % 4 == 0 && cache_megabytes(g, es) < 480) return g.nx;
   const int32_t n = int32_t(kSector / es);
   const int32_t up = (g.nx + n - 1) / n * n;
   return up < g.xs ? up : g.xs;
-}
-
-// Plain stores where both grids fit the 256 MB cache, and for single steps a
-// little past it; non-temporal ones from there on.  Measured, us a step,
-// non-temporal / plain, by the size of both grids: single 233 MB (112^3 FP32) 46
-// / 29, 289 MB (144^3 FP16) 64 / 60, 304 MB (128^3 FP32) 63 / 58, 342 MB (96^3
-// FP64) 55 / 53, 356 MB (160^3 FP16) 75 / 88, 371 MB (100^3 FP64) 65 / 70;
-// pairs 186 MB (100^3 FP32) 28 / 21, 304 MB 41 / 43, 371 MB 43 / 46; the
-// adjoint from moments 304 MB 60 / 66 (72 x 80 x 100 FP32, 137 MB: 29 / 20).
-constexpr size_t kCached1 = size_t(340) << 20, kCached2 = size_t(256) << 20;
-void store_policy(lbm::Plan* g, size_t grid_bytes) {
-  g->stream = 2 * grid_bytes > kCached1;
-  g->stream2 = 2 * grid_bytes > kCached2;
 }
 
 struct lbm_ctx {
@@ -401,9 +444,6 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
   c->p = *p;
   c->sz = sz;
   c->geo = lbm::make_plan(p->nx, p->ny, p->nz, int(sz.xs), sz.dir);
-  store_policy(&c->geo, sz.grid_bytes);
-  c->geo_own = c->geo;
-  c->geo_own.xfill = row_fill(c->geo, elem_size(p->storage));
   c->ph.omega = std::isinf(p->tau) ? 0.0 : 1.0 / p->tau;
   for (int d = 0; d < 3; ++d) c->ph.F[d] = p->force[d];
   c->ph.scale = p->storage == LBM_F16 ? std::ldexp(1.0, p->f16_scale_log2) : 1.0;
@@ -412,6 +452,12 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
       flags != nullptr && (p->wall_u[0] != 0.0 || p->wall_u[1] != 0.0 || p->wall_u[2] != 0.0);
   c->ph.incomp = p->equilibrium == LBM_EQ_INCOMPRESSIBLE;
   c->ph.split = p->obstacle_kernel == 1;
+  const size_t es = elem_size(p->storage);
+  const bool reloads = flags && !c->ph.split;
+  c->geo.stream = !cached_stores(c->geo, p->storage, es, reloads, c->ph.moving);
+  c->geo.stream2 = 2 * sz.grid_bytes > kCachedPairs;
+  c->geo_own = c->geo;
+  c->geo_own.xfill = row_fill(c->geo, es, reloads);
   c->grid[0] = grid_a;
   c->grid[1] = grid_b;
   c->flags = flags;

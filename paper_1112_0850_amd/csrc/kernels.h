@@ -34,8 +34,8 @@ static_assert(sizeof(Geo) == 40, "Geo grew: see above");
 struct Plan : Geo {
   int32_t nblocks;  // blocks launched (4 segments each)
   int32_t xfill;    // columns of a row that a single step stores: nx, or more (zeros past nx)
-  bool stream;      // non-temporal stores in the single step,
-  bool stream2;     //   and in the pair pass and the adjoint (see store_policy)
+  bool stream;      // non-temporal stores in the single step (see cached_stores),
+  bool stream2;     //   and in the pair pass and the adjoint
 };
 
 // Launch geometry of the two-step kernel: 64 x TY tiles in (x, y), z chunks.

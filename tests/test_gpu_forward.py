@@ -155,7 +155,7 @@ def test_filled_rows_above_the_cache(storage, nx, geo):
     grids, which fills nothing, padding included."""
     size, xs, ny = {"f64": 8, "f32": 4, "f32x": 4}.get(storage, 2), -(-nx // 64) * 64, 64
     lines = -(-nx * size // 128) * 128  # bytes of a row in the cache
-    shape = (-(-(360 << 20) // (2 * 19 * lines * ny)), ny, nx)
+    shape = (-(-(480 << 20) // (2 * 19 * lines * ny)), ny, nx)
     say("filled rows", storage, shape, geo)
     u0 = 0.03 * (torch.rand((3,) + shape, generator=torch.Generator().manual_seed(9)) - 0.5)
     kw = {}
@@ -182,6 +182,32 @@ def test_filled_rows_above_the_cache(storage, nx, geo):
     sim.step(1)
     a, b = (sim.grid_view(v, fill)[..., :up] for v in (two, sim.grids[0]))
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("storage,shape,geo", [
+    ("f32x", (29, 58, 54), "walls"), ("f64", (29, 31, 52), "walls"), ("f16", (35, 64, 71), "walls"),
+    ("bf16", (30, 72, 66), "walls"), ("f32", (70, 41, 64), "cavity"), ("f32x", (33, 81, 95), "cavity"),
+    ("f64", (30, 56, 64), "cavity")])
+def test_boxes_of_the_l2s_size(storage, shape, geo):
+    """Boxes with solids that take non-temporal stores although both grids fit the
+    memory-side cache: the bytes of a box of twice the height with the same content
+    twice, which takes plain ones or fills no rows."""
+    say("L2-sized box", storage, shape, geo)
+    fl = I.cavity_flags(shape) if geo == "cavity" else \
+        I.random_flags(shape, 65, solid_fraction=0.1, noforce_fraction=0.1)
+    if geo != "cavity":
+        fl[:, 0] = fl[:, -1] = 1
+    u0 = 0.03 * (torch.rand((3,) + shape, generator=torch.Generator().manual_seed(10)) - 0.5)
+    u0[:, torch.from_numpy(fl & 1 == 1)] = 0
+    runs = []
+    for n in (1, 2):
+        sim = LBM((n * shape[0],) + shape[1:], 0.7, (1e-5, 0, 2e-5), storage, u0=torch.cat([u0] * n, 1),
+                  flags=np.concatenate([fl] * n), f16_scale_log2=8 if storage == "f16" else 0,
+                  wall_u=(0.04, 0.01, 0) if geo == "cavity" else (0, 0, 0)).step(5)
+        runs.append(sim.populations().clone())
+    it = {2: torch.int16, 4: torch.int32, 8: torch.int64}[runs[0].element_size()]
+    a, b = (r.contiguous().view(it)[..., :shape[2]] for r in runs)
+    assert torch.equal(a, b[:, :shape[0]]) and torch.equal(a, b[:, shape[0]:])
 
 
 def _run_pair(shape, tau, F, storage, flags, u0, steps, s=0):
