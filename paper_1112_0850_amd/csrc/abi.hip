@@ -185,16 +185,17 @@ lbm_status noalloc_scratch_here(int* dev_out, double** out) {
 //    where a row's last sector is written in part (85 x 115 x 181 FP32, 285 MB, 62
 //    / 56; 81 x 171 x 189 F32X, 404 MB, 80 / 103), with solids in 16 bits up to 272
 //    (98 x 211 x 241 FP16 porous, 402 MB, 91 / 110; 147 x 149 x 183, 320 MB, 74 / 85);
-//  - but not in some boxes of about the size of the L2s (8 x 4 MB).  Solids there:
-//    the bounce-back reloads find less of the pulled lines.  Rows of one unit,
-//    F32X channel 69 x 42 x 64 (28 MB) 6.0 / 6.7, FP64 32 x 30 x 58 (19 MB) 4.8 /
-//    5.1; 16-bit rows of more units, whose last sectors can be filled, FP16 35 x 64
-//    x 71 channel (22 MB) 7.9 / 10.0, without solids 28 x 52 x 72 (14 MB) 5.1 /
-//    6.1; moving walls, F32X 33 x 81 x 95 (39 MB) 9.8 / 10.5, FP64 30 x 56 x 64 (33
-//    MB) 8.1 / 8.5, FP32 70 x 41 x 64 (28 MB) 8.0 / 8.5.  Smaller grids gain from
-//    plain stores again (24^3 F32X channel 3.8 / 3.6); inside these limits single
-//    boxes may still gain or lose 5% by the other choice (F32X 64 x 40 x 51
-//    channel 7.0 / 6.6, FP32 31 x 56 x 64 4.3 / 4.5).
+//  - but not in boxes of about the size of the L2s (8 x 4 MB) where few lanes are
+//    idle (rows that fill 78% of their units) or reload at moving walls: with plain
+//    stores the pulls and reloads find less there.  F32X spheres 5 x 78 x 336 (20
+//    MB) 5.7 / 6.7, channel 69 x 42 x 64 (28 MB) 6.0 / 6.7; FP64 3 x 97 x 192 (17
+//    MB) 5.2 / 5.5; FP32 2 x 132 x 424 (17 MB) 5.1 / 5.6; cavities F32X 33 x 81 x 95
+//    (39 MB) 9.8 / 10.5, FP64 30 x 56 x 64 (33 MB) 8.1 / 8.5, FP32 70 x 41 x 64 (28
+//    MB) 8.0 / 8.5.  16-bit rows of several units, whose last sectors can be
+//    filled: FP16 35 x 64 x 71 channel (22 MB) 7.9 / 10.0, BF16 1 x 720 x 512 cavity
+//    (28 MB) 8.7 / 9.7, without solids 28 x 52 x 72 (14 MB) 5.1 / 6.1.  Rows that
+//    waste more lanes gain from plain stores (F32X 64 x 40 x 51 channel 7.0 / 6.6),
+//    and so do smaller grids (24^3 F32X channel 3.8 / 3.6).
 struct Megabytes {
   double from, to;
 };
@@ -205,16 +206,18 @@ double cache_megabytes(const lbm::Plan& g, size_t es) {
 // reloads: solid cells, whose neighbours load their own cell's slots
 bool cached_stores(const lbm::Plan& g, int32_t storage, size_t es, bool reloads, bool moving) {
   const double mb = cache_megabytes(g, es);
+  const bool busy = g.nx >= 0.78 * 64 * g.nseg;
   Megabytes not_in = {0, 0};
-  if (reloads && moving) {
-    if (storage == LBM_F32) not_in = {22, 34};
+  if (es == 2) {
+    if (g.nx > 64) not_in = {11, reloads ? 46.0 : 16.0};
+  } else if (reloads && moving) {
+    if (storage == LBM_F32) not_in = {busy ? 15.0 : 22.0, 34};
     if (storage == LBM_F32X) not_in = {16, 50};
     if (storage == LBM_F64) not_in = {16, 34};
-  } else if (es == 2) {
-    if (g.nx > 64) not_in = {11, reloads ? 34.0 : 16.0};
-  } else if (reloads && g.nx <= 64) {
-    if (storage == LBM_F32X) not_in = {10, 32};
-    if (storage == LBM_F64) not_in = {13, 20};
+  } else if (busy) {
+    if (storage == LBM_F32) not_in = {reloads ? 15.0 : 13.0, reloads ? 26.0 : 19.0};
+    if (storage == LBM_F32X && reloads) not_in = {10, 32};
+    if (storage == LBM_F64) not_in = {13, 21};
   }
   if (mb >= not_in.from && mb < not_in.to) return false;
   const int most = reloads && es == 2 ? 272 : (size_t(g.nx) * es % 64 ? 290 : 340);
@@ -234,16 +237,16 @@ constexpr size_t kCachedPairs = size_t(256) << 20;
 // FP16 511 -> 456 us, FP32 880 -> 854, FP64 1702 -> 1631; 250^3 FP16 299 -> 266,
 // FP32 516 -> 470.  With plain stores it gains nothing, and in boxes of the L2s'
 // size only in 16 bits (35 x 64 x 71 FP16 channel 9.6 -> 7.9, 43 x 42 x 51 F32X 5.0
-// -> 5.4).  16-bit rows of whole quadruples of units have a kernel of their own,
-// which with solids the filling one beats far past the cache only (83 x 204 x 195
-// FP16 channel, 256 MB, 68.3 us, filled 71.6; 115 x 211 x 217 BF16, 472 MB, 98.3 /
-// 98.6; 191 x 263 x 157, 733 MB, 161 / 147).  Filling 128 bytes gains less; zeros
+// -> 5.4).  16-bit rows that run four units a lane (step_fours) have a kernel of
+// their own, which with solids the filling one beats far past the cache only (83 x
+// 204 x 195 FP16 channel, 256 MB, 68.3 us, filled 71.6; 115 x 211 x 217 BF16, 472
+// MB, 98.3 / 98.6; 191 x 263 x 157, 733 MB, 161 / 147).  Filling 128 bytes gains less; zeros
 // stored apart from the row (by the lanes past its end, ahead of their pulls) half
 // as much; the pair pass is not bound by its stores, lost 1-2% and does not fill.
 constexpr size_t kSector = 64;
 int32_t row_fill(const lbm::Plan& g, size_t es, bool reloads) {
   if (!g.stream || (es != 2 && !g.stream2)) return g.nx;
-  if (es == 2 && reloads && (g.nx + 63) / 64 % 4 == 0 && cache_megabytes(g, es) < 480) return g.nx;
+  if (es == 2 && reloads && lbm::step_fours(g.nx) && cache_megabytes(g, es) < 480) return g.nx;
   const int32_t n = int32_t(kSector / es);
   const int32_t up = (g.nx + n - 1) / n * n;
   return up < g.xs ? up : g.xs;

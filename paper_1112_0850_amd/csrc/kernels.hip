@@ -2139,9 +2139,9 @@ constexpr int band_rows(int M) { return M >= 4 ? 16 : 32; }
   return h;
 }
 
-// A row's units are dealt evenly to as few waves as M allows.  Where every wave
-// gets M the kernel is the one for exactly M; elsewhere each wave runs its own
-// count (M = 0).  Waves of always 4 units ran 1, 2 or 3 of them past the row
+// A row's units are dealt evenly to as few waves as M allows.  Where they nearly
+// fill waves of M (step_fours) the kernel is the one for exactly M; elsewhere each
+// wave runs its own count (M = 0).  Waves of always 4 units ran 1, 2 or 3 of them past the row
 // end: FP16, us a step, 64^3 7.0 -> 5.8, 128^3 37.4 -> 34.2, 320^3 546 -> 518
 // (porous).  The kernel for exactly 4 stays, being 3% faster than the switch at
 // 256^3 (271 / 281) and 1% at 512^3.
@@ -2158,9 +2158,9 @@ static void step_t(const Plan& g, const PhysParams& ph, const void* src, void* d
                        make_stepk<typename S::C>(ph), more...);
   };
   constexpr int ANY = M > 1 ? 0 : 1;
-  const bool some = (g.nx + 63) / 64 % M != 0;  // waves of fewer units than M
+  const bool some = M > 1 && !step_fours(g.nx);  // waves of their own number of units
   if (!h.stream) {
-    if (M > 1 && some) return go(k_step_cached<K, WALLS, FORCE, INC, ANY>);
+    if (some) return go(k_step_cached<K, WALLS, FORCE, INC, ANY>);
     return go(k_step_cached<K, WALLS, FORCE, INC, M>);
   }
   if constexpr (WALLS != 4) {
