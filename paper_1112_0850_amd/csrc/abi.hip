@@ -307,7 +307,7 @@ lbm_status enqueue_steps(lbm_ctx* c, int32_t n, int* cur, hipStream_t s, int32_t
   const bool pairs =
       c->p.steps_per_pass == 2 ||
       (c->p.steps_per_pass == LBM_STEPS_AUTO && c->p.obstacle_kernel == 0 &&
-       lbm::step2_pays(c->p.storage, c->geo));
+       c->geo.pairs.pays);
   while (n > 0) {
     const int k = *cur;
     if (pairs && n >= 2) {
@@ -456,6 +456,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* grid_a, void* grid
   c->ph.incomp = p->equilibrium == LBM_EQ_INCOMPRESSIBLE;
   c->ph.split = p->obstacle_kernel == 1;
   const size_t es = elem_size(p->storage);
+  c->geo.pairs = lbm::plan_pairs(p->storage, p->nx, p->ny, p->nz);
   const bool reloads = flags && !c->ph.split;
   c->geo.stream = !cached_stores(c->geo, p->storage, es, reloads, c->ph.moving);
   c->geo.stream2 = 2 * sz.grid_bytes > kCachedPairs;

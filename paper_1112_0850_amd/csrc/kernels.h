@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "pair_plan.h"
+
 namespace lbm {
 
 // Launch geometry shared by every per-cell kernel.  A wavefront owns a
@@ -36,6 +38,7 @@ struct Plan : Geo {
   int32_t xfill;    // columns of a row that a single step stores: nx, or more (zeros past nx)
   bool stream;      // non-temporal stores in the single step (see cached_stores),
   bool stream2;     //   and in the pair pass and the adjoint
+  PairPlan pairs;   // the two-step pass (of the context's storage)
 };
 
 // Launch geometry of the two-step kernel: 64 x TY tiles in (x, y), z chunks.
@@ -94,14 +97,6 @@ hipError_t launch_step(int storage, bool solids, bool force, const Plan& g, cons
 hipError_t launch_step2(int storage, bool solids, bool force, const Plan& g, const PhysParams& ph,
                         const void* src, void* dst, const uint8_t* flags, const uint32_t* lmask,
                         hipStream_t s);
-// Whether two fused steps are faster than two single ones on this grid (they
-// give the same bits).
-bool step2_pays(int storage, const Plan& g);
-// Whether they go through the small-box kernel: us a step, small-box / z-marching
-// kernel, FP32 48^3 4.9 / 6.3, 64^3 7.7 / 7.1; FP64 48^3 5.8 / 6.8, 64^3 10.8 / 10.8.
-inline bool step2_tiles(const Plan& g) {
-  return int64_t(g.nx) * g.ny * g.nz <= (int64_t(1) << 17);
-}
 // The same two steps storing the intermediate level too: mid = f*(t+1)
 // (FP32 storage only: hipErrorInvalidValue otherwise).
 hipError_t launch_step2_mid(int storage, bool solids, bool force, const Plan& g,

@@ -52,6 +52,7 @@ Plan make_plan(int nx, int ny, int nz, int xs, uint64_t dir_stride) {
   g.upw = 1;
   g.xfill = nx;
   g.stream = g.stream2 = true;
+  g.pairs = {};
   g.yb = g.ny;
   return g;
 }
@@ -733,40 +734,6 @@ __device__ __forceinline__ U pick(uint32_t sel, U a, U b) {
     return U(bfi32(sel, uint32_t(a), uint32_t(b)));
   }
 }
-constexpr int kTB2MinChunk = 2;  // shortest z chunk (planes per block)
-// The longest: blocks that march further drift apart and find less of their
-// halos in L2 (640^3 FP16 with chunks of 640 planes 76.5k MLUPS, of 128 83k).
-constexpr int kTB2MaxChunk = 128;
-constexpr int kCUs = 256;
-
-// Tile rows per block, the first the one that large grids take: 13 (16 waves,
-// 1024 threads, one block per CU: the FP32 ring takes 127 KB of LDS) for 4- and
-// 2-byte storage, which fit 128 VGPRs without spills; at 512^3 13 rows beat 12,
-// 8, 6 and 5.  FP64 storage takes 5 (118 KB of LDS; 6 rows cap the 9 waves at
-// 168 VGPRs, spill and ran 0.7% slower), and F32X (FP64 arithmetic) 8, whose 11
-// waves may use 168 VGPRs.  The others serve the sizes that the first leaves a
-// last round nearly empty on (see make_geo2); `cost` is the measured time of a
-// plane against the first's (FP32 6.2 / 4.55 / 4.1 us, FP16 4.3 / 3.3 / 2.9,
-// FP64 4.7 / 4.0).
-struct Tb2Rows {
-  int rows;
-  double cost;
-};
-template <int K>
-struct Tb2 {
-  static constexpr int N = 3;
-  static constexpr Tb2Rows choice[N] = {{13, 1.0}, {10, 0.74}, {8, 0.67}};
-};
-template <>
-struct Tb2<ST_F64> {
-  static constexpr int N = 2;
-  static constexpr Tb2Rows choice[N] = {{5, 1.0}, {4, 0.85}};
-};
-template <>
-struct Tb2<ST_F32X> {
-  static constexpr int N = 1;
-  static constexpr Tb2Rows choice[N] = {{8, 1.0}};
-};
 __host__ __device__ constexpr int tb2_nslot(int i) {
   return D3Q19::cz[i] > 0 ? 3 : (D3Q19::cz[i] == 0 ? 2 : 1);
 }
@@ -2257,17 +2224,9 @@ hipError_t launch_step(int storage, bool solids, bool force, const Plan& g, cons
 }
 #endif  // LBM_PART == 0
 
-// Geometry of the two-step kernel's launch with tiles of `rows` rows; *cost gets
-// its time in planes.  One block fills a CU, so the blocks run in rounds of
-// kCUs, and a block's time is its planes plus the two it recomputes plus about
-// two planes of start-up -- measured 6.1-6.6 us a plane and round in FP32 from
-// 128^3 to 512^3, 4.1-4.3 in BF16 and 4.6-4.8 in FP64, whatever the z chunk.  So
-// the chunk length is the one with the least rounds * (planes + 4).  (Against
-// chunks of 128 planes halved down to 16 until there were 1280 blocks: 128^3
-// FP32 103 -> 85 us a pass, 128 x 128 x 256 204 -> 155, 200^3 404 -> 329, 256^3
-// 589 -> 541, 200^3 BF16 289 -> 225, 100^3 FP64 130 -> 84; 512^3 keeps its 128
-// planes.)
-[[maybe_unused]] static Geo2 make_geo2(const Plan& g, int rows, int64_t* cost) {
+// Geometry of the two-step kernel's launch with tiles of `rows` rows and chunks of
+// zc planes.
+[[maybe_unused]] static Geo2 make_geo2(const Plan& g, int rows, int zc) {
   Geo2 h;
   h.nx = g.nx;
   h.ny = g.ny;
@@ -2276,46 +2235,10 @@ hipError_t launch_step(int storage, bool solids, bool force, const Plan& g, cons
   h.plane = g.plane;
   h.ntx = (g.nx + 63) / 64;
   h.nty = (g.ny + rows - 1) / rows;
-  const int64_t tiles = int64_t(h.ntx) * h.nty;
-  *cost = INT64_MAX;
-  h.zc = g.nz;
-  for (int n = (g.nz + kTB2MaxChunk - 1) / kTB2MaxChunk; n <= g.nz; ++n) {
-    const int zc = (g.nz + n - 1) / n;
-    if (zc < kTB2MinChunk && n > 1) break;
-    const int64_t rounds = (tiles * ((g.nz + zc - 1) / zc) + kCUs - 1) / kCUs;
-    if (rounds * (zc + 4) < *cost) {
-      *cost = rounds * (zc + 4);
-      h.zc = zc;
-    }
-  }
-  const int nzc = (g.nz + h.zc - 1) / h.zc;
-  h.nblocks = h.ntx * h.nty * nzc;
+  h.zc = zc;
+  h.nblocks = h.ntx * h.nty * ((g.nz + zc - 1) / zc);
   h.nb8 = (h.nblocks / 8) * 8;
   return h;
-}
-
-// The choice of tile rows for a grid: the first unless another one's time, by
-// the same measure, is 6% less, in boxes of more than 2^23 cells 12% (the halo
-// rows of smaller tiles cost memory traffic that the measure leaves out, and the
-// more so the longer the pass runs: 640^3 with 10 rows, 7% less by the measure,
-// FP16 78k MLUPS against 84k with 13).  Measured, us a pass, 13 rows against the
-// chosen: FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256 171 /
-// 157 (8), 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4).
-template <int K>
-static int tb2_choice(const Plan& g) {
-  int best = 0;
-  double least = 0.0;
-  for (int i = 0; i < Tb2<K>::N; ++i) {
-    int64_t planes;
-    make_geo2(g, Tb2<K>::choice[i].rows, &planes);
-    const double c = double(planes) * Tb2<K>::choice[i].cost;
-    if (i == 0) least = (int64_t(g.nx) * g.ny * g.nz > (1 << 23) ? 0.88 : 0.94) * c;
-    else if (c < least) {
-      least = c;
-      best = i;
-    }
-  }
-  return best;
 }
 
 template <int K, int WALLS, bool FORCE, bool INC, int OUT, int CHOICE, bool NT>
@@ -2323,9 +2246,8 @@ static void step2_go(const Plan& g, const PhysParams& ph, const void* src, void*
                      const uint8_t* flags, const uint32_t* lmask, hipStream_t s, void* mid,
                      float* mom2) {
   using S = Storage<K>;
-  constexpr int rows = Tb2<K>::choice[CHOICE].rows;
-  int64_t cost;
-  const Geo2 h = make_geo2(g, rows, &cost);
+  constexpr int rows = tb2_table(K).choice[CHOICE].rows;
+  const Geo2 h = make_geo2(g, rows, g.pairs.zc[CHOICE]);
   hipLaunchKernelGGL((k_step2<K, WALLS, FORCE, INC, OUT, rows, NT>), dim3(h.nblocks),
                      dim3(64 * (rows + 3)), 0, s, reinterpret_cast<const typename S::T*>(src),
                      reinterpret_cast<typename S::T*>(mid), mom2,
@@ -2333,37 +2255,9 @@ static void step2_go(const Plan& g, const PhysParams& ph, const void* src, void*
                      make_stepk<typename S::C>(ph));
 }
 
-// The tile of the small-box kernel: the least rounds of kCUs blocks times the
-// waves of a block's two steps, the rows its pulls touch weighing a tenth of a
-// wave each (32^3 FP32: 16 x 2 x 4 5.8 us a pass, 8 x 4 x 4 and 32 x 2 x 2 6.2,
-// 8 x 4 x 2 6.8).
 [[maybe_unused]] static GeoT make_geot(const Plan& g) {
-  static constexpr int dims[][3] = {{8, 4, 2}, {16, 2, 4}, {8, 4, 4}, {8, 8, 4}, {12, 6, 6}};
-  GeoT best{};
-  double least = 0.0;
-  for (const auto& d : dims) {
-    GeoT h;
-    h.nx = g.nx;
-    h.ny = g.ny;
-    h.nz = g.nz;
-    h.xs = g.xs;
-    h.plane = g.plane;
-    h.tx = d[0];
-    h.ty = d[1];
-    h.tz = d[2];
-    h.ntx = (g.nx + h.tx - 1) / h.tx;
-    h.nty = (g.ny + h.ty - 1) / h.ty;
-    h.nblocks = h.ntx * h.nty * ((g.nz + h.tz - 1) / h.tz);
-    h.nb8 = h.nblocks / 8 * 8;
-    const int rows = (h.ty + 2) * (h.tz + 2), e = (h.tx + 2) * rows, o = h.tx * h.ty * h.tz;
-    const double c =
-        ((h.nblocks + kCUs - 1) / kCUs) * ((e + 63) / 64 + (o + 63) / 64 + 0.1 * rows);
-    if (!best.nblocks || c < least) {
-      least = c;
-      best = h;
-    }
-  }
-  return best;
+  const TilePlan& t = g.pairs.tile;
+  return {g.nx, g.ny, g.nz, g.xs, g.plane, t.tx, t.ty, t.tz, t.ntx, t.nty, t.nblocks, t.nblocks / 8 * 8};
 }
 
 template <int K, int WALLS, bool FORCE, bool INC, int OUT>
@@ -2388,7 +2282,7 @@ static void step2_t(const Plan& g, const PhysParams& ph, const void* src, void* 
   };
   constexpr std::integral_constant<int, 0> c0;
   if constexpr (OUT != kOutMid) {
-    if (step2_tiles(g))
+    if (g.pairs.tiles)
       return step2_tile_go<K, WALLS == 4 ? 1 : (WALLS == 5 ? 2 : WALLS), FORCE, INC, OUT>(g, ph, src, dst, flags, s,
                                                                        mid, mom2);
   }
@@ -2396,12 +2290,12 @@ static void step2_t(const Plan& g, const PhysParams& ph, const void* src, void* 
   // without the link mask (pairs of direction arrays over 4 GiB, or a context
   // made for single steps)
   if constexpr (OUT != kOutMid && WALLS != 1 && WALLS != 2) {
-    const int c = tb2_choice<K>(g);
-    if constexpr (Tb2<K>::N > 2) {
+    const int c = g.pairs.choice;
+    if constexpr (tb2_table(K).n > 2) {
       constexpr std::integral_constant<int, 2> c2;
       if (c == 2) return g.stream2 ? go(c2, std::true_type{}) : go(c2, std::false_type{});
     }
-    if constexpr (Tb2<K>::N > 1) {
+    if constexpr (tb2_table(K).n > 1) {
       constexpr std::integral_constant<int, 1> c1;
       if (c == 1) return g.stream2 ? go(c1, std::true_type{}) : go(c1, std::false_type{});
     }
@@ -2447,44 +2341,6 @@ extern template void step2_k<ST_F64>(bool, bool, const Plan&, const PhysParams&,
                                    const uint8_t*, const uint32_t*, hipStream_t);
 extern template void step2_k<ST_F32X>(bool, bool, const Plan&, const PhysParams&, const void*, void*,
                                    const uint8_t*, const uint32_t*, hipStream_t);
-
-
-// Blocks of a z-marching launch with the storage's first choice of tile rows.
-template <int K>
-static int step2_blocks_k(const Plan& g) {
-  int64_t cost;
-  return make_geo2(g, Tb2<K>::choice[0].rows, &cost).nblocks;
-}
-
-// Single steps / pairs, us a step.  In the small-box kernel pairs win where one
-// round of blocks with tiles of at most 128 cells covers the box: FP32 24^3 3.4 /
-// 2.5, 32^3 3.6 / 3.2 (porous 4.2 / 3.9), FP16 32^3 3.2 / 2.5, FP64 5.3 / 3.5;
-// past that only some do (29 x 26 x 46 porous FP32 4.4 / 5.2, box F32X 3.6 / 3.8,
-// FP64 5.2 / 4.2).  In the z-marching kernel fewer
-// blocks than 128 leave most CUs idle, and a pass of few planes per block fills
-// the ring more than it uses it; by storage from the size where no kind of
-// wall loses more than 2%: FP32 56 x 60 x 72 porous 10.7 / 11.9, 64^3 8.9 / 8.8,
-// 96^3 24.0 / 23.7; FP64 14.8 / 15.7, 13.2 / 12.8, 57 / 46; BF16 64^3 cavity 7.6
-// / 8.4, 80^3 18.1 / 14.6; F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33.
-bool step2_pays(int storage, const Plan& g) {
-  if (step2_tiles(g)) {
-    const GeoT h = make_geot(g);
-    return h.nblocks <= kCUs && h.tx * h.ty * h.tz <= 128;
-  }
-  const int64_t least = storage == ST_F32X                          ? 1 << 20
-                        : storage == ST_F32 || storage == ST_F64 ? 1 << 18
-                                                                  : 400000;
-  if (int64_t(g.nx) * g.ny * g.nz < least) return false;
-  int blocks = 0;
-  switch (storage) {
-    case ST_F32: blocks = step2_blocks_k<ST_F32>(g); break;
-    case ST_F16: blocks = step2_blocks_k<ST_F16>(g); break;
-    case ST_BF16: blocks = step2_blocks_k<ST_BF16>(g); break;
-    case ST_F64: blocks = step2_blocks_k<ST_F64>(g); break;
-    case ST_F32X: blocks = step2_blocks_k<ST_F32X>(g); break;
-  }
-  return blocks >= 128;
-}
 
 hipError_t launch_step2(int storage, bool solids, bool force, const Plan& g, const PhysParams& ph,
                         const void* src, void* dst, const uint8_t* flags, const uint32_t* lmask,
@@ -2752,9 +2608,8 @@ template <int CHOICE>
 static void adj2_go(const Plan& g, const PhysParams& ph, const float* mom1, const float* mom2,
                     const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
                     hipStream_t s) {
-  constexpr int rows = Tb2<ST_F32>::choice[CHOICE].rows;
-  int64_t cost;
-  const Geo2 h = make_geo2(g, rows, &cost);
+  constexpr int rows = tb2_table(ST_F32).choice[CHOICE].rows;
+  const Geo2 h = make_geo2(g, rows, g.pairs.zc[CHOICE]);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(h.nblocks), dim3(64 * (rows + 3)), 0, s, mom1, mom2, nu2, nu0,
                        lmask, partials, h, to_phys<float>(ph));
@@ -2763,15 +2618,16 @@ static void adj2_go(const Plan& g, const PhysParams& ph, const float* mom1, cons
 }
 
 bool adj_pair_fits(const Plan& g) {
-  int64_t cost;  // one record of partials per block
-  return make_geo2(g, Tb2<ST_F32>::choice[tb2_choice<ST_F32>(g)].rows, &cost).nblocks <= g.nblocks;
+  // one record of partials per block
+  const int c = g.pairs.choice;
+  return make_geo2(g, tb2_table(ST_F32).choice[c].rows, g.pairs.zc[c]).nblocks <= g.nblocks;
 }
 
 hipError_t launch_adj_pair(const Plan& g, const PhysParams& ph, const float* mom1, const float* mom2,
                            const float* nu2, float* nu0, const uint32_t* lmask, double* partials,
                            hipStream_t s) {
-  static_assert(Tb2<ST_F32>::N == 3, "tile rows");
-  switch (tb2_choice<ST_F32>(g)) {
+  static_assert(tb2_table(ST_F32).n == 3, "tile rows");
+  switch (g.pairs.choice) {
     case 1: adj2_go<1>(g, ph, mom1, mom2, nu2, nu0, lmask, partials, s); break;
     case 2: adj2_go<2>(g, ph, mom1, mom2, nu2, nu0, lmask, partials, s); break;
     default: adj2_go<0>(g, ph, mom1, mom2, nu2, nu0, lmask, partials, s); break;

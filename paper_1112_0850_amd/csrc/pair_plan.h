@@ -1,0 +1,144 @@
+// pair_plan.h -- how the two-step pass is laid out on a box: the tile rows and z
+// chunks of the z-marching kernel and the tiles of the small-box kernel.  Host
+// arithmetic on the box alone, done once per context: searched for at every
+// launch it took 11 us of host time at 512 planes and 2 ms at 100000.
+#pragma once
+
+#include <stdint.h>
+
+#include "../../include/lbm.h"
+
+namespace lbm {
+
+constexpr int kTB2MinChunk = 2;  // shortest z chunk (planes per block)
+// The longest: blocks that march further drift apart and find less of their
+// halos in L2 (640^3 FP16 with chunks of 640 planes 76.5k MLUPS, of 128 83k).
+constexpr int kTB2MaxChunk = 128;
+constexpr int kCUs = 256;
+
+// Tile rows per block, the first the one that large grids take: 13 (16 waves,
+// 1024 threads, one block per CU: the FP32 ring takes 127 KB of LDS) for 4- and
+// 2-byte storage, which fit 128 VGPRs (forced FP32 along moving walls with two
+// spilled); at 512^3 13 rows beat 12, 8, 6 and 5.  FP64 storage takes 5 (118 KB of
+// LDS; 6 rows cap the 9 waves at 168 VGPRs, spill and ran 0.7% slower), and F32X
+// (FP64 arithmetic) 8, whose 11 waves may use 168 VGPRs.  The others serve the
+// sizes that the first leaves a last round nearly empty on (see plan_pairs);
+// `cost` is the measured time of a plane against the first's (FP32 6.2 / 4.55 /
+// 4.1 us, FP16 4.3 / 3.3 / 2.9, FP64 4.7 / 4.0).
+struct Tb2Rows {
+  int rows;
+  double cost;
+};
+struct Tb2Table {
+  int n;
+  Tb2Rows choice[3];
+};
+constexpr Tb2Table tb2_table(int storage) {
+  return storage == LBM_F64    ? Tb2Table{2, {{5, 1.0}, {4, 0.85}, {}}}
+         : storage == LBM_F32X ? Tb2Table{1, {{8, 1.0}, {}, {}}}
+                               : Tb2Table{3, {{13, 1.0}, {10, 0.74}, {8, 0.67}}};
+}
+
+// The z chunk of tiles of `rows` rows; *cost gets the pass's time in planes.  One
+// block fills a CU, so the blocks run in rounds of kCUs, and a block's time is its
+// planes plus the two it recomputes plus about two planes of start-up -- measured
+// 6.1-6.6 us a plane and round in FP32 from 128^3 to 512^3, 4.1-4.3 in BF16 and
+// 4.6-4.8 in FP64, whatever the z chunk.  So the chunk length is the one with the
+// least rounds * (planes + 4), the longest of several.  (Against chunks of 128
+// planes halved down to 16 until there were 1280 blocks: 128^3 FP32 103 -> 85 us a
+// pass, 128 x 128 x 256 204 -> 155, 200^3 404 -> 329, 256^3 589 -> 541, 200^3 BF16
+// 289 -> 225, 100^3 FP64 130 -> 84; 512^3 keeps its 128 planes.)
+inline int z_chunk(int nx, int ny, int nz, int rows, int64_t* cost) {
+  const int64_t tiles = int64_t((nx + 63) / 64) * ((ny + rows - 1) / rows);
+  int best = nz;
+  *cost = INT64_MAX;
+  for (int zc = nz < kTB2MaxChunk ? nz : kTB2MaxChunk; zc >= kTB2MinChunk || zc == nz; --zc) {
+    const int64_t rounds = (tiles * ((nz + zc - 1) / zc) + kCUs - 1) / kCUs;
+    if (rounds * (zc + 4) < *cost) {
+      *cost = rounds * (zc + 4);
+      best = zc;
+    }
+  }
+  return best;
+}
+
+struct TilePlan {
+  int32_t tx, ty, tz, ntx, nty, nblocks;
+  double cost;
+};
+
+// The tile of the small-box kernel: the least rounds of kCUs blocks times the
+// waves of a block's two steps, the rows its pulls touch weighing a tenth of a
+// wave each (32^3 FP32: 16 x 2 x 4 5.8 us a pass, 8 x 4 x 4 and 32 x 2 x 2 6.2,
+// 8 x 4 x 2 6.8).
+inline TilePlan plan_tiles(int nx, int ny, int nz) {
+  constexpr int dims[][3] = {{8, 4, 2}, {16, 2, 4}, {8, 4, 4}, {8, 8, 4}, {12, 6, 6}};
+  TilePlan best{};
+  for (const auto& d : dims) {
+    TilePlan t{d[0], d[1], d[2], (nx + d[0] - 1) / d[0], (ny + d[1] - 1) / d[1], 0, 0.0};
+    t.nblocks = t.ntx * t.nty * ((nz + t.tz - 1) / t.tz);
+    const int rows = (t.ty + 2) * (t.tz + 2), e = (t.tx + 2) * rows, o = t.tx * t.ty * t.tz;
+    t.cost = ((t.nblocks + kCUs - 1) / kCUs) * ((e + 63) / 64 + (o + 63) / 64 + 0.1 * rows);
+    if (!best.nblocks || t.cost < best.cost) best = t;
+  }
+  return best;
+}
+
+struct PairPlan {
+  int32_t choice;  // tile rows of the z-marching kernel: index into tb2_table
+  int32_t zc[3];   // z chunk with each of them
+  bool tiles;      // the pass goes through the small-box kernel, with these tiles
+  TilePlan tile;
+  bool pays;       // two fused steps are faster than two single ones (the same bits)
+};
+
+inline PairPlan plan_pairs(int storage, int nx, int ny, int nz) {
+  const Tb2Table table = tb2_table(storage);
+  const int64_t cells = int64_t(nx) * ny * nz;
+  PairPlan p{};
+  // The choice of tile rows: the first unless another one's time, by the same
+  // measure, is 6% less, in boxes of more than 2^23 cells 12% (the halo rows of
+  // smaller tiles cost memory traffic that the measure leaves out, and the more so
+  // the longer the pass runs: 640^3 with 10 rows, 7% less by the measure, FP16 78k
+  // MLUPS against 84k with 13).  Measured, us a pass, 13 rows against the chosen:
+  // FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256 171 / 157 (8),
+  // 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4).
+  double least = 0.0;
+  for (int i = 0; i < table.n; ++i) {
+    int64_t planes;
+    p.zc[i] = z_chunk(nx, ny, nz, table.choice[i].rows, &planes);
+    const double c = double(planes) * table.choice[i].cost;
+    if (i == 0) least = (cells > (1 << 23) ? 0.88 : 0.94) * c;
+    else if (c < least) {
+      least = c;
+      p.choice = i;
+    }
+  }
+  // us a step, small-box / z-marching kernel, FP32 48^3 4.9 / 6.3, 64^3 7.7 / 7.1;
+  // FP64 48^3 5.8 / 6.8, 64^3 10.8 / 10.8
+  p.tiles = cells <= (int64_t(1) << 17);
+  if (p.tiles) p.tile = plan_tiles(nx, ny, nz);
+  // Single steps / pairs, us a step.  In the small-box kernel pairs win where one
+  // round of blocks with tiles of at most 128 cells covers the box: FP32 24^3 3.4 /
+  // 2.5, 32^3 3.6 / 3.2 (porous 4.2 / 3.9), FP16 32^3 3.2 / 2.5, FP64 5.3 / 3.5;
+  // past that only some do (29 x 26 x 46 porous FP32 4.4 / 5.2, box F32X 3.6 / 3.8,
+  // FP64 5.2 / 4.2).  In the z-marching kernel fewer
+  // blocks than 128 leave most CUs idle, and a pass of few planes per block fills
+  // the ring more than it uses it; by storage from the size where no kind of
+  // wall loses more than 2%: FP32 56 x 60 x 72 porous 10.7 / 11.9, 64^3 8.9 / 8.8,
+  // 96^3 24.0 / 23.7; FP64 14.8 / 15.7, 13.2 / 12.8, 57 / 46; BF16 64^3 cavity 7.6
+  // / 8.4, 80^3 18.1 / 14.6; F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33.
+  if (p.tiles) {
+    p.pays = p.tile.nblocks <= kCUs && p.tile.tx * p.tile.ty * p.tile.tz <= 128;
+  } else {
+    const int64_t from = storage == LBM_F32X                              ? 1 << 20
+                         : storage == LBM_F32 || storage == LBM_F64 ? 1 << 18
+                                                                      : 400000;
+    const int rows = table.choice[0].rows;
+    p.pays = cells >= from && int64_t((nx + 63) / 64) * ((ny + rows - 1) / rows) *
+                                      ((nz + p.zc[0] - 1) / p.zc[0]) >= 128;
+  }
+  return p;
+}
+
+}  // namespace lbm
