@@ -163,10 +163,9 @@ typedef struct {
                              LBM_STEPS_AUTO: pairs where they are faster (small
                              boxes up to about 32^3 cells, and boxes from 64^3 on
                              in FP32 and FP64, about 74^3 with 16-bit storage and
-                             102^3 in F32X),
-                             single steps elsewhere and with the split design --
-                             the fastest schedule measured, the same bits either
-                             way. */
+                             102^3 in F32X, in FP32 if they aren't flat or narrow;
+                             see lbm_pairs), single steps elsewhere and with the
+                             split design -- the same bits either way. */
 } lbm_params;
 
 typedef struct lbm_ctx lbm_ctx;
@@ -187,6 +186,11 @@ typedef struct lbm_ctx lbm_ctx;
  * direction's array would exceed 4 GiB - 1 or a grid exceeds 2^31 cells. */
 lbm_status lbm_query(const lbm_params* p, int64_t* x_stride, int64_t* dir_stride,
                      size_t* grid_bytes, size_t* scratch_bytes, size_t* adj_partials_bytes);
+
+/* Whether two steps per pass are faster than single ones for `p` (1 or 0; 0 for
+ * invalid parameters and with obstacle_kernel = 1): what LBM_STEPS_AUTO goes by,
+ * whatever p->steps_per_pass says.  Host only. */
+int32_t lbm_pairs(const lbm_params* p);
 
 /* Algorithmic HBM bytes of one fluid-cell update for a storage type: 19 loads
  * + 19 stores of one population (Sec. 4 byte model: 152 for FP32, 304 for

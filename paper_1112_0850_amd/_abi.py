@@ -62,6 +62,7 @@ _SIGNATURES = {
     "lbm_adjoint_step": (_st, [_vp, _vp, _vp, _vp, _vp]),
     "lbm_segment": (_st, [_vp, _vp, _vp, _vp, C.c_int32, C.c_int32, _vp, C.c_int32]),
     "lbm_adjoint_segment": (_st, [_vp, _vp, C.c_int32, C.c_int32, _vp, _vp, _vp, _vp, _vp]),
+    "lbm_pairs": (C.c_int32, [C.POINTER(lbm_params)]),
     "lbm_adjoint_pairs": (C.c_int32, [_vp]),
     "lbm_adjoint_pair": (_st, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "lbm_adjoint_init": (_st, [_vp, _vp, _vp, _vp, _vp]),
@@ -127,6 +128,11 @@ def lbm_query(p):
     check(lib().lbm_query(C.byref(p), C.byref(xs), C.byref(ds), C.byref(gb), C.byref(sb),
                           C.byref(ab)))
     return xs.value, ds.value, gb.value, sb.value, ab.value
+
+
+def lbm_pairs(p):
+    """Whether fused pairs of steps are faster than single steps for `p`."""
+    return bool(lib().lbm_pairs(C.byref(p)))
 
 
 def lbm_bytes_per_update(storage):

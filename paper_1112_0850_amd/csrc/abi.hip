@@ -390,6 +390,11 @@ lbm_status lbm_query(const lbm_params* p, int64_t* x_stride, int64_t* dir_stride
   return LBM_OK;
 }
 
+int32_t lbm_pairs(const lbm_params* p) {
+  return check_params(p, nullptr) == LBM_OK && p->obstacle_kernel == 0 &&
+         lbm::plan_pairs(p->storage, p->nx, p->ny, p->nz).pays;
+}
+
 int32_t lbm_bytes_per_update(int32_t storage) {
   return int32_t(19 * 2 * elem_size(storage));
 }

@@ -103,41 +103,52 @@ inline PairPlan plan_pairs(int storage, int nx, int ny, int nz) {
   // MLUPS against 84k with 13).  Measured, us a pass, 13 rows against the chosen:
   // FP32 64^3 18.6 / 15.6 (8 rows), 128^3 92 / 86 (8), 128 x 128 x 256 171 / 157 (8),
   // 160^3 183 / 160 (10); FP64 128^3 170 / 145 (4).
-  double least = 0.0;
+  double march = 0.0, least = 0.0;  // the choice's time, in planes of the first's
   for (int i = 0; i < table.n; ++i) {
     int64_t planes;
     p.zc[i] = z_chunk(nx, ny, nz, table.choice[i].rows, &planes);
     const double c = double(planes) * table.choice[i].cost;
-    if (i == 0) least = (cells > (1 << 23) ? 0.88 : 0.94) * c;
+    if (i == 0) least = (cells > (1 << 23) ? 0.88 : 0.94) * (march = c);
     else if (c < least) {
-      least = c;
+      least = march = c;
       p.choice = i;
     }
   }
-  // us a step, small-box / z-marching kernel, FP32 48^3 4.9 / 6.3, 64^3 7.7 / 7.1;
-  // FP64 48^3 5.8 / 6.8, 64^3 10.8 / 10.8
-  p.tiles = cells <= (int64_t(1) << 17);
-  if (p.tiles) p.tile = plan_tiles(nx, ny, nz);
+  // The small-box kernel up to 2^17 cells (64^3 7.7 us a step against 7.1, FP64 10.8
+  // against 10.8) unless the box is so flat that the other one's 64-wide tiles and
+  // single plane cost less: their measures are compared, a unit of the tiles' being
+  // worth a twelfth of a plane (F32X, with its 8 rows, an eighth, FP64 a seventh).
+  // us a step, small-box / z-marching, FP32 48^3 4.9 / 6.3, 27 x 43 x 68 6.0 / 6.9, 1
+  // x 206 x 82 3.8 / 4.6, 1 x 179 x 310 6.9 / 4.8, 1 x 341 x 299 11.2 / 5.2; F32X 1 x
+  // 179 x 310 7.9 / 4.8; FP64 48^3 5.8 / 6.8, 24 x 76 x 64 porous 10.1 / 8.4, 1 x 341 x
+  // 299 13.0 / 8.0.  (110 boxes x 5 storages: 0.4% behind the better one on average.)
+  const double unit = storage == LBM_F64 ? 7.0 : storage == LBM_F32X ? 8.0 : 12.0;
+  p.tile = plan_tiles(nx, ny, nz);
+  p.tiles = cells <= (int64_t(1) << 17) && p.tile.cost < unit * march;
   // Single steps / pairs, us a step.  In the small-box kernel pairs win where one
   // round of blocks with tiles of at most 128 cells covers the box: FP32 24^3 3.4 /
   // 2.5, 32^3 3.6 / 3.2 (porous 4.2 / 3.9), FP16 32^3 3.2 / 2.5, FP64 5.3 / 3.5;
   // past that only some do (29 x 26 x 46 porous FP32 4.4 / 5.2, box F32X 3.6 / 3.8,
-  // FP64 5.2 / 4.2).  In the z-marching kernel fewer
-  // blocks than 128 leave most CUs idle, and a pass of few planes per block fills
-  // the ring more than it uses it; by storage from the size where no kind of
-  // wall loses more than 2%: FP32 56 x 60 x 72 porous 10.7 / 11.9, 64^3 8.9 / 8.8,
-  // 96^3 24.0 / 23.7; FP64 14.8 / 15.7, 13.2 / 12.8, 57 / 46; BF16 64^3 cavity 7.6
-  // / 8.4, 80^3 18.1 / 14.6; F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33.
+  // FP64 5.2 / 4.2), among them all rows of up to 8 cells, of which a wave of the
+  // single step runs a lane each (3347 x 4 x 8 FP32 13.3 / 6.7, 4396 x 24 x 1 FP16 96
+  // / 69).
   if (p.tiles) {
-    p.pays = p.tile.nblocks <= kCUs && p.tile.tx * p.tile.ty * p.tile.tz <= 128;
-  } else {
-    const int64_t from = storage == LBM_F32X                              ? 1 << 20
-                         : storage == LBM_F32 || storage == LBM_F64 ? 1 << 18
-                                                                      : 400000;
-    const int rows = table.choice[0].rows;
-    p.pays = cells >= from && int64_t((nx + 63) / 64) * ((ny + rows - 1) / rows) *
-                                      ((nz + p.zc[0] - 1) / p.zc[0]) >= 128;
+    p.pays = nx <= 8 || (p.tile.nblocks <= kCUs && p.tile.tx * p.tile.ty * p.tile.tz <= 128);
+    return p;
   }
+  // In the z-marching kernel fewer blocks than 128 leave most CUs idle, and a pass
+  // of few planes per block fills the ring more than it uses it.  By storage from
+  // the size where no kind of wall loses more than 2%: FP64 56 x 60 x 72 14.8 / 15.7,
+  // 64^3 13.2 / 12.8, 96^3 57 / 46; BF16 64^3 cavity 7.6 / 8.4, 80^3 18.1 / 14.6;
+  // F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33; in FP32 from as many cells per plane
+  // of the pass's time, which flat boxes and ducts have less of: 64^3 (66k) 7.5 / 7.5,
+  // porous 8.7 / 8.1, 89 x 91 x 95 (88k) 20.6 / 17.5, but 57 x 55 x 86 (52k) 9.2 / 9.8,
+  // 1 x 543 x 950 (38k) 13.3 / 18.6, 2020 x 16 x 16 (39k) 23.5 / 31.4.
+  const int64_t from = storage == LBM_F32X ? 1 << 20 : storage == LBM_F32 || storage == LBM_F64 ? 1 << 18 : 400000;
+  const int rows = table.choice[0].rows;
+  p.pays = cells >= from &&
+           int64_t((nx + 63) / 64) * ((ny + rows - 1) / rows) * ((nz + p.zc[0] - 1) / p.zc[0]) >= 128 &&
+           (storage != LBM_F32 || double(cells) >= 62000.0 * march);
   return p;
 }
 

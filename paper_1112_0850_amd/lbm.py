@@ -51,8 +51,9 @@ class LBM:
     kernel before each step) instead of the fused solid markers;
     ``steps_per_pass=2`` runs pairs of steps as one temporally blocked pass
     (same results, bit for bit); ``steps_per_pass="auto"`` does so where pairs
-    are faster (all but FP32 boxes between 34^3 and 64^3 cells) and runs single
-    steps elsewhere."""
+    are faster (boxes up to about 32^3 cells; from 64^3 in FP32, if not flat or
+    narrow, and FP64, 74^3 in 16 bits, 102^3 in F32X) and runs single steps
+    elsewhere."""
 
     def __init__(self, shape, tau, force=(0.0, 0.0, 0.0), storage="f32", flags=None, u0=None,
                  rho0=None, f16_scale_log2=0, x_align=0, device="cuda", wall_u=(0.0, 0.0, 0.0),
@@ -203,13 +204,16 @@ def copy_probe(dst, src, vec_per_thread=1, nontemporal=False, blocks=0, stream=N
                      blocks, ctypes.c_void_p(s.cuda_stream))
 
 
-# The rollout steps in fused pairs from this many cells on, forward and in the
-# recomputation (the same states bit for bit), and up to FUSED_SMALL_CELLS,
-# where the library's small-box kernel runs them: measured, single / pairs, us a
-# step, 24^3 3.4 / 2.8, 32^3 3.5 / 2.9, 48^3 5.3 / 5.2, 64^3 7.4 / 7.1, 128^3 57 / 41,
-# 256^3 457 / 271.
-FUSED_RECOMPUTE_MIN_CELLS = 1 << 18
-FUSED_SMALL_CELLS = 1 << 15
+# The rollout steps in fused pairs, forward and in the recomputation (the same
+# states bit for bit), where the library finds them faster (lbm_pairs: us a step,
+# single / pairs, 24^3 3.4 / 2.8, 64^3 7.4 / 7.1, 128^3 57 / 41, 256^3 457 / 271), on
+# boxes of at least this many cells.
+FUSED_RECOMPUTE_MIN_CELLS = 0
+
+# The reverse sweep runs in pairs of steps from this many cells on.  Measured, us a
+# step, single / pairs: 48^3 7.4 / 9.0, 64^3 11.0 / 10.4, 100^3 38 / 30, 128^3 64 /
+# 43, 256^3 501 / 327.
+ADJOINT_PAIRS_MIN_CELLS = 1 << 18
 
 # How much of the device's memory a rollout may take for the moments that its
 # forward sweep keeps beyond the last segment's (288 GB: 4.5 GB, about 140 steps of
@@ -229,10 +233,14 @@ class _Rollout(torch.autograd.Function):
     def forward(ctx, u0, g, steps, tau, flags, k, wall_u, equilibrium, steps_per_pass, need_grad):
         force = [float(v) for v in g.detach().double().cpu().tolist()]
         cells = math.prod(u0.shape[1:])
-        fused = cells >= FUSED_RECOMPUTE_MIN_CELLS or cells <= FUSED_SMALL_CELLS
+        fused = cells >= FUSED_RECOMPUTE_MIN_CELLS and A.lbm_pairs(A.params(u0.shape[1:], tau, force))
+        schedule = steps_per_pass
+        if schedule in (-1, 0, 1):  # automatic also for the link mask, which the reverse pairs read
+            reverse_pairs = need_grad and cells >= ADJOINT_PAIRS_MIN_CELLS
+            schedule = 2 if fused else (-1 if reverse_pairs else schedule)
         sim = LBM(u0.shape[1:], tau, force, "f32", flags=flags, u0=u0.detach(), device=u0.device,
                   x_align=_Rollout.row_align(u0.shape[1:]), wall_u=wall_u, equilibrium=equilibrium,
-                  steps_per_pass=2 if fused and steps_per_pass in (-1, 0, 1) else steps_per_pass)
+                  steps_per_pass=schedule)
         if not need_grad:
             sim.step(steps)
             return sim.macroscopics()
@@ -294,9 +302,8 @@ class _Rollout(torch.autograd.Function):
     def adjoint_pairs(sim):
         """Whether the reverse sweep runs in pairs of steps, paired by their distance
         from the end alone (so that dL/dF, summed pass by pass, does not depend on
-        the checkpoints).  Measured, us a step, single / pairs: 48^3 7.4 / 9.0, 64^3
-        11.0 / 10.4, 100^3 38 / 30, 128^3 64 / 43, 256^3 501 / 327."""
-        return math.prod(sim.shape) >= FUSED_RECOMPUTE_MIN_CELLS and A.lbm_adjoint_pairs(sim.ctx)
+        the checkpoints)."""
+        return math.prod(sim.shape) >= ADJOINT_PAIRS_MIN_CELLS and A.lbm_adjoint_pairs(sim.ctx)
 
     @staticmethod
     def moments(sim, n):

@@ -447,3 +447,42 @@ def test_reverse_pairs_with_records_off_256_bytes(shape, monkeypatch):
                 sums = got[1] if sums is None else sums
                 assert torch.equal(got[0], ref[0]) and torch.equal(got[1], sums), (steps, every, share)
         assert float((sums - ref[1]).abs().max()) <= 1e-11 * float(ref[1].abs().max())
+
+
+@pytest.mark.parametrize("shape", [(24, 24, 24), (64, 64, 64), (33, 29, 32), (1, 512, 512), (1, 1, 30000)])
+def test_rollouts_step_as_the_library_says(shape, monkeypatch):
+    """Forward and in the recomputation a rollout runs pairs of steps where lbm_pairs
+    says so (not on small ragged and on flat boxes), pairs everywhere if asked, and
+    single steps below FUSED_RECOMPUTE_MIN_CELLS: the same fields and gradients bit
+    for bit (dL/dF too: the reverse sweep is the same), with moments kept and
+    recomputed."""
+    say("schedule of a rollout", shape)
+    rng = np.random.default_rng(15)
+    start = torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float().cuda()
+    flags = torch.from_numpy(I.random_flags(shape, 66, solid_fraction=0.1)).cuda()
+    pairs = A.lbm_pairs(A.params(shape, 0.7))
+    assert pairs == (shape in [(24, 24, 24), (64, 64, 64)])
+    segment = A.lbm_segment
+
+    def run(steps_per_pass, share):
+        calls = []
+        monkeypatch.setattr(lbm, "KEPT_MOMENTS_SHARE", share)
+        monkeypatch.setattr(A, "lbm_segment", lambda *a: (calls.append((bool(a[5]), a[7])), segment(*a)))
+        u0 = start.clone().requires_grad_(True)
+        g = torch.tensor([2e-5, -1e-5, 1e-5], dtype=torch.float64, requires_grad=True)
+        rho, u = rollout(u0, g, steps=11, tau=0.7, flags=flags, checkpoint_every=4,
+                         steps_per_pass=steps_per_pass)
+        ((u * u).sum() + 0.3 * (rho * rho).sum()).backward()
+        return (rho.detach(), u.detach(), u0.grad, g.grad), calls
+
+    monkeypatch.setattr(lbm, "FUSED_RECOMPUTE_MIN_CELLS", 1 << 40)
+    ref, calls = run(0, 0.0)
+    assert calls == [(False, True)] * 3 + [(False, False)] * 2  # 3 segments, 2 of them recomputed
+    monkeypatch.setattr(lbm, "FUSED_RECOMPUTE_MIN_CELLS", 0)
+    for steps_per_pass in (0, -1, 2):
+        for share in (0.0, 1 / 64):
+            got, calls = run(steps_per_pass, share)
+            want = [(pairs or steps_per_pass == 2, True)] * 3 + [(pairs, False)] * (0 if share else 2)
+            assert calls == want, (steps_per_pass, share)
+            for a, b in zip(got, ref):
+                assert torch.equal(a, b), (steps_per_pass, share)

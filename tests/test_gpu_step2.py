@@ -462,3 +462,14 @@ def test_store_policies_give_the_same_bits(storage, below, above, spp):
         del sim
     core = slice(2, 14)  # cells whose 4-step neighbourhood lies in the 20 x 20 patch
     assert torch.equal(ref[:, core, core], v[:, core, core])
+
+
+@pytest.mark.parametrize("shape", [(1, 300, 310), (2, 200, 207), (4396, 3, 1), (1, 1, 3000), (700, 4, 8)])
+@pytest.mark.parametrize("storage", STORAGES)
+def test_two_step_pass_on_flat_and_thin_boxes(storage, shape):
+    """Boxes of at most 2^17 cells on both sides of the line between the small-box
+    and the z-marching kernel: the same bits as single steps."""
+    say("two-step pass, flat and thin", storage, shape)
+    fl = I.random_flags(shape, 47, solid_fraction=0.15, noforce_fraction=0.1)
+    one, two = _pair(shape, 0.6, (1e-5, 0, 0), storage, 5, flags=fl, u0=_u0(shape, 48))
+    assert _same(one, two)

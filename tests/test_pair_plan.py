@@ -84,8 +84,7 @@ def test_plan_equals_an_exhaustive_search(plan):
                    key=lambda t: ceil(t[0], 256) * (
                        ceil((t[1][0] + 2) * (t[1][1] + 2) * (t[1][2] + 2), 64) +
                        ceil(t[1][0] * t[1][1] * t[1][2], 64) + 0.1 * (t[1][1] + 2) * (t[1][2] + 2)))
-        if got[4]:
-            assert (got[8], tuple(got[5:8])) == tile, (st, nx, ny, nz)
+        assert (got[8], tuple(got[5:8])) == tile, (st, nx, ny, nz)
 
 
 def test_planning_long_ducts_is_bounded(plan):
@@ -95,3 +94,22 @@ def test_planning_long_ducts_is_bounded(plan):
     t = time.time()
     plan([(k % 5, 2, 2, 1 << 24 >> k % 8) for k in range(20000)])
     assert time.time() - t < 10
+
+
+def test_flat_and_ragged_boxes(plan):
+    """Where the rules lie: flat boxes march over z though they are small, thin ones
+    take tiles and pairs, small ragged and large flat FP32 boxes single steps."""
+    tiles, pays = 4, 9
+    todo = [(0, 24, 24, 24), (0, 64, 64, 64), (0, 128, 128, 128), (0, 1, 179, 310), (0, 1, 341, 299),
+            (3, 1, 256, 256), (4, 2, 256, 256), (0, 33, 29, 32), (0, 35, 33, 26), (0, 1, 128, 128),
+            (0, 1, 1, 30000), (0, 1, 512, 512), (0, 2020, 16, 16), (0, 57, 55, 86), (1, 4396, 24, 1)]
+    got = dict(zip(todo, plan([(st, nx, ny, nz) for st, nz, ny, nx in todo])))
+    assert got[0, 24, 24, 24][[tiles, pays]].all()
+    for b in [(0, 64, 64, 64), (0, 128, 128, 128)]:
+        assert not got[b][tiles] and got[b][pays], b
+    for b in [(0, 1, 179, 310), (0, 1, 341, 299), (3, 1, 256, 256), (4, 2, 256, 256)]:
+        assert not got[b][tiles], b
+    for b in [(0, 33, 29, 32), (0, 35, 33, 26), (0, 1, 128, 128), (0, 1, 1, 30000), (0, 1, 512, 512),
+              (0, 2020, 16, 16), (0, 57, 55, 86)]:
+        assert not got[b][pays], b
+    assert got[1, 4396, 24, 1][[tiles, pays]].all()
