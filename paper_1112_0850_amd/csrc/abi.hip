@@ -183,8 +183,10 @@ lbm_status noalloc_scratch_here(int* dev_out, double** out) {
 //  - up to 340 MiB where rows end on a 64-byte sector (128^3 FP32, 319 MB, 65 / 62;
 //    96^3 FP64, 359 MB, 57 / 56; 121 x 170 x 128 F32X, 400 MB, 80 / 83), up to 290
 //    where a row's last sector is written in part (85 x 115 x 181 FP32, 285 MB, 62
-//    / 56; 81 x 171 x 189 F32X, 404 MB, 80 / 103), with solids in 16 bits up to 272
-//    (98 x 211 x 241 FP16 porous, 402 MB, 91 / 110; 147 x 149 x 183, 320 MB, 74 / 85);
+//    / 56; 81 x 171 x 189 F32X, 404 MB, 80 / 103), up to 272 with solids in 16 bits
+//    (98 x 211 x 241 FP16 porous, 402 MB, 91 / 110; 147 x 149 x 183, 320 MB, 74 / 85)
+//    and where at least half of the rows' pitch is padding, which leaves lines of the
+//    cache unused (1000 x 64 x 16 FP64, 311 MB, 92 / 98);
 //  - but not in boxes of about the size of the L2s (8 x 4 MB) where few lanes are
 //    idle (rows that fill 78% of their units) or reload at moving walls: with plain
 //    stores the pulls and reloads find less there.  F32X spheres 5 x 78 x 336 (20
@@ -199,9 +201,10 @@ lbm_status noalloc_scratch_here(int* dev_out, double** out) {
 struct Megabytes {
   double from, to;
 };
-// Megabytes of the 128-byte lines that the rows of both grids take.
+// Bytes of the 128-byte lines that a row takes, and megabytes of both grids' rows.
+size_t cache_row(const lbm::Plan& g, size_t es) { return (size_t(g.nx) * es + 127) / 128 * 128; }
 double cache_megabytes(const lbm::Plan& g, size_t es) {
-  return 2e-6 * lbm::Q * double((size_t(g.nx) * es + 127) / 128 * 128) * g.nrows;
+  return 2e-6 * lbm::Q * double(cache_row(g, es)) * g.nrows;
 }
 // reloads: solid cells, whose neighbours load their own cell's slots
 bool cached_stores(const lbm::Plan& g, int32_t storage, size_t es, bool reloads, bool moving) {
@@ -220,7 +223,8 @@ bool cached_stores(const lbm::Plan& g, int32_t storage, size_t es, bool reloads,
     if (storage == LBM_F64) not_in = {13, 21};
   }
   if (mb >= not_in.from && mb < not_in.to) return false;
-  const int most = reloads && es == 2 ? 272 : (size_t(g.nx) * es % 64 ? 290 : 340);
+  const bool sparse = 2 * cache_row(g, es) <= size_t(g.xs) * es;
+  const int most = sparse || (reloads && es == 2) ? 272 : (size_t(g.nx) * es % 64 ? 290 : 340);
   return mb <= most * 1.048576;
 }
 
