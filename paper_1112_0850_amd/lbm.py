@@ -218,7 +218,8 @@ ADJOINT_PAIRS_MIN_CELLS = 1 << 18
 # How much of the device's memory a rollout may take for the moments that its
 # forward sweep keeps beyond the last segment's (288 GB: 4.5 GB, about 140 steps of
 # 128^3).  Kept, a step's moments cost the pass that runs anyway 5 us at 128^3;
-# recomputed, half of a 95 us pass.
+# recomputed, half of a 95 us pass.  Rollouts that wait for their backward together
+# take no more than half of the memory in this way.
 KEPT_MOMENTS_SHARE = 1 / 64
 
 
@@ -248,7 +249,7 @@ class _Rollout(torch.autograd.Function):
         starts = range(0, steps, k)  # the segments of k steps
         last = len(starts) - 1
         first = _Rollout.first_kept(sim, steps, k)
-        cur, spare, tmp = sim.grids[0], None, sim.new_grid()
+        cur, spare, tmp = sim.grids[0], None, _Rollout.second_grid(sim, min(k, steps), pairs)
         ckpts, moms = [], []
         for s, t in enumerate(starts):
             if s < first:
@@ -268,7 +269,7 @@ class _Rollout(torch.autograd.Function):
         sim.set_current(0 if cur is sim.grids[0] else 1, steps)
         rho, u = sim.macroscopics()
         ctx.sim, ctx.ckpts, ctx.steps, ctx.k = sim, ckpts, steps, k
-        ctx.tmp, ctx.moms, ctx.fused = tmp, moms, fused
+        ctx.moms, ctx.fused = moms, fused
         ctx.g_meta = (g.dtype, g.device)
         return rho, u
 
@@ -286,17 +287,27 @@ class _Rollout(torch.autograd.Function):
 
     @staticmethod
     def first_kept(sim, steps, k):
-        """The first segment whose moments the forward sweep keeps: as many of the
-        latest ones as fit in KEPT_MOMENTS_SHARE of the device's memory, but the
-        last one alone where less than half of that memory is free."""
-        last = (steps - 1) // k
-        if last == 0:
+        """The first segment whose moments the forward sweep keeps: the last one and
+        as many before it as fit in KEPT_MOMENTS_SHARE of the device's memory, if
+        half of that memory stays free (blocks that torch holds unused count as
+        free).  Else none: the rollout then holds its checkpoints only."""
+        last, record = (steps - 1) // k, 16 * sim.dir_stride  # bytes of a step's moments
+        least = (steps - last * k) * record
+        if last == 0 and least < 1 << 26:  # not worth asking
             return 0
         free, total = torch.cuda.mem_get_info(sim.device)
-        if 2 * free < total:
-            return last
-        fit = int(KEPT_MOMENTS_SHARE * total) // (16 * sim.dir_stride)  # steps
-        return min(last, max(0, -((fit - steps) // k)))
+        room = max(least, int(KEPT_MOMENTS_SHARE * total))
+        if free - total // 2 < room:
+            free += torch.cuda.memory_reserved(sim.device) - torch.cuda.memory_allocated(sim.device)
+        fit = min(room, free - total // 2)
+        if fit < least:
+            return last + 1
+        return min(last, max(0, -((fit // record - steps) // k)))
+
+    @staticmethod
+    def second_grid(sim, n, pairs):
+        """The other grid of a segment of n steps, unless one pass does."""
+        return sim.new_grid() if n > (2 if pairs else 1) else None
 
     @staticmethod
     def adjoint_pairs(sim):
@@ -324,7 +335,7 @@ class _Rollout(torch.autograd.Function):
         gu = None if g_u is None else g_u.to(torch.float32).contiguous()
         record = 4 * sim.dir_stride
         pairs = _Rollout.adjoint_pairs(sim)
-        cur, mom, left = 0, None, None  # left: a state whose reverse step waits for the next pair
+        cur, mom, tmp, left = 0, None, None, None  # left: a state that waits for the next pair
         for s in range(len(moms) - 1, -1, -1):
             seed = s == len(moms) - 1
             n = min(k, steps - s * k)
@@ -332,10 +343,11 @@ class _Rollout(torch.autograd.Function):
             if seg is None:
                 if mom is None:
                     mom = _Rollout.moments(sim, k)
+                    tmp = _Rollout.second_grid(sim, k, ctx.fused)
                 elif left is not None:
                     left = left.clone()
                 seg = mom
-                A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(ctx.tmp), _ptr(sim.grids[1]), n,
+                A.lbm_segment(sim.ctx, _ptr(ckpts[s]), _ptr(tmp), _ptr(sim.grids[1]), n,
                               ctx.fused, _ptr(seg), False)
             if not pairs:
                 A.lbm_adjoint_segment(sim.ctx, _ptr(seg), n, seed, _ptr(gr), _ptr(gu),
@@ -373,10 +385,12 @@ def rollout(u0, g, *, steps, tau, flags=None, checkpoint_every=20, wall_u=(0.0, 
     equilibrium are supported (no gradient for the wall velocity).
     ``steps_per_pass=2`` runs the forward sweep in fused pairs of steps on
     every box, not only where they are faster (the same states bit for bit, so
-    the same gradients).  The reverse sweep needs 16 B per cell of every state:
-    those of the latest steps are kept, up to 1/64 of the device's memory while
-    half of it is free, the others recomputed from checkpoints every
-    ``checkpoint_every`` steps (the gradients are the same for any spacing)."""
+    the same gradients).  The reverse sweep needs 16 B per cell of every state.
+    Until its backward a rollout holds two grids of 76 B per cell, those 16 B of
+    the last ``checkpoint_every`` steps, of earlier ones up to 1/64 of the device's
+    memory, and a grid for every further ``checkpoint_every`` steps, from which the
+    others are recomputed; if that left less than half of the memory free, it holds
+    the grids only.  (The gradients are the same either way and for any spacing.)"""
     if u0.dim() != 4 or u0.shape[0] != 3:
         raise ValueError("u0 must be [3, nz, ny, nx]")
     if g.numel() != 3:

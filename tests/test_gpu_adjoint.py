@@ -486,3 +486,56 @@ def test_rollouts_step_as_the_library_says(shape, monkeypatch):
             assert calls == want, (steps_per_pass, share)
             for a, b in zip(got, ref):
                 assert torch.equal(a, b), (steps_per_pass, share)
+
+
+@pytest.mark.parametrize("shape", [(24, 20, 39), (64, 64, 64)])
+@pytest.mark.parametrize("steps,every", [(1, 1), (5, 1), (5, 2), (11, 4), (7, 20)])
+def test_rollout_holds_grids_only_when_memory_is_short(shape, steps, every, monkeypatch):
+    """With less than half of the memory free a rollout keeps no moments and no more
+    grids than one per segment and one more; blocks that torch's allocator holds
+    unused count as free.  The gradients are those with everything kept."""
+    say("memory of a rollout", shape, steps, every)
+    rng = np.random.default_rng(16)
+    start = torch.from_numpy(0.03 * (rng.random((3,) + shape) - 0.5)).float().cuda()
+    total = torch.cuda.mem_get_info()[1]
+    kept = []
+    first_kept = lbm._Rollout.first_kept
+    monkeypatch.setattr(lbm._Rollout, "first_kept", staticmethod(
+        lambda *a: (kept.append(first_kept(*a)), kept[-1])[1]))
+
+    def run(free, cached):
+        with monkeypatch.context() as m:
+            if free is not None:
+                m.setattr(torch.cuda, "mem_get_info", lambda device=None: (free, total))
+                m.setattr(torch.cuda, "memory_reserved", lambda device=None: cached)
+                m.setattr(torch.cuda, "memory_allocated", lambda device=None: 0)
+                m.setattr(lbm, "KEPT_MOMENTS_SHARE", 1 / 64)
+            u0 = start.clone().requires_grad_(True)
+            g = torch.tensor([2e-5, -1e-5, 1e-5], dtype=torch.float64, requires_grad=True)
+            rho, u = rollout(u0, g, steps=steps, tau=0.7, checkpoint_every=every)
+            ((u * u).sum() + 0.3 * (rho * rho).sum()).backward()
+            return u0.grad, g.grad
+
+    ref = run(None, 0)
+    segments = -(-steps // every)
+    assert kept == [0]
+    for free, cached, first in ((total, 0, 0), (total // 2, 0, segments), (total // 4, total // 2, 0)):
+        if segments == 1 and 16 * steps * 64 * 64 * 64 < 1 << 26:
+            first = 0  # less than 64 MB: not worth asking
+        del kept[:]
+        got = run(free, cached)
+        assert kept == [first], (free, cached)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), (free, cached)
+    # what is held between forward and backward, in grids
+    sim = LBM(shape, 0.7, storage="f32", x_align=lbm._Rollout.row_align(shape))
+    grid, fields = sim.grid_bytes, 4 * 4 * start[0].numel()
+    del sim
+    monkeypatch.setattr(lbm._Rollout, "first_kept", staticmethod(lambda *a: segments))
+    u0 = start.clone().requires_grad_(True)
+    g = torch.zeros(3, dtype=torch.float64, requires_grad=True)
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    out = rollout(u0, g, steps=steps, tau=0.7, checkpoint_every=every)
+    held = torch.cuda.memory_allocated() - before - fields
+    assert held <= (segments + 1) * (grid + 512) + (8 << 20), held / grid
+    del out
