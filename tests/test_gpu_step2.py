@@ -197,6 +197,30 @@ def test_link_mask_content():
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 5), (2, 3, 1), (1, 9, 70), (5, 2, 65)])
+def test_link_mask_of_short_axes_with_moving_walls(shape):
+    """The link mask where an axis is one or two cells long, so that both
+    neighbours wrap, with moving walls: bit 21 some link
+    to a moving cell, bit 22 the cell itself."""
+    rng = np.random.default_rng(5)
+    solid, moving = rng.random(shape) < 0.4, rng.random(shape) < 0.5
+    fl = (solid * 1 | (solid & moving) * 4).astype(np.uint8)
+    fl.flat[0] = 5
+    solid, moving = (fl & 1) == 1, (fl & 4) == 4
+    sim = LBM(shape, 0.6, (1e-5, 0, 0), "f32", flags=fl, wall_u=(0.02, 0.01, 0), steps_per_pass=2)
+    torch.cuda.synchronize()
+    cells = int(np.prod(shape))
+    off = (1024 * 5 * 8 + 255) // 256 * 256
+    got = sim.scratch.view(torch.uint8)[off:off + 4 * cells].view(torch.int32).cpu().numpy()
+    e, _, _ = O.lattice()
+    want = np.where(solid, 1 << 19, 0) | np.where(moving, 1 << 22, 0)
+    for i in range(1, 19):
+        cx, cy, cz = (int(v) for v in e[i])
+        src, to = (np.roll(a, (cz, cy, cx), axis=(0, 1, 2)) for a in (solid, moving))
+        want |= np.where(src, 1 << i, 0) | np.where(to, 1 << 21, 0)
+    assert np.array_equal(got.view(np.uint32).reshape(shape), want.astype(np.uint32))
+
+
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 def test_two_step_pass_with_graph_replays(storage):
     """Graphs of 6 steps (three fused passes: the replay ends on the other
