@@ -136,19 +136,30 @@ inline PairPlan plan_pairs(int storage, int nx, int ny, int nz) {
     p.pays = nx <= 8 || (p.tile.nblocks <= kCUs && p.tile.tx * p.tile.ty * p.tile.tz <= 128);
     return p;
   }
-  // In the z-marching kernel fewer blocks than 128 leave most CUs idle, and a pass
-  // of few planes per block fills the ring more than it uses it.  By storage from
-  // the size where no kind of wall loses more than 2%: FP64 56 x 60 x 72 14.8 / 15.7,
-  // 64^3 13.2 / 12.8, 96^3 57 / 46; BF16 64^3 cavity 7.6 / 8.4, 80^3 18.1 / 14.6;
-  // F32X porous 96^3 24.5 / 25.7, 112^3 37 / 33; in FP32 from as many cells per plane
-  // of the pass's time, which flat boxes and ducts have less of: 64^3 (66k) 7.5 / 7.5,
-  // porous 8.7 / 8.1, 89 x 91 x 95 (88k) 20.6 / 17.5, but 57 x 55 x 86 (52k) 9.2 / 9.8,
-  // 1 x 543 x 950 (38k) 13.3 / 18.6, 2020 x 16 x 16 (39k) 23.5 / 31.4.
-  const int64_t from = storage == LBM_F32X ? 1 << 20 : storage == LBM_F32 || storage == LBM_F64 ? 1 << 18 : 400000;
+  // In the z-marching kernel a pass that is short of blocks leaves CUs idle, and one
+  // of few planes per block fills the ring more than it uses it.  Both are in the
+  // plan's measure, so pairs run from as many cells per plane of the pass's time as
+  // single steps are worth.  Measured, us a step, single / pairs:
+  //   FP32 62000: 64^3 (66k) 7.5 / 7.5, porous 8.7 / 8.1, 89 x 91 x 95 (88k) 20.6 /
+  //     17.5, but 57 x 55 x 86 (52k) 9.2 / 9.8, 1 x 543 x 950 (38k) 13.3 / 18.6, 2020 x
+  //     16 x 16 (39k) 23.5 / 31.4.
+  //   FP64 24000: 4 x 175 x 328 (29k) 13.0 / 11.3, 4 x 121 x 477 (34k) 12.5 / 11.0, but
+  //     1 x 804 x 336 (14k) 13.8 / 17.2; between solids pairs gain less, 8 x 250 x 135
+  //     (26k) porous 15.1 / 17.8; in boxes above the memory-side cache 15000: 2 x 697 x
+  //     717 (24k) 61.9 / 43.7, 1 x 1226 x 3328 (16k) 245.1 / 232.3.
+  //   16 bits 62000: 3 x 204 x 603 (71k) 7.7 / 7.9, along a moving lid 17.4 / 12.2, 8 x
+  //     288 x 239 (93k) 10.5 / 9.3, but 2 x 397 x 529 (52k) porous 11.0 / 12.1, 1 x 445
+  //     x 1536 (37k) 11.0 / 18.0; above 2^20 cells 78000, as the halos of flat tiles
+  //     then cost more: 3 x 381 x 1728 (76k) lid 37.0 / 52.3, 6 x 527 x 411 (97k) 19.1
+  //     / 16.0.
+  // F32X pays from 2^20 cells and 128 blocks: porous 96^3 24.5 / 25.7, 112^3 37 / 33.
   const int rows = table.choice[0].rows;
-  p.pays = cells >= from &&
-           int64_t((nx + 63) / 64) * ((ny + rows - 1) / rows) * ((nz + p.zc[0] - 1) / p.zc[0]) >= 128 &&
-           (storage != LBM_F32 || double(cells) >= 62000.0 * march);
+  const int64_t blocks = int64_t((nx + 63) / 64) * ((ny + rows - 1) / rows) * ((nz + p.zc[0] - 1) / p.zc[0]);
+  const double each = double(cells) / march;
+  p.pays = storage == LBM_F64    ? each >= (cells * 304 > (int64_t(256) << 20) ? 15000.0 : 24000.0)
+           : storage == LBM_F32X ? cells >= (1 << 20) && blocks >= 128
+           : storage == LBM_F32  ? cells >= (1 << 18) && blocks >= 128 && each >= 62000.0
+                                 : each >= (cells > (1 << 20) ? 78000.0 : 62000.0);
   return p;
 }
 

@@ -113,3 +113,16 @@ def test_flat_and_ragged_boxes(plan):
               (0, 2020, 16, 16), (0, 57, 55, 86)]:
         assert not got[b][pays], b
     assert got[1, 4396, 24, 1][[tiles, pays]].all()
+
+
+def test_flat_boxes_by_cells_per_plane_of_the_pass(plan):
+    """FP64 and 16-bit pairs pay by the cells per plane of the pass's time, so not in
+    single planes of any size, and in flat boxes below the size that a cube needs."""
+    pays = 9
+    yes = [(3, 2, 1000, 650), (3, 4, 175, 328), (3, 4, 121, 477), (3, 1, 1226, 3328),
+           (1, 3, 204, 603), (2, 3, 326, 389),
+           (1, 6, 527, 411), (1, 128, 128, 128), (2, 512, 512, 512), (3, 64, 64, 64), (3, 512, 512, 512)]
+    no = [(3, 1, 804, 336), (3, 1, 664, 723), (1, 1, 445, 1536), (2, 1, 1226, 3328), (1, 2, 397, 529),
+          (2, 3, 381, 1728), (1, 1, 1351, 592)]
+    got = plan([(st, nx, ny, nz) for st, nz, ny, nx in yes + no])[:, pays]
+    assert got[:len(yes)].all() and not got[len(yes):].any(), list(zip(yes + no, got))
