@@ -32,7 +32,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1112_0850_amd", "csrc", f)
-               for f in ("kernels.hip", "kernels.h", "d3q19.h", "abi.hip")]
+               for f in ("kernels.hip", "kernels.h", "pair_plan.h", "d3q19.h", "abi.hip")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_porous512_f32.json")
 
 
@@ -827,8 +827,8 @@ def roofline_of(key, leg):
         out["traffic_over_alg"] = out["traffic"] / out["alg_bytes_per_launch"]
     if spl == 2:
         out["note"] = ("algorithmic bytes of two single-step updates (the intermediate level stays "
-                       "in LDS, so the kernel's HBM traffic is below them); the pass is bound by "
-                       "latency and instruction issue, not by HBM")
+                       "in LDS, so the kernel's HBM traffic is below them); the pass waits for "
+                       "its pulls and stores, and its traffic runs below the copy's rate")
     return out
 
 

@@ -1069,9 +1069,10 @@ __global__ __launch_bounds__(64 * (TY + 3)) void k_step2(
 // per thread) from src, all 19 results of each cell into LDS, one barrier, step
 // 2 on the tile from there.  Both are the single step's pull, marker test,
 // collision and rounding, so the result has the same bits.  Halo cells are
-// computed by every tile that needs them (2 to 3 times the tile's own work, so
-// only for small boxes: 64^3 FP32 runs 7.1 us a step in z-marching tiles, 7.7
-// here).  Bound by latency and the collisions' issue: 32^3 FP32 2.9 us a step
+// computed by every tile that needs them (with them step 1 is 2.07 to 3.75 times
+// the tile's cells, by the tile's shape, so only for small boxes: 64^3 FP32 runs
+// 7.1 us a step in z-marching tiles, 7.7 here).  Bound by latency and the
+// collisions' issue: 32^3 FP32 2.9 us a step
 // against 3.3-4.1 single, 24^3 2.8 against 3.3-4.1, 48^3 FP64 5.8 against 7.6.
 // ---------------------------------------------------------------------------
 constexpr int kTileThreads = 512;  // of a block; at most as many tile cells, and twice as many with the halo
